@@ -1,7 +1,9 @@
-"""ctypes binding of liblq.so: same names as the C entry points, argument marshalling only.
+"""Binding of liblq.so: same names as the C entry points, argument marshalling only.
 
 torch is used for device memory (inputs, outputs, workspaces) and for the current
-stream handle; every arithmetic step runs inside the library's kernels.
+stream handle; every arithmetic step runs inside the library's kernels.  The calls that a
+query makes hand their arguments to the native marshalling of ``_lqpy.so``; the others
+(yardsticks, size queries, group discovery, incremental updates) go through ctypes.
 """
 from __future__ import annotations
 
@@ -182,6 +184,12 @@ def _load():
 
 _lib = _load()
 
+try:
+    from . import _lqpy
+except ImportError as e:
+    raise ImportError("_lqpy.so is missing or does not load: build it with `python -m paper_2306_08367_amd.build`") from e
+_lqpy.set_error_class(LQError)
+
 
 def lq_last_error() -> str:
     return _lib.lq_last_error().decode()
@@ -299,21 +307,7 @@ def lq_project_dims(dims: Sequence[torch.Tensor], W0: torch.Tensor, c_f: int,
     """P_k = D_k times its rows of W0 (pre-fusion stage).  Allocates P unless given: in the model's element type
     unless p_dtype says otherwise (the specialised kernels of the join stage take tables of the model's type;
     fp32 tables under a bf16 model run on the shape-agnostic kernel, several times slower)."""
-    if P is None:
-        # rows start 16 bytes apart at the least (the stride is padded to 4 floats / 8 bf16 values): the fast kernels of
-        # the join stage then take any hidden width, the padding is never read as data
-        pd = p_dtype or W0.dtype
-        per16 = 4 if pd == torch.float32 else 8
-        l1 = int(W0.shape[1])
-        ld = (l1 + per16 - 1) // per16 * per16
-        P = [_empty(stream, (d.shape[0], ld), dtype=pd, device=d.device)[:, :l1] for d in dims]
-    fact = lq_mat(None, 0, int(c_f), max(int(c_f), 1), _dtype_code(W0))
-    dims_arr = _mat_array(dims)
-    star = lq_star(0, fact, len(dims), dims_arr, _ptr_array([None] * len(dims)))
-    model = _Model([W0], None)
-    P_arr = _mat_array(P)
-    _check(_lib.lq_project_dims(ctypes.byref(star), ctypes.byref(model.c), P_arr, _stream(stream)))
-    return P
+    return _lqpy.project_dims(dims, W0, c_f, P, p_dtype, stream)
 
 
 def lq_fused_join_predict(X: Optional[torch.Tensor], fks: Sequence[torch.Tensor],
@@ -322,30 +316,7 @@ def lq_fused_join_predict(X: Optional[torch.Tensor], fks: Sequence[torch.Tensor]
                           Y: Optional[torch.Tensor] = None, y_dtype: Optional[torch.dtype] = None,
                           flags: int = 0, ws: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Y = MLP(x W_f + sum_k P_k[fk_k]) without forming the joined table."""
-    n = _n_of(X, fks)
-    dev = weights[0].device
-    if Y is None:
-        Y = _empty(stream, (n, weights[-1].shape[1]), dtype=y_dtype or weights[0].dtype, device=dev)
-    star = _Star(n, X, None, fks)
-    model = _Model(weights, biases)
-    if ws is None and n > 0 and len(weights) >= 2 and (max(int(w.shape[1]) for w in weights) > 128 or
-                                                       (X is not None and X.shape[1] > 16)):
-        # a model that the fused kernels may not take (a layer wider than 128, more than 16 fact columns): room for the
-        # layered form (activations of a chunk of rows, at most a quarter of a gigabyte); the library uses it only if
-        # it needs to
-        per_row = int(_lib.lq_workspace_bytes(LQ_CALL_FUSED, ctypes.byref(star.c), ctypes.byref(model.c), 256) - 256) // 256
-        rows = max(4096, min(n, (256 << 20) // max(per_row, 1)))
-        ws = _empty(stream, int(_lib.lq_workspace_bytes(LQ_CALL_FUSED, ctypes.byref(star.c), ctypes.byref(model.c), rows)),
-                    dtype=torch.uint8, device=dev)
-    if ws is None and (flags & LQ_CHECK_FKS):
-        ws = _empty(stream, 256, dtype=torch.uint8, device=dev)
-    P_arr = _mat_array(P)
-    Ym = _mat(Y)
-    _check(_lib.lq_fused_join_predict(ctypes.byref(star.c), ctypes.byref(model.c), P_arr,
-                                      ctypes.byref(Ym), None if ws is None else ws.data_ptr(),
-                                      0 if ws is None else ws.numel() * ws.element_size(),
-                                      flags, _stream(stream)))
-    return Y
+    return _lqpy.fused_join_predict(X, fks, P, weights, biases, Y, y_dtype, flags, ws, stream)
 
 
 def lq_workspace_bytes(which_call: int, k: int, weights: Sequence[torch.Tensor], chunk_rows: int) -> int:
@@ -362,21 +333,7 @@ def lq_materialized_join_predict(X: Optional[torch.Tensor], dims: Sequence[torch
                                  ws: Optional[torch.Tensor] = None, chunk_rows: Optional[int] = None,
                                  flags: int = 0, stream=None) -> torch.Tensor:
     """The non-fused pipeline: write T chunk by chunk, then run the model on it layer by layer."""
-    n = _n_of(X, fks)
-    dev = weights[0].device
-    if Y is None:
-        Y = _empty(stream, (n, weights[-1].shape[1]), dtype=y_dtype or weights[0].dtype, device=dev)
-    if ws is None:
-        rows = chunk_rows or min(max(n, 256), 1 << 22)
-        nbytes = lq_workspace_bytes(LQ_CALL_MATERIALIZED, int(weights[0].shape[0]), weights, rows)
-        ws = _empty(stream, nbytes, dtype=torch.uint8, device=dev)
-    star = _Star(n, X, dims, fks)
-    model = _Model(weights, biases)
-    Ym = _mat(Y)
-    _check(_lib.lq_materialized_join_predict(ctypes.byref(star.c), ctypes.byref(model.c),
-                                             ctypes.byref(Ym), ws.data_ptr(),
-                                             ws.numel() * ws.element_size(), flags, _stream(stream)))
-    return Y
+    return _lqpy.materialized_join_predict(X, dims, fks, weights, biases, Y, y_dtype, ws, chunk_rows, flags, stream)
 
 
 def lq_groupby_workspace_bytes(dim_rows: Sequence[int], group_card: Sequence[int], n_measures: int) -> int:
@@ -402,49 +359,8 @@ def lq_masked_groupby_sum(fks: Sequence[torch.Tensor], dim_rows: Sequence[int],
                           counts: Optional[torch.Tensor] = None, want_counts: bool = True,
                           ws: Optional[torch.Tensor] = None, flags: int = 0, stream=None):
     """Filtered star join + GROUP BY + SUM/COUNT.  Returns (sums [M x G] int64, counts [G] int64 or None)."""
-    K = len(fks)
-    n = int(measures[0].shape[0])
-    dev = measures[0].device
-    for f in fks:
-        _expect(f, torch.int32, "foreign-key column")
-        if f.shape[0] != n:
-            raise ValueError("foreign-key column length differs from the measures")
-    for m in measures:
-        _expect(m, torch.int32, "measure column")
-    masks = list(dim_mask) if dim_mask is not None else [None] * K
-    codes = list(dim_code) if dim_code is not None else [None] * K
-    for k in range(K):
-        if masks[k] is not None:
-            _expect(masks[k], torch.uint8, "dimension mask")
-            if masks[k].shape[0] != dim_rows[k]:
-                raise ValueError("mask length differs from dim_rows")
-        if codes[k] is not None:
-            _expect(codes[k], torch.int32, "dimension group code")
-            if codes[k].shape[0] != dim_rows[k]:
-                raise ValueError("code length differs from dim_rows")
-    if fact_mask is not None:
-        _expect(fact_mask, torch.uint8, "fact mask")
-    G = 1
-    for k in range(K):
-        if codes[k] is not None:
-            G *= int(group_card[k])
-    if sums is None:
-        sums = _empty(stream, (len(measures), G), dtype=torch.int64, device=dev)
-    if counts is None and want_counts:
-        counts = _empty(stream, (G,), dtype=torch.int64, device=dev)
-    if ws is None:
-        eff_card = [int(group_card[k]) if codes[k] is not None else 1 for k in range(K)]
-        ws = _empty(stream, max(lq_groupby_workspace_bytes(dim_rows, group_card, len(measures)),
-                                lq_groupby_bucket_workspace_bytes(n, dim_rows, eff_card, len(measures))),
-                    dtype=torch.uint8, device=dev)
-    rows = (ctypes.c_int64 * max(1, K))(*[int(r) for r in dim_rows])
-    card = (ctypes.c_int32 * max(1, K))(*[int(c) for c in group_card])
-    _check(_lib.lq_masked_groupby_sum(
-        n, K, _ptr_array(fks), rows, _ptr_array(masks), _ptr_array(codes), card,
-        None if fact_mask is None else fact_mask.data_ptr(), len(measures), _ptr_array(measures),
-        sums.data_ptr(), None if counts is None else counts.data_ptr(), ws.data_ptr(),
-        ws.numel() * ws.element_size(), flags, _stream(stream)))
-    return sums, counts
+    return _lqpy.masked_groupby_sum(fks, dim_rows, dim_mask, dim_code, group_card, fact_mask, measures, sums, counts, want_counts,
+                                    ws, flags, stream)
 
 
 def lq_static_scratch_bytes() -> int:
@@ -572,17 +488,7 @@ def lq_tree_table_ld(n_leaves: int) -> int:
 
 def lq_tree_project_dims(dims: Sequence[torch.Tensor], c_f: int, feature, threshold, H, stream=None):
     """Pre-fused tree tables (uint8 [r_k x ld] per dimension) and the target vector (uint8 [ld])."""
-    tree = _tree(feature, threshold, H)
-    ld = lq_tree_table_ld(tree.n_leaves)
-    dev = H.device
-    tables = [_empty(stream, (d.shape[0], ld), dtype=torch.uint8, device=dev) for d in dims]
-    target = _empty(stream, (ld,), dtype=torch.uint8, device=dev)
-    fact = lq_mat(None, 0, int(c_f), max(int(c_f), 1), LQ_F32)
-    dims_arr = _mat_array(dims)
-    star = lq_star(0, fact, len(dims), dims_arr, _ptr_array([None] * len(dims)))
-    _check(_lib.lq_tree_project_dims(ctypes.byref(star), ctypes.byref(tree), _ptr_array(tables),
-                                     target.data_ptr(), _stream(stream)))
-    return tables, target
+    return _lqpy.tree_project_dims(dims, c_f, feature, threshold, H, stream)
 
 
 def lq_fused_join_tree(X: Optional[torch.Tensor], fks: Sequence[torch.Tensor], tables, target, feature,
@@ -590,23 +496,7 @@ def lq_fused_join_tree(X: Optional[torch.Tensor], fks: Sequence[torch.Tensor], t
                        stream=None):
     """Leaf reached by every fact row (int32 [n]) and / or the one-hot matrix (uint8 [n x l]).
     With LQ_CHECK_FKS the keys are first checked against the row counts of the tables."""
-    tree = _tree(feature, threshold, H)
-    n = _n_of(X, fks)
-    dev = H.device
-    leaf = _empty(stream, (n,), dtype=torch.int32, device=dev) if want_leaf else None
-    onehot = _empty(stream, (n, tree.n_leaves), dtype=torch.uint8, device=dev) if want_onehot else None
-    star = _Star(n, X, None, fks)
-    ws = None
-    if flags & LQ_CHECK_FKS:
-        rows_arr = (lq_mat * max(1, len(tables)))(*[lq_mat(None, int(t.shape[0]), 1, 1, LQ_F32) for t in tables])
-        star.c.dims = rows_arr
-        ws = _empty(stream, 256, dtype=torch.uint8, device=dev)
-    _check(_lib.lq_fused_join_tree(ctypes.byref(star.c), ctypes.byref(tree), _ptr_array(tables),
-                                   target.data_ptr(), None if leaf is None else leaf.data_ptr(),
-                                   None if onehot is None else onehot.data_ptr(), flags,
-                                   None if ws is None else ws.data_ptr(), 0 if ws is None else ws.numel(),
-                                   _stream(stream)))
-    return leaf, onehot
+    return _lqpy.fused_join_tree(X, fks, tables, target, feature, threshold, H, want_leaf, want_onehot, flags, stream)
 
 
 def lq_tree_mask_words(n_leaves: int) -> int:
@@ -615,16 +505,7 @@ def lq_tree_mask_words(n_leaves: int) -> int:
 
 def lq_tree_compress_tables(dims: Sequence[torch.Tensor], tables, feature, threshold, H, c_f: int = 0, stream=None):
     """Leaf masks (int64 bit patterns [r_k x words] per dimension) of pre-fused tree tables."""
-    tree = _tree(feature, threshold, H)
-    words = lq_tree_mask_words(tree.n_leaves)
-    dev = H.device
-    masks = [_empty(stream, (d.shape[0], words), dtype=torch.int64, device=dev) for d in dims]
-    fact = lq_mat(None, 0, int(c_f), max(int(c_f), 1), LQ_F32)
-    dims_arr = _mat_array(dims)
-    star = lq_star(0, fact, len(dims), dims_arr, _ptr_array([None] * len(dims)))
-    _check(_lib.lq_tree_compress_tables(ctypes.byref(star), ctypes.byref(tree), _ptr_array(tables), _ptr_array(masks),
-                                        _stream(stream)))
-    return masks
+    return _lqpy.tree_compress_tables(dims, tables, feature, threshold, H, c_f, stream)
 
 
 def lq_tree_project_dim_rows(dims: Sequence[torch.Tensor], c_f: int, tables, masks, feature, threshold, H,
@@ -645,10 +526,7 @@ def lq_tree_fact_mask_bytes(n_nodes: int, n_leaves: int) -> int:
 
 def lq_tree_fact_masks(c_f: int, feature, threshold, H, stream=None):
     """Packed mask rows (opaque uint8 buffer) of the nodes that test the fact table's own columns."""
-    tree = _tree(feature, threshold, H)
-    buf = _empty(stream, (lq_tree_fact_mask_bytes(tree.n_nodes, tree.n_leaves),), dtype=torch.uint8, device=H.device)
-    _check(_lib.lq_tree_fact_masks(int(c_f), ctypes.byref(tree), buf.data_ptr(), _stream(stream)))
-    return buf
+    return _lqpy.tree_fact_masks(c_f, feature, threshold, H, stream)
 
 
 def lq_fused_join_tree_masks(fks: Sequence[torch.Tensor], masks, feature, threshold, H, want_leaf: bool = True,
@@ -656,20 +534,7 @@ def lq_fused_join_tree_masks(fks: Sequence[torch.Tensor], masks, feature, thresh
                              X: Optional[torch.Tensor] = None, fact_masks: Optional[torch.Tensor] = None):
     """The join stage on leaf masks: same results as lq_fused_join_tree.  X / fact_masks: the fact
     table's own columns and the buffer of lq_tree_fact_masks, when the tree tests such columns."""
-    tree = _tree(feature, threshold, H)
-    n = _n_of(X, fks)
-    dev = H.device
-    leaf = _empty(stream, (n,), dtype=torch.int32, device=dev) if want_leaf else None
-    onehot = _empty(stream, (n, tree.n_leaves), dtype=torch.uint8, device=dev) if want_onehot else None
-    star = _Star(n, X, None, fks)
-    # row counts of the mask tables (the library may then keep small tables in LDS); no data pointers
-    rows_arr = (lq_mat * max(1, len(masks)))(*[lq_mat(None, int(m.shape[0]), 1, 1, LQ_F32) for m in masks])
-    star.c.dims = rows_arr
-    _check(_lib.lq_fused_join_tree_masks(ctypes.byref(star.c), ctypes.byref(tree), _ptr_array(masks),
-                                         None if fact_masks is None else fact_masks.data_ptr(),
-                                         None if leaf is None else leaf.data_ptr(),
-                                         None if onehot is None else onehot.data_ptr(), flags, _stream(stream)))
-    return leaf, onehot
+    return _lqpy.fused_join_tree_masks(fks, masks, feature, threshold, H, want_leaf, want_onehot, flags, stream, X, fact_masks)
 
 
 def lq_materialized_join_tree(X: Optional[torch.Tensor], dims, fks, feature, threshold, H,
@@ -702,11 +567,7 @@ def lq_keymap_bytes(max_keys: int) -> int:
 
 def lq_keymap_build(keys: torch.Tensor, max_keys: Optional[int] = None, flags: int = 0, stream=None) -> torch.Tensor:
     """Hash map from the key values of a dimension to its row numbers; returns the map buffer."""
-    _expect(keys, torch.int32, "dimension key column")
-    nbytes = lq_keymap_bytes(max(int(keys.shape[0]), max_keys or 0))
-    table = _empty(stream, nbytes, dtype=torch.uint8, device=keys.device)
-    _check(_lib.lq_keymap_build(table.data_ptr(), nbytes, keys.data_ptr(), int(keys.shape[0]), flags, _stream(stream)))
-    return table
+    return _lqpy.keymap_build(keys, max_keys, flags, stream)
 
 
 def lq_keymap_insert(table: torch.Tensor, keys: torch.Tensor, first_row: int, flags: int = 0, stream=None) -> None:
@@ -718,12 +579,7 @@ def lq_keymap_insert(table: torch.Tensor, keys: torch.Tensor, first_row: int, fl
 def lq_keymap_lookup(table: torch.Tensor, fact_keys: torch.Tensor, fk: Optional[torch.Tensor] = None,
                      stream=None) -> torch.Tensor:
     """fk[i] = dimension row whose key equals fact_keys[i], -1 where there is none."""
-    _expect(fact_keys, torch.int32, "fact key column")
-    if fk is None:
-        fk = _empty(stream, fact_keys.shape, dtype=fact_keys.dtype, device=fact_keys.device)
-    _check(_lib.lq_keymap_lookup(table.data_ptr(), table.numel(), fact_keys.data_ptr(),
-                                 int(fact_keys.shape[0]), fk.data_ptr(), _stream(stream)))
-    return fk
+    return _lqpy.keymap_lookup(table, fact_keys, fk, stream)
 
 
 def lq_keymap64_bytes(max_keys: int) -> int:
@@ -732,11 +588,7 @@ def lq_keymap64_bytes(max_keys: int) -> int:
 
 def lq_keymap64_build(keys: torch.Tensor, max_keys: Optional[int] = None, flags: int = 0, stream=None) -> torch.Tensor:
     """Map from the int64 key values of a dimension to its row numbers; returns the map buffer."""
-    _expect(keys, torch.int64, "dimension key column")
-    nbytes = lq_keymap64_bytes(max(int(keys.shape[0]), max_keys or 0))
-    table = _empty(stream, nbytes, dtype=torch.uint8, device=keys.device)
-    _check(_lib.lq_keymap64_build(table.data_ptr(), nbytes, keys.data_ptr(), int(keys.shape[0]), flags, _stream(stream)))
-    return table
+    return _lqpy.keymap64_build(keys, max_keys, flags, stream)
 
 
 def lq_keymap64_insert(table: torch.Tensor, keys: torch.Tensor, first_row: int, flags: int = 0, stream=None) -> None:
@@ -748,12 +600,7 @@ def lq_keymap64_insert(table: torch.Tensor, keys: torch.Tensor, first_row: int, 
 def lq_keymap64_lookup(table: torch.Tensor, fact_keys: torch.Tensor, fk: Optional[torch.Tensor] = None,
                        stream=None) -> torch.Tensor:
     """fk[i] = dimension row whose key equals fact_keys[i] (int64), -1 where there is none."""
-    _expect(fact_keys, torch.int64, "fact key column")
-    if fk is None:
-        fk = _empty(stream, fact_keys.shape, dtype=torch.int32, device=fact_keys.device)
-    _check(_lib.lq_keymap64_lookup(table.data_ptr(), table.numel(), fact_keys.data_ptr(),
-                                   int(fact_keys.shape[0]), fk.data_ptr(), _stream(stream)))
-    return fk
+    return _lqpy.keymap64_lookup(table, fact_keys, fk, stream)
 
 
 def lq_compact_matches(fk: torch.Tensor, stream=None):
@@ -799,35 +646,7 @@ def lq_order_groups(group_card: Sequence[int], sums: Optional[torch.Tensor], cou
                     n_out: Optional[torch.Tensor] = None, stream=None):
     """ORDER BY over the populated groups.  keys: (kind, index, descending) triples.
     Returns (order int32 [G] padded with -1, n_out int32 [1]), both on the device."""
-    _expect(counts, torch.int64, "counts")
-    G = int(counts.shape[0])
-    n_measures = 0
-    if sums is not None:
-        _expect(sums, torch.int64, "sums")
-        if sums.dim() != 2 or sums.shape[1] != G or not sums.is_contiguous():
-            raise ValueError("sums must be a contiguous [n_measures x G] tensor")
-        n_measures = int(sums.shape[0])
-    prod = 1
-    for c in group_card:
-        prod *= int(c)
-    if prod != G:
-        raise ValueError("counts length differs from the product of group_card")
-    card = (ctypes.c_int32 * max(1, len(group_card)))(*[int(c) for c in group_card])
-    karr = (lq_sort_key * max(1, len(keys)))()
-    for q, (kind, index, desc) in enumerate(keys):
-        karr[q] = lq_sort_key(int(kind), int(index), int(bool(desc)))
-    if order is None:
-        order = _empty(stream, G, dtype=torch.int32, device=counts.device)
-    if n_out is None:
-        n_out = _empty(stream, 1, dtype=torch.int32, device=counts.device)
-    _expect(order, torch.int32, "order")
-    _expect(n_out, torch.int32, "n_out")
-    if order.numel() < G or n_out.numel() < 1:
-        raise ValueError("order needs G entries and n_out one")
-    _check(_lib.lq_order_groups(len(group_card), card, n_measures, None if sums is None else sums.data_ptr(),
-                                counts.data_ptr(), len(keys), karr, order.data_ptr(), n_out.data_ptr(),
-                                _stream(stream)))
-    return order, n_out
+    return _lqpy.order_groups(group_card, sums, counts, keys, order, n_out, stream)
 
 
 # ---------------------------------------------------------------- incremental pre-fusion, advice
@@ -875,42 +694,7 @@ def lq_groupby_agg(fks: Sequence[torch.Tensor], dim_rows: Sequence[int], dim_mas
                    ws: Optional[torch.Tensor] = None, flags: int = 0, stream=None) -> dict:
     """Filtered star join + GROUP BY with fact range predicates ``[(column, lo, hi)]``, measures
     ``[(op, a, b)]`` (op in col / mul / sub) and SUM / MIN / MAX / COUNT.  Returns a dict of int64 tensors."""
-    K = len(fks)
-    n = int(measures[0][1].shape[0])
-    dev = measures[0][1].device
-    for f in fks:
-        _expect(f, torch.int32, "foreign-key column")
-    masks = list(dim_mask) if dim_mask is not None else [None] * K
-    codes = list(dim_code) if dim_code is not None else [None] * K
-    G = 1
-    for k in range(K):
-        if codes[k] is not None:
-            G *= int(group_card[k])
-    M = len(measures)
-    pa = (lq_range_pred * max(1, len(preds)))()
-    for q, (col, lo, hi) in enumerate(preds):
-        _expect(col, torch.int32, "predicate column")
-        pa[q] = lq_range_pred(col.data_ptr(), int(lo), int(hi))
-    ma = (lq_measure * M)()
-    for m, (op, a, b) in enumerate(measures):
-        _expect(a, torch.int32, "measure column")
-        if b is not None:
-            _expect(b, torch.int32, "measure column")
-        ma[m] = lq_measure(_MEASURE_OPS[op], a.data_ptr(), None if b is None else b.data_ptr())
-    out = {}
-    for name in ("sum", "min", "max"):
-        out[name] = _empty(stream, (M, G), dtype=torch.int64, device=dev) if name in want else None
-    out["count"] = _empty(stream, (G,), dtype=torch.int64, device=dev) if "count" in want else None
-    rows = (ctypes.c_int64 * max(1, K))(*[int(r) for r in dim_rows])
-    card = (ctypes.c_int32 * max(1, K))(*[int(c) for c in group_card])
-    if ws is None:
-        need = int(_lib.lq_groupby_agg_workspace_bytes(K, rows, card, M))
-        if not preds and "min" not in want and "max" not in want and "sum" in want:
-            eff = (ctypes.c_int32 * max(1, K))(*[int(group_card[k]) if codes[k] is not None else 1 for k in range(K)])
-            need = max(need, int(_lib.lq_groupby_agg_bucket_workspace_bytes(n, K, rows, eff, M, ctypes.cast(ma, ctypes.c_void_p))))
-        ws = _empty(stream, need, dtype=torch.uint8, device=dev)
-    ptr = lambda t: None if t is None else t.data_ptr()
-    _check(_lib.lq_groupby_agg(n, K, _ptr_array(fks), rows, _ptr_array(masks), _ptr_array(codes), card,
-                               len(preds), pa, M, ma, ptr(out["sum"]), ptr(out["min"]), ptr(out["max"]),
-                               ptr(out["count"]), ws.data_ptr(), ws.numel(), flags, _stream(stream)))
-    return out
+    sums, mins, maxs, counts = _lqpy.groupby_agg(
+        fks, dim_rows, dim_mask, dim_code, group_card, preds, [(_MEASURE_OPS[op], a, b) for op, a, b in measures],
+        "sum" in want, "min" in want, "max" in want, "count" in want, ws, flags, stream)
+    return {"sum": sums, "min": mins, "max": maxs, "count": counts}

@@ -75,16 +75,20 @@ int launch_group_avg(int32_t M, int64_t G, const int64_t* sums, const int64_t* c
 
 namespace {
 
-int check_mat(const lq_mat& m, const char* what, bool need_data) {
-  if (m.rows < 0 || m.cols < 0) return fail(LQ_ERR_SHAPE, "%s: negative size", what);
-  if (!dtype_ok(m.dtype)) return fail(LQ_ERR_DTYPE, "%s: unknown dtype %d", what, m.dtype);
-  if (m.rows > 0 && m.cols > 0) {
-    if (m.ld < m.cols) return fail(LQ_ERR_SHAPE, "%s: ld %lld < cols %d", what, (long long)m.ld, m.cols);
-    if (need_data && !m.data) return fail(LQ_ERR_NULL, "%s: data is NULL", what);
-    if (m.data && !aligned(m.data, dtype_size(m.dtype)))
-      return fail(LQ_ERR_SHAPE, "%s: data is not aligned to its element size", what);
+// `index` >= 0: the message names entry `index` of the array `what` (written only when something is wrong: a call
+// checks up to a dozen matrices, and formatting their names cost it most of a microsecond).
+int check_mat(const lq_mat& m, const char* what, int index, bool need_data) {
+  const char* wrong = nullptr;
+  int code = LQ_ERR_SHAPE;
+  if (m.rows < 0 || m.cols < 0) wrong = "negative size";
+  else if (!dtype_ok(m.dtype)) { wrong = "unknown dtype"; code = LQ_ERR_DTYPE; }
+  else if (m.rows > 0 && m.cols > 0) {
+    if (m.ld < m.cols) wrong = "ld smaller than cols";
+    else if (need_data && !m.data) { wrong = "data is NULL"; code = LQ_ERR_NULL; }
+    else if (m.data && !aligned(m.data, dtype_size(m.dtype))) wrong = "data is not aligned to its element size";
   }
-  return LQ_OK;
+  if (!wrong) return LQ_OK;
+  return index >= 0 ? fail(code, "%s[%d]: %s", what, index, wrong) : fail(code, "%s: %s", what, wrong);
 }
 
 // Validates star + model (+ optional P) and works out the common dtype and the joined width.
@@ -109,7 +113,7 @@ int check_star_model(const lq_star* star, const lq_model* model, bool need_dims,
   int rc = LQ_OK;
   int32_t kw = 0;
   if (star->fact.cols > 0) {
-    if ((rc = check_mat(star->fact, "fact", star->n_fact > 0))) return rc;
+    if ((rc = check_mat(star->fact, "fact", -1, star->n_fact > 0))) return rc;
     if (star->fact.rows != star->n_fact) return fail(LQ_ERR_SHAPE, "fact.rows != n_fact");
     if (star->fact.dtype != dt) return fail(LQ_ERR_DTYPE, "fact and W[0] differ in dtype");
     kw = star->fact.cols;
@@ -120,22 +124,18 @@ int check_star_model(const lq_star* star, const lq_model* model, bool need_dims,
     if (star->n_fact > 0 && !star->fks[k]) return fail(LQ_ERR_NULL, "fks[%d] is NULL", k);
     if (star->fks[k] && !aligned(star->fks[k], 4)) return fail(LQ_ERR_SHAPE, "fks[%d] is not 4-byte aligned", k);
     if (need_dims || star->dims) {
-      char name[32];
-      snprintf(name, sizeof(name), "dims[%d]", k);
-      if ((rc = check_mat(star->dims[k], name, true))) return rc;
-      if (star->dims[k].dtype != dt) return fail(LQ_ERR_DTYPE, "%s and W[0] differ in dtype", name);
-      if (star->dims[k].rows < 1 && star->n_fact > 0) return fail(LQ_ERR_SHAPE, "%s has no rows", name);
+      if ((rc = check_mat(star->dims[k], "dims", k, true))) return rc;
+      if (star->dims[k].dtype != dt) return fail(LQ_ERR_DTYPE, "dims[%d] and W[0] differ in dtype", k);
+      if (star->dims[k].rows < 1 && star->n_fact > 0) return fail(LQ_ERR_SHAPE, "dims[%d] has no rows", k);
       kw += star->dims[k].cols;
     }
   }
   for (int j = 0; j < model->n_layers; ++j) {
-    char name[32];
-    snprintf(name, sizeof(name), "W[%d]", j);
-    if ((rc = check_mat(model->W[j], name, true))) return rc;
+    if ((rc = check_mat(model->W[j], "W", j, true))) return rc;
     if (model->W[j].dtype != dt) return fail(LQ_ERR_DTYPE, "all layers must share one dtype");
-    if (model->W[j].cols < 1) return fail(LQ_ERR_SHAPE, "%s has no columns", name);
+    if (model->W[j].cols < 1) return fail(LQ_ERR_SHAPE, "W[%d] has no columns", j);
     if (j > 0 && model->W[j].rows != model->W[j - 1].cols)
-      return fail(LQ_ERR_SHAPE, "%s has %lld rows but the previous layer has %d outputs", name,
+      return fail(LQ_ERR_SHAPE, "W[%d] has %lld rows but the previous layer has %d outputs", j,
                   (long long)model->W[j].rows, model->W[j - 1].cols);
     if (model->bias && model->bias[j] && !aligned(model->bias[j], dtype_size(dt)))
       return fail(LQ_ERR_SHAPE, "bias[%d] is misaligned", j);
@@ -152,7 +152,7 @@ int check_star_model(const lq_star* star, const lq_model* model, bool need_dims,
 
 int check_Y(const lq_mat* Y, int64_t n, int32_t l_out, int32_t model_dtype) {
   if (!Y) return fail(LQ_ERR_NULL, "Y is NULL");
-  int rc = check_mat(*Y, "Y", n > 0);
+  int rc = check_mat(*Y, "Y", -1, n > 0);
   if (rc) return rc;
   if (Y->rows != n || Y->cols != l_out)
     return fail(LQ_ERR_SHAPE, "Y is %lld x %d, expected %lld x %d", (long long)Y->rows, Y->cols,
@@ -230,14 +230,12 @@ int lq_project_dims(const lq_star* star, const lq_model* model, lq_mat* P, void*
   if (rc) return rc;
   if (star->n_dims > 0 && !P) return fail(LQ_ERR_NULL, "P is NULL");
   for (int k = 0; k < star->n_dims; ++k) {
-    char name[32];
-    snprintf(name, sizeof(name), "P[%d]", k);
-    if ((rc = check_mat(P[k], name, true))) return rc;
+    if ((rc = check_mat(P[k], "P", k, true))) return rc;
     if (P[k].rows != star->dims[k].rows || P[k].cols != c.l1)
-      return fail(LQ_ERR_SHAPE, "%s is %lld x %d, expected %lld x %d", name, (long long)P[k].rows,
+      return fail(LQ_ERR_SHAPE, "P[%d] is %lld x %d, expected %lld x %d", k, (long long)P[k].rows,
                   P[k].cols, (long long)star->dims[k].rows, c.l1);
     if (P[k].dtype == LQ_BF16 && c.dtype != LQ_BF16)
-      return fail(LQ_ERR_DTYPE, "%s: bf16 projected tables need a bf16 model", name);
+      return fail(LQ_ERR_DTYPE, "P[%d]: bf16 projected tables need a bf16 model", k);
   }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int32_t off = star->fact.cols > 0 ? star->fact.cols : 0;
@@ -252,7 +250,7 @@ int lq_project_dim_rows(const lq_star* star, const lq_model* model, lq_mat* P, i
   if (rc) return rc;
   if (!P) return fail(LQ_ERR_NULL, "P is NULL");
   if (dim < 0 || dim >= star->n_dims) return fail(LQ_ERR_SHAPE, "dimension %d outside 0..%d", dim, star->n_dims - 1);
-  if ((rc = check_mat(P[dim], "P[dim]", true))) return rc;
+  if ((rc = check_mat(P[dim], "P", dim, true))) return rc;
   const lq_mat& D = star->dims[dim];
   if (P[dim].rows != D.rows || P[dim].cols != c.l1) return fail(LQ_ERR_SHAPE, "P[dim] does not match its dimension table");
   if (P[dim].dtype == LQ_BF16 && c.dtype != LQ_BF16) return fail(LQ_ERR_DTYPE, "bf16 projected tables need a bf16 model");
@@ -351,18 +349,16 @@ int lq_fused_join_predict(const lq_star* star, const lq_model* model, const lq_m
   a.K = star->n_dims;
   int64_t rows[LQ_MAX_DIMS];
   for (int k = 0; k < a.K; ++k) {
-    char name[32];
-    snprintf(name, sizeof(name), "P[%d]", k);
-    if ((rc = check_mat(P[k], name, true))) return rc;
+    if ((rc = check_mat(P[k], "P", k, true))) return rc;
     if (P[k].cols != c.l1 || P[k].rows < 1)
-      return fail(LQ_ERR_SHAPE, "%s is %lld x %d, expected r_k x %d", name, (long long)P[k].rows,
+      return fail(LQ_ERR_SHAPE, "P[%d] is %lld x %d, expected r_k x %d", k, (long long)P[k].rows,
                   P[k].cols, c.l1);
     if (P[k].dtype != P[0].dtype) return fail(LQ_ERR_DTYPE, "projected tables differ in dtype");
     if (P[k].dtype == LQ_BF16 && c.dtype != LQ_BF16)
-      return fail(LQ_ERR_DTYPE, "%s: bf16 projected tables need a bf16 model", name);
+      return fail(LQ_ERR_DTYPE, "P[%d]: bf16 projected tables need a bf16 model", k);
     if (star->dims) {
       if (star->dims[k].rows != P[k].rows)
-        return fail(LQ_ERR_SHAPE, "%s has %lld rows, dims[%d] has %lld", name, (long long)P[k].rows, k,
+        return fail(LQ_ERR_SHAPE, "P[%d] has %lld rows, dims[%d] has %lld", k, (long long)P[k].rows, k,
                     (long long)star->dims[k].rows);
     }
     a.P[k] = P[k].data;
