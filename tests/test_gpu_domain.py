@@ -143,3 +143,14 @@ def test_argument_errors(lq):
     with pytest.raises(lq.LQError) as e:
         lq.lq_group_domain([torch.zeros(4, dtype=torch.int32, device="cuda")] * 5)
     assert e.value.status == "LQ_ERR_SHAPE"
+
+
+@pytest.mark.parametrize("G", [31, 32, 33, 1_023, 1_024, 1_025, 8_191])
+def test_order_groups_at_the_edges_of_its_tiles(lq, G):
+    """32 groups per workgroup, 1,024 keys staged at a time; keys that pack into 50 bits and keys that do not."""
+    r = np.random.default_rng(G)
+    counts = r.integers(0, 2, size=G)
+    sums = np.stack([r.integers(0, 2**33, size=G), r.integers(-2**62, 2**62, size=G)])
+    for keys in ([(D.KEY_SUM, 0, True)], [(D.KEY_COUNT, 0, False), (D.KEY_SUM, 1, False)],
+                 [(D.KEY_GROUP_COLUMN, 0, True), (D.KEY_SUM, 0, False), (D.KEY_COUNT, 0, True)]):
+        _check_order(lq, [G], sums, counts, keys)
