@@ -10,8 +10,9 @@
 //     a key in the domain is key - smallest key, and the buffer is the array "row of that key or -1":
 //     one 4-byte read per fact row, no comparison, no probing;
 //   * hashed: otherwise an open-addressing table over the keys (capacity a power of two of at least
-//     twice the key count, linear probing, 8-byte slots "key << 32 | row"): one or two probes per
-//     fact row instead of log2(r) dependent searches.
+//     twice the key count, 8-byte slots "key << 32 | row", two slots to a 16-byte bucket, double
+//     hashing over buckets): one probe for nearly every fact row instead of log2(r) dependent
+//     searches.
 // Both take inserts for incremental updates (a direct map only inside its window), and the fact
 // side streams through once.  A key that is not in the map gives -1 (the row does not appear in
 // the join result, Section 2.3.2).  The row-mapping matrices I_R / I_S of Section 2.3.3 (COO index
@@ -36,6 +37,13 @@ struct Header {
 
 __device__ __forceinline__ uint32_t slot_of(int32_t key, uint32_t shift) {
   return (static_cast<uint32_t>(key) * 0x9E3779B1u) >> shift;
+}
+
+// Distance to the next bucket on a key's path, in slots: an odd number of buckets (so that the path visits them all)
+// that depends on the key, because with a fixed distance full buckets grow into runs, and a wavefront waits for the
+// longest path among its keys.
+__device__ __forceinline__ uint32_t step_of(int32_t key) {
+  return 2u * ((static_cast<uint32_t>(key) * 0x85EBCA6Bu >> 8) | 1u);
 }
 
 __global__ __launch_bounds__(256) void keymap_clear_kernel(u64* slots, u64 capacity, Header* header) {
@@ -100,12 +108,13 @@ __global__ __launch_bounds__(256) void keymap_insert_kernel(u64* slots, uint32_t
     return;
   }
   const u64 mine = (static_cast<u64>(static_cast<uint32_t>(key)) << 32) | static_cast<uint32_t>(row0 + i);
-  uint32_t s = slot_of(key, shift) & mask;
+  // first slot of the bucket, second slot, next bucket: a bucket's second slot is only taken when its first one is
+  uint32_t s = slot_of(key, shift) & mask & ~1u;
   for (uint32_t probes = 0; probes <= mask; ++probes) {           // bounded: at most one sweep of the table
     const u64 old = atomicCAS(&slots[s], EMPTY, mine);
     if (old == EMPTY) return;
     if (static_cast<int32_t>(old >> 32) == key) { atomicOr(&header->flags, FLAG_DUPLICATE); return; }
-    s = (s + 1) & mask;
+    s = (probes & 1) ? ((s & ~1u) + step_of(key)) & mask : s + 1;
   }
   atomicOr(&header->flags, FLAG_FULL);
 }
@@ -120,29 +129,69 @@ __device__ __forceinline__ Form form_of(const Header* header, uint32_t mask) {
   return f;
 }
 
-__device__ __forceinline__ int32_t probe(const u64* slots, uint32_t mask, uint32_t shift, int32_t key) {
-  uint32_t s = slot_of(key, shift) & mask;
-  for (uint32_t probes = 0; probes <= mask; ++probes) {           // bounded: at most one sweep of the table
-    const u64 v = slots[s];
-    if (v == EMPTY) return -1;
-    if (static_cast<int32_t>(v >> 32) == key) return static_cast<int32_t>(v & 0xffffffffu);
-    s = (s + 1) & mask;
-  }
-  return -1;
-}
-
-template <typename SLOTS>
-__device__ __forceinline__ int32_t find(SLOTS slots, uint32_t mask, uint32_t shift, const Form& f, int32_t key) {
+// Rows of N keys.  A lookup is a random access of a few bytes, and what bounds the kernels is how many of them are in
+// flight: all N first probes are issued together, and only keys whose bucket is full of other keys go on (at most half
+// of the slots are taken, so about one in twenty).  A bucket is one 16-byte load, that is one request to the cache,
+// where slot-by-slot probing needs 1.3 on average and its slowest lane four or five, one after the other.
+template <int N, typename SLOTS>
+__device__ __forceinline__ void find(SLOTS slots, uint32_t mask, uint32_t shift, const Form& f, const int32_t (&key)[N], int32_t (&row)[N]) {
   if (f.direct) {
-    const int64_t cell = static_cast<int64_t>(key) - f.base;
-    return (cell >= 0 && cell < f.cells) ? reinterpret_cast<const int32_t*>(slots)[cell] : -1;
+    const int32_t* cells = reinterpret_cast<const int32_t*>(slots);
+    int32_t v[N];
+    bool in[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const int64_t cell = static_cast<int64_t>(key[q]) - f.base;
+      in[q] = cell >= 0 && cell < f.cells;
+      v[q] = cells[in[q] ? cell : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) row[q] = in[q] ? v[q] : -1;
+    return;
   }
-  return probe(slots, mask, shift, key);
+  uint32_t s[N];
+  uint4 b[N];
+  bool open = false, more[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    s[q] = slot_of(key[q], shift) & mask & ~1u;
+    b[q] = *reinterpret_cast<const uint4*>(&slots[s[q]]);
+  }
+  // (an empty slot holds -1 as its row: a key of -1 that "matches" one gets the right answer)
+  auto resolve = [&](int q) {
+    const uint32_t k = static_cast<uint32_t>(key[q]);
+    row[q] = b[q].y == k ? static_cast<int32_t>(b[q].x) : b[q].w == k ? static_cast<int32_t>(b[q].z) : -1;
+    more[q] = b[q].y != k && b[q].w != k && (b[q].z & b[q].w) != 0xffffffffu;
+    open = open || more[q];
+  };
+#pragma unroll
+  for (int q = 0; q < N; ++q) resolve(q);
+  for (uint32_t probes = 2; open && probes <= mask; probes += 2) {   // bounded: at most one sweep of the table
+    open = false;
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      if (more[q]) {
+        s[q] = (s[q] + step_of(key[q])) & mask;
+        b[q] = *reinterpret_cast<const uint4*>(&slots[s[q]]);
+      }
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      if (more[q]) resolve(q);
+  }
+}
+template <typename SLOTS>
+__device__ __forceinline__ int32_t find_one(SLOTS slots, uint32_t mask, uint32_t shift, const Form& f, int32_t key) {
+  const int32_t k[1] = {key};
+  int32_t r[1];
+  find<1>(slots, mask, shift, f, k, r);
+  return r[0];
 }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// Four keys per thread (one 16-byte load, four probes in flight); the tail is done one by one.
+// Four keys per thread (one 16-byte load); the tail is done one by one.  Bound by the rate at which the vector memory
+// path takes unrelated addresses (a table of 2 MB in L2 serves 2.5e11 a second, one of 32 MB 0.65e11): 6e6 keys of
+// 30,000 / 200,000 rows take 36 / 40 us hashed (46 / 46 probing slot by slot) and 24 / 28 us through a direct map.
 __global__ __launch_bounds__(256) void keymap_lookup_kernel(const Header* __restrict__ header,
                                                             const u64* __restrict__ slots, uint32_t mask,
                                                             uint32_t shift, const int32_t* __restrict__ keys,
@@ -152,31 +201,43 @@ __global__ __launch_bounds__(256) void keymap_lookup_kernel(const Header* __rest
   if (vec_ok) {
     const int64_t n4 = n / 4;
     if (t < n4) {
-      const v4i k = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(keys) + t);
-      v4i r;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = find(slots, mask, shift, f, k[q]);
-      __builtin_nontemporal_store(r, reinterpret_cast<v4i*>(fk) + t);
+      const v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(keys) + t);
+      const int32_t k[4] = {v[0], v[1], v[2], v[3]};
+      int32_t r[4];
+      find<4>(slots, mask, shift, f, k, r);
+      const v4i out = {r[0], r[1], r[2], r[3]};
+      __builtin_nontemporal_store(out, reinterpret_cast<v4i*>(fk) + t);
     } else if (t - n4 < n - 4 * n4) {
       const int64_t i = 4 * n4 + (t - n4);
-      fk[i] = find(slots, mask, shift, f, keys[i]);
+      fk[i] = find_one(slots, mask, shift, f, keys[i]);
     }
   } else if (t < n) {
-    fk[t] = find(slots, mask, shift, f, keys[t]);
+    fk[t] = find_one(slots, mask, shift, f, keys[t]);
   }
 }
 
 // Small maps: every workgroup copies the whole cell / slot array into LDS and serves a contiguous
 // slice of the fact keys from there, so lookups never leave the compute unit.  Two 16-byte key
-// loads are in flight per thread.
+// loads are in flight per thread, the first ones while the map is copied.  A hashed map of fewer slots than
+// `lds_mask` + 1 is spread over that many on the way (a table half full sends a tenth of the keys on to a second bucket
+// and some wavefront-mate of each to a fourth; an eighth full, one in a hundred):
+// 2,000 keys in 4,096 slots, 6e6 lookups: 32 us in the map's own slots, one after the other, 18 us so.
 constexpr int LDS_LOOKUP_THREADS = 1024;
 __global__ __launch_bounds__(LDS_LOOKUP_THREADS) void keymap_lookup_lds_kernel(const Header* __restrict__ header,
                                                                               const u64* __restrict__ slots,
                                                                               uint32_t mask, uint32_t shift,
                                                                               const int32_t* __restrict__ keys,
                                                                               int64_t n, int32_t* __restrict__ fk,
-                                                                              int64_t per_block) {
+                                                                              int64_t per_block, uint32_t lds_mask,
+                                                                              uint32_t lds_shift) {
   extern __shared__ __align__(16) u64 lds_slots[];
+  const int64_t n4 = n / 4;
+  const int64_t lo = static_cast<int64_t>(blockIdx.x) * per_block, hi = min(n4, lo + per_block);
+  const v4i* kp = reinterpret_cast<const v4i*>(keys);
+  int64_t t = lo + threadIdx.x;
+  v4i k0 = {0, 0, 0, 0}, k1 = {0, 0, 0, 0};
+  if (t < hi) k0 = __builtin_nontemporal_load(kp + t);
+  if (t + LDS_LOOKUP_THREADS < hi) k1 = __builtin_nontemporal_load(kp + t + LDS_LOOKUP_THREADS);
   Form f = form_of(header, mask);
   if (f.direct) f.cells = static_cast<int64_t>(header->max_key) - f.base + 1;   // cells beyond hold -1 and are not copied
   {
@@ -185,29 +246,41 @@ __global__ __launch_bounds__(LDS_LOOKUP_THREADS) void keymap_lookup_lds_kernel(c
     // a direct map only uses the cells up to its largest key
     const uint32_t pieces = f.direct ? static_cast<uint32_t>((static_cast<int64_t>(header->max_key) - f.base) / 4 + 1)
                                      : (mask + 1u) / 2u;
-    for (uint32_t i = threadIdx.x; i < pieces; i += LDS_LOOKUP_THREADS) dst[i] = src[i];
+    if (f.direct || lds_mask == mask) {
+      for (uint32_t i = threadIdx.x; i < pieces; i += LDS_LOOKUP_THREADS) dst[i] = src[i];
+    } else {
+      const uint4 none = {~0u, ~0u, ~0u, ~0u};
+      for (uint32_t i = threadIdx.x; i < (lds_mask + 1u) / 2u; i += LDS_LOOKUP_THREADS) dst[i] = none;
+      __syncthreads();
+      for (uint32_t i = threadIdx.x; i <= mask; i += LDS_LOOKUP_THREADS) {
+        const u64 v = slots[i];
+        if (v == EMPTY) continue;
+        const int32_t key = static_cast<int32_t>(v >> 32);
+        uint32_t s = slot_of(key, lds_shift) & lds_mask & ~1u;
+        for (uint32_t probes = 0; probes <= lds_mask; ++probes) {     // (there is room: the LDS table has more slots)
+          if (atomicCAS(&lds_slots[s], EMPTY, v) == EMPTY) break;
+          s = (probes & 1) ? ((s & ~1u) + step_of(key)) & lds_mask : s + 1;
+        }
+      }
+      mask = lds_mask;
+      shift = lds_shift;
+    }
   }
   __syncthreads();
-  const int64_t n4 = n / 4;
-  const int64_t lo = static_cast<int64_t>(blockIdx.x) * per_block, hi = min(n4, lo + per_block);
-  for (int64_t t = lo + threadIdx.x; t < hi; t += 2 * LDS_LOOKUP_THREADS) {
-    const int64_t t1 = t + LDS_LOOKUP_THREADS;
-    const v4i k0 = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(keys) + t);
-    v4i k1 = {0, 0, 0, 0};
-    if (t1 < hi) k1 = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(keys) + t1);
-    v4i r;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) r[q] = find(lds_slots, mask, shift, f, k0[q]);
-    __builtin_nontemporal_store(r, reinterpret_cast<v4i*>(fk) + t);
-    if (t1 < hi) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = find(lds_slots, mask, shift, f, k1[q]);
-      __builtin_nontemporal_store(r, reinterpret_cast<v4i*>(fk) + t1);
-    }
+  for (; t < hi; t += 2 * LDS_LOOKUP_THREADS) {
+    const int64_t t1 = t + LDS_LOOKUP_THREADS, t2 = t + 2 * LDS_LOOKUP_THREADS, t3 = t + 3 * LDS_LOOKUP_THREADS;
+    const int32_t k[8] = {k0[0], k0[1], k0[2], k0[3], k1[0], k1[1], k1[2], k1[3]};
+    if (t2 < hi) k0 = __builtin_nontemporal_load(kp + t2);
+    if (t3 < hi) k1 = __builtin_nontemporal_load(kp + t3);
+    int32_t r[8];
+    find<8>(lds_slots, mask, shift, f, k, r);
+    const v4i r0 = {r[0], r[1], r[2], r[3]}, r1 = {r[4], r[5], r[6], r[7]};
+    __builtin_nontemporal_store(r0, reinterpret_cast<v4i*>(fk) + t);
+    if (t1 < hi) __builtin_nontemporal_store(r1, reinterpret_cast<v4i*>(fk) + t1);
   }
   if (blockIdx.x == 0) {
     const int64_t i = 4 * n4 + threadIdx.x;
-    if (i < n) fk[i] = find(lds_slots, mask, shift, f, keys[i]);
+    if (i < n) fk[i] = find_one(lds_slots, mask, shift, f, keys[i]);
   }
 }
 
@@ -368,15 +441,20 @@ int lq_keymap_lookup(const void* table, size_t table_bytes, const int32_t* fact_
   const size_t slot_bytes = static_cast<size_t>(g.capacity) * 8;
   if (vec_ok && slot_bytes <= 128 * 1024 && n >= (1 << 20)) {
     const int64_t n4 = n / 4;
-    const int per_cu = slot_bytes <= 64 * 1024 ? 2 : 1;       // workgroups whose copies fit one compute unit's LDS
+    // 64 KB of LDS for every smaller map: two workgroups still share a compute unit
+    Geometry lds = g;
+    while (lds.capacity * 8 < 64 * 1024) { lds.capacity *= 2; --lds.shift; }
+    lds.mask = static_cast<uint32_t>(lds.capacity - 1);
+    const size_t lds_bytes = static_cast<size_t>(lds.capacity) * 8;
+    const int per_cu = lds_bytes <= 64 * 1024 ? 2 : 1;       // workgroups whose copies fit one compute unit's LDS
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n4 + LDS_LOOKUP_THREADS - 1) / LDS_LOOKUP_THREADS,
                                                                   static_cast<int64_t>(num_cus()) * per_cu));
     const int64_t per_block = (n4 + blocks - 1) / blocks;
-    if (slot_bytes > 64 * 1024)
+    if (lds_bytes > 64 * 1024)
       LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&keymap_lookup_lds_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(slot_bytes)));
-    hipLaunchKernelGGL(keymap_lookup_lds_kernel, dim3(static_cast<unsigned>(blocks)), dim3(LDS_LOOKUP_THREADS), slot_bytes, s,
-                       header, slots, g.mask, g.shift, fact_keys, n, fk, per_block);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes)));
+    hipLaunchKernelGGL(keymap_lookup_lds_kernel, dim3(static_cast<unsigned>(blocks)), dim3(LDS_LOOKUP_THREADS), lds_bytes, s,
+                       header, slots, g.mask, g.shift, fact_keys, n, fk, per_block, lds.mask, lds.shift);
     LQ_LAUNCH_CHECK("keymap_lookup_lds_kernel");
     return LQ_OK;
   }

@@ -224,3 +224,22 @@ def test_int64_extremes_duplicates_inserts_and_the_reserved_key(lq):
             part = lq.lq_keymap64_build(torch.from_numpy(ks).cuda(), flags=lq.LQ_CHECK_KEYS)
         fk_w, _, _ = MJ.key_to_row(kr, ks)
         np.testing.assert_array_equal(lq.lq_keymap64_lookup(part, torch.from_numpy(kr).cuda()).cpu().numpy(), fk_w)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("r", [1, 500, 2_000, 4_096, 4_097, 8_192])
+def test_small_maps_in_lds(lq, r, dense, wide):
+    """More than 2^20 fact keys: small maps are served from LDS, hashed ones spread over more slots there (500 and 2,000 keys;
+    4,096 fill 8,192 slots half, 4,097 are past the 64-bit limit, 8,192 at the 32-bit one).  Whole numbers, exact."""
+    g = np.random.default_rng(r + dense)
+    n = (1 << 20) + 4 * r + 3
+    dt = np.int64 if wide else np.int32
+    key_S = (g.permutation(r) + 17).astype(dt) if dense else (g.permutation(8 * r + 40)[:r].astype(dt) * dt(1_000_003 if wide else 101))
+    key_R = g.choice(np.concatenate([key_S, key_S + dt(1)]), size=n).astype(dt)
+    order = np.argsort(key_S)
+    at = np.minimum(np.searchsorted(key_S[order], key_R), r - 1)
+    want = np.where(key_S[order][at] == key_R, order[at], -1)
+    build, lookup = (lq.lq_keymap64_build, lq.lq_keymap64_lookup) if wide else (lq.lq_keymap_build, lq.lq_keymap_lookup)
+    table = build(torch.from_numpy(key_S).cuda(), flags=lq.LQ_CHECK_KEYS)
+    np.testing.assert_array_equal(lookup(table, torch.from_numpy(key_R).cuda()).cpu().numpy(), want)
