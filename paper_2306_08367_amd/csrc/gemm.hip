@@ -91,7 +91,7 @@ __device__ __forceinline__ v4u load_chunk(const T* p, int valid, bool vec_ok) {
 }
 
 template <typename TA, typename TC, int BN>
-__global__ __launch_bounds__(TILED_THREADS) void gemm_tiled_kernel(GemmBatch batch) {
+__global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch batch) {
   int problem = 0;
   while (problem + 1 < batch.count && static_cast<int32_t>(blockIdx.x) >= batch.first_tile[problem + 1]) ++problem;
   const GemmArgs g = batch.g[problem];
@@ -174,28 +174,70 @@ __global__ __launch_bounds__(TILED_THREADS) void gemm_tiled_kernel(GemmBatch bat
     }
   };
 
-  fetch(0);
-  for (int k0 = 0; k0 < g.Kd; k0 += BK) {
-    __syncthreads();          // previous tile fully consumed
-    stage();
-    __syncthreads();
-    if (k0 + BK < g.Kd) fetch(k0 + BK);
+  // fp32: vector instructions delay the matrix instructions of the SIMD, so those of the fetch cost more than its
+  // loads do.  A whole k-tile needs no test per element: the tile's corner stays in scalar registers and each
+  // thread keeps one 32-bit byte offset per 16-byte piece.  Columns past N are never stored, so a piece that lies
+  // past N repeats the tile's first one.  The last part of k, column counts that end inside a piece of a tile and
+  // row strides whose offsets would pass 32 bits go through fetch().  16,555 x 683 -> 2,048 columns: 462 -> 437 us
+  // (100 -> 106 TFLOP/s; 153 is what these instructions reach alone), with operands read a step ahead.
+  const bool whole = F32 && (n0 + BN <= g.N || g.N % VEC == 0) && max(g.lda, g.ldb) < (int64_t{1} << 31) / (BM * 4);
+  uint32_t off_a[A_CHUNKS], off_b[B_CHUNKS];
+  if constexpr (F32) {
+#pragma unroll
+    for (int c = 0; c < A_CHUNKS; ++c) {
+      const int id = tid + c * TILED_THREADS;
+      const int64_t r = min(static_cast<int64_t>(id / A_CPR), g.M - 1 - m0);      // rows past the end repeat the last row
+      off_a[c] = static_cast<uint32_t>((r * g.lda + id % A_CPR * VEC) * 4);
+    }
+#pragma unroll
+    for (int c = 0; c < B_CHUNKS; ++c) {
+      const int id = tid + c * TILED_THREADS;
+      const int nc = id % B_CPR * VEC;
+      off_b[c] = static_cast<uint32_t>((id / B_CPR * g.ldb + (n0 + nc < g.N ? nc : 0)) * 4);
+    }
+  }
+  auto load_whole = [](const char* p) {
+    const Words4 t = *reinterpret_cast<const Words4*>(p);
+    return v4u{t.x, t.y, t.z, t.w};
+  };
+  auto fetch_whole = [&](int k0) {
+    const char* pa = reinterpret_cast<const char*>(A + m0 * g.lda + k0);
+    const char* pb = reinterpret_cast<const char*>(B + static_cast<int64_t>(k0) * g.ldb + n0);
+#pragma unroll
+    for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load_whole(pa + off_a[c]);
+#pragma unroll
+    for (int c = 0; c < B_CHUNKS; ++c) rb[c] = load_whole(pb + off_b[c]);
+  };
+  auto multiply = [&](int k0) {
     if constexpr (F32) {
       const float* As = reinterpret_cast<const float*>(smemA);
       const float* Bs = reinterpret_cast<const float*>(smemB);
-#pragma unroll 4
-      for (int kk = 0; kk < BK; kk += 2) {
-        const int k = kk + (lane >> 5);
-        float a[2], b[TN];
+      // In halves: the second one of a last part of at most BK / 2 holds nothing but zeros (a joined table of 16
+      // columns has no other part).  The operands of a step are read one step ahead.
 #pragma unroll
-        for (int i = 0; i < 2; ++i) a[i] = As[k * (BM + PADF) + wm * 64 + i * 32 + (lane & 31)];
+      for (int half = 0; half < BK; half += BK / 2) {
+        if (half >= g.Kd - k0) break;
+        float a[2][2], b[2][TN];
+        auto read = [&](int kk, int at) {
+          const int k = kk + (lane >> 5);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) b[j] = Bs[k * (BN + PADF) + wn * WN + j * 32 + (lane & 31)];
+          for (int i = 0; i < 2; ++i) a[at][i] = As[k * (BM + PADF) + wm * 64 + i * 32 + (lane & 31)];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+          for (int j = 0; j < TN; ++j) b[at][j] = Bs[k * (BN + PADF) + wn * WN + j * 32 + (lane & 31)];
+        };
+        read(half, 0);
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int st = 0; st < BK / 4; ++st) {
+          const int at = st & 1;
+          if (st + 1 < BK / 4) read(half + 2 * st + 2, at ^ 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[at][i], b[at][j], acc[i][j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     } else {
 #pragma unroll
@@ -216,6 +258,28 @@ __global__ __launch_bounds__(TILED_THREADS) void gemm_tiled_kernel(GemmBatch bat
                                                                 __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
       }
     }
+  };
+
+  int k0 = 0;
+  if constexpr (F32) {
+    // A loop of its own: next to fetch()'s branches the loads would be waited for before the products.
+    const int end = whole ? g.Kd / BK * BK : 0;
+    if (end > 0) fetch_whole(0);
+    for (; k0 < end; k0 += BK) {
+      __syncthreads();          // previous tile fully consumed
+      stage();
+      __syncthreads();
+      fetch_whole(min(k0 + BK, end - BK));
+      multiply(k0);
+    }
+  }
+  if (k0 < g.Kd) fetch(k0);
+  for (; k0 < g.Kd; k0 += BK) {
+    __syncthreads();            // previous tile fully consumed
+    stage();
+    __syncthreads();
+    if (k0 + BK < g.Kd) fetch(k0 + BK);
+    multiply(k0);
   }
 
   // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.

@@ -436,6 +436,31 @@ def test_materialised_chunking_does_not_change_results(lq):
         assert_close(Y, want, TOL_F32, f"chunk {chunk}")
 
 
+@pytest.mark.parametrize("rows,cols,n,pad", [
+    ((1, 128), (32, 64), 128, 0),          # whole k-tiles only; one row, one whole row tile
+    ((127, 129), (31, 33), 132, 1),        # k ends inside a tile, odd row strides, a column tile of one piece
+    ((257, 300), (95, 65), 130, 3),        # columns that end inside a piece: the last column tile goes element by element
+    ((130, 64), (40, 683), 17, 0),         # the narrow tile, columns end inside a piece
+    ((200, 5), (96, 1), 60, 5),            # the narrow tile, columns end between pieces
+])
+def test_projection_tile_edges_are_exact_on_small_integers(lq, rows, cols, n, pad):
+    """Small integers: every product and sum is exact in fp32.  The padding after each row holds NaN."""
+    rng = torch.Generator().manual_seed(sum(rows) + n)
+    ints = lambda r, c: torch.randint(-8, 9, (r, c), generator=rng).float()
+    dims, W = [ints(r, c) for r, c in zip(rows, cols)], ints(2 + sum(cols), n)
+
+    def strided(t):
+        buf = torch.full((t.shape[0], t.shape[1] + pad), float("nan"), device="cuda")
+        buf[:, :t.shape[1]] = t
+        return buf[:, :t.shape[1]]
+
+    P = lq.lq_project_dims([strided(d) for d in dims], strided(W), 2)
+    off = 2
+    for p, d in zip(P, dims):
+        assert torch.equal(p.cpu().double(), d.double() @ W[off:off + d.shape[1]].double())
+        off += d.shape[1]
+
+
 def test_incremental_prefusion_refreshes_only_the_given_rows(lq):
     for layers, rows in (((64, 1), (1_000, 5_003)), ((4,), (300, 2_001))):
         w = WL.make_predict("incr", 100, 4, rows, (32, 24), layers, seed=WL.SEED0 + 90, w_sigma=[0.2] * len(layers))
