@@ -15,29 +15,53 @@ struct MatArgs {
   void* T; int64_t ldt; int32_t kw;  // joined width
 };
 
-// One thread per (row, column) of the chunk, columns fastest: the writes to T are
-// fully coalesced and the reads of one dimension row are contiguous across lanes.
+// Any column counts and strides.  A workgroup takes `rb` rows, columns fastest: the writes to T are coalesced and the
+// reads of one dimension row are contiguous across lanes.  The row's keys and the segments (fact columns, dimension
+// 0, ..) come from LDS and the row of an element from a 32-bit product; U elements of a thread are in flight, since
+// what bounds the kernel is the latency of key, then element.
+constexpr int MAT_ROWS = 64;
 template <typename E>
-__global__ __launch_bounds__(256) void materialize_kernel(MatArgs a) {
-  const int64_t total = a.rows * a.kw;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
-       idx += stride) {
-    const int64_t r = idx / a.kw;
-    const int col = static_cast<int>(idx - r * a.kw);
-    const int64_t row = a.row0 + r;
-    E v;
-    if (col < a.c_f) {
-      v = static_cast<const E*>(a.X)[row * a.ldx + col];
-    } else {
-      int k = 0;
+__global__ __launch_bounds__(256) void materialize_kernel(MatArgs a, int rb, uint32_t magic /*ceil(2^32 / kw), kw > 1*/) {
+  constexpr int U = 4;
+  struct Segment { const E* base; int64_t ld; };      // base: where column 0 of the joined row would be
+  __shared__ Segment seg[LQ_MAX_DIMS + 1];
+  __shared__ int32_t key[LQ_MAX_DIMS + 1][MAT_ROWS];
+  const int tid = threadIdx.x;
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rb;
+  const int n = static_cast<int>(min(static_cast<int64_t>(rb), a.rows - r0));
+  if (tid == 0) {
+    seg[0].base = static_cast<const E*>(a.X) + (a.c_f > 0 ? (a.row0 + r0) * a.ldx : 0);
+    seg[0].ld = a.ldx;
+  }
+  for (int r = tid; r < n; r += 256) key[0][r] = r;
 #pragma unroll
-      for (int q = 1; q < LQ_MAX_DIMS; ++q)
-        if (q < a.K && col >= a.off[q]) k = q;
-      const int64_t j = a.fk[k][row];
-      v = static_cast<const E*>(a.D[k])[j * a.ldd[k] + (col - a.off[k])];
+  for (int k = 0; k < LQ_MAX_DIMS; ++k) {
+    if (k >= a.K) break;
+    if (tid == 0) { seg[k + 1].base = static_cast<const E*>(a.D[k]); seg[k + 1].ld = a.ldd[k]; }
+    if (tid < n) key[k + 1][tid] = a.fk[k][a.row0 + r0 + tid];
+  }
+  __syncthreads();
+  E* T = static_cast<E*>(a.T) + r0 * a.ldt;
+  const uint32_t kw = static_cast<uint32_t>(a.kw), total = static_cast<uint32_t>(n) * kw;
+  for (uint32_t e0 = tid; e0 < total; e0 += 256 * U) {
+    E v[U];
+    int64_t at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t e = min(e0 + 256u * u, total - 1);
+      uint32_t r = kw > 1 ? __umulhi(e, magic) : e;   // at most one too large (e < 2^31)
+      r -= r * kw > e;
+      const int32_t col = static_cast<int32_t>(e - r * kw);
+      int k = 0, off = 0;
+#pragma unroll
+      for (int q = 0; q < LQ_MAX_DIMS; ++q)
+        if (q < a.K && col >= a.off[q]) { k = q + 1; off = a.off[q]; }
+      v[u] = seg[k].base[key[k][r] * seg[k].ld + (col - off)];
+      at[u] = static_cast<int64_t>(r) * a.ldt + col;
     }
-    static_cast<E*>(a.T)[r * a.ldt + col] = v;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + 256u * u < total) T[at[u]] = v[u];
   }
 }
 
@@ -166,13 +190,16 @@ int launch_materialize(const lq_star& star, void* T, int64_t ldt, int64_t row0, 
       return LQ_OK;
     }
   }
-  const int64_t blocks = std::min<int64_t>((total + 255) / 256, static_cast<int64_t>(num_cus()) * 16);
+  const int rb = std::max(1, std::min(MAT_ROWS, 4096 / off));     // wide rows: enough workgroups for short chunks too
+  const uint32_t magic = off > 1 ? static_cast<uint32_t>(((uint64_t{1} << 32) + off - 1) / off) : 0u;
   const int32_t dt = a.c_f > 0 ? star.fact.dtype : star.dims[0].dtype;
-  if (dt == LQ_BF16)
-    hipLaunchKernelGGL(materialize_kernel<uint16_t>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(materialize_kernel<float>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a);
-  LQ_LAUNCH_CHECK("materialize_kernel");
+  const int64_t most = int64_t{0x7fffff} * rb;  // rows of one grid (its threads stay below 2^32)
+  for (; a.rows > 0; a.row0 += most, a.T = static_cast<char*>(a.T) + most * a.ldt * dtype_size(dt), a.rows -= most) {
+    const dim3 grid(static_cast<unsigned>((std::min(a.rows, most) + rb - 1) / rb));
+    if (dt == LQ_BF16) hipLaunchKernelGGL(materialize_kernel<uint16_t>, grid, dim3(256), 0, s, a, rb, magic);
+    else hipLaunchKernelGGL(materialize_kernel<float>, grid, dim3(256), 0, s, a, rb, magic);
+    LQ_LAUNCH_CHECK("materialize_kernel");
+  }
   return LQ_OK;
 }
 

@@ -461,6 +461,26 @@ def test_projection_tile_edges_are_exact_on_small_integers(lq, rows, cols, n, pa
         off += d.shape[1]
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,c_f,cols", [
+    (1, 0, (1,)), (64, 0, (1,)),                 # one joined column
+    (65, 3, (5, 2, 1)), (1_027, 0, (6, 5, 5)),   # a last workgroup of one row; several steps of one
+    (130, 1, (1,) * 8),                          # every segment of the fact table and eight dimensions
+    (9, 7, (2_049, 2_050)),                      # joined rows wider than a workgroup's share
+])
+def test_materialised_rows_of_odd_widths(lq, n, c_f, cols, dtype):
+    """An identity operator returns the joined table itself."""
+    rng = torch.Generator().manual_seed(n + sum(cols))
+    ints = lambda r, c: torch.randint(-100, 101, (r, c), generator=rng).to(dtype).cuda()
+    rows = [3 + 5 * k for k in range(len(cols))]
+    X = ints(n, c_f + 2)[:, 1:1 + c_f] if c_f else None
+    dims = [ints(r, c + 3)[:, 2:2 + c] for r, c in zip(rows, cols)]
+    fks = [torch.randint(0, r, (n,), generator=rng, dtype=torch.int32).cuda() for r in rows]
+    want = torch.cat(([X] if c_f else []) + [d[f.long()] for d, f in zip(dims, fks)], 1)
+    Y = lq.lq_materialized_join_predict(X, dims, fks, [torch.eye(want.shape[1], dtype=dtype, device="cuda")])
+    assert torch.equal(Y.to(dtype), want)
+
+
 def test_incremental_prefusion_refreshes_only_the_given_rows(lq):
     for layers, rows in (((64, 1), (1_000, 5_003)), ((4,), (300, 2_001))):
         w = WL.make_predict("incr", 100, 4, rows, (32, 24), layers, seed=WL.SEED0 + 90, w_sigma=[0.2] * len(layers))
