@@ -481,6 +481,27 @@ def test_materialised_rows_of_odd_widths(lq, n, c_f, cols, dtype):
     assert torch.equal(Y.to(dtype), want)
 
 
+@pytest.mark.parametrize("m,cols,n,bias", [
+    (1, (1,), 17, False), (31, (2, 1), 64, True),          # less than one row block; k shorter than a 16-byte piece
+    (129, (6, 5, 5), 128, False), (128, (8, 8), 65, True),  # one row past a wavefront's share; a second column group of one column
+    (1_027, (17,), 127, True), (33, (16, 15), 63, False),   # the longer form, k ends inside a piece
+    (260, (20, 12), 128, True), (260, (20, 13), 128, True), (70, (9, 7), 129, True),   # its last k; what the tiled kernel keeps
+])
+def test_products_of_few_columns_are_exact_on_small_integers(lq, m, cols, n, bias):
+    """Small integers: every product and sum is exact in fp32.  The padding after each row of the weights holds NaN."""
+    rng = torch.Generator().manual_seed(m + n)
+    ints = lambda r, c: torch.randint(-8, 9, (r, c), generator=rng).float()
+    rows = [7 + 3 * k for k in range(len(cols))]
+    dims, W, b = [ints(r, c) for r, c in zip(rows, cols)], ints(sum(cols), n), ints(1, n)[0]
+    fks = [torch.randint(0, r, (m,), generator=rng, dtype=torch.int32) for r in rows]
+    want = torch.cat([d[f.long()] for d, f in zip(dims, fks)], 1).double() @ W.double() + (b.double() if bias else 0)
+    Wd = torch.full((sum(cols), n + 3), float("nan"), device="cuda")
+    Wd[:, :n] = W
+    Y = lq.lq_materialized_join_predict(None, [d.cuda() for d in dims], [f.cuda() for f in fks], [Wd[:, :n]],
+                                        [b.cuda()] if bias else None)
+    assert torch.equal(Y.cpu().double(), want)
+
+
 def test_incremental_prefusion_refreshes_only_the_given_rows(lq):
     for layers, rows in (((64, 1), (1_000, 5_003)), ((4,), (300, 2_001))):
         w = WL.make_predict("incr", 100, 4, rows, (32, 24), layers, seed=WL.SEED0 + 90, w_sigma=[0.2] * len(layers))
