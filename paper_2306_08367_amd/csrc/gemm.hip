@@ -365,7 +365,7 @@ __global__ __launch_bounds__(SKINNY_THREADS) void gemm_skinny_kernel(GemmArgs g)
 
 // ------------------------------------------------------------------ short k ------------
 
-// fp32, at most 32 rows of weights and 17 to 128 columns (a narrow star under a wide first layer).  The result is most of
+// fp32, at most 16 rows of weights and 17 to 128 columns (a narrow star under a wide first layer).  The result is most of
 // the traffic, so what bounds the product is how steadily it is written; a tile of the kernel above has one k-step, and
 // its two barriers and the way through LDS are then most of a workgroup's time.  Here a wavefront keeps 64 columns of the
 // weights in registers and walks over its row blocks without LDS or barriers: A goes from memory into the operand (both
@@ -444,8 +444,7 @@ int launch_short(const GemmArgs& g, hipStream_t s) {
   const int64_t waves = (g.M + per_wave - 1) / per_wave * col_groups, wgs = (waves + 3) / 4;
   if (wgs > 0x7fffff) return -1;             // (a grid's threads stay below 2^32)
   const dim3 grid(static_cast<unsigned>(wgs)), threads(SHORT_THREADS);
-  if (g.Kd <= 16) hipLaunchKernelGGL(gemm_short_kernel<16>, grid, threads, 0, s, g);
-  else hipLaunchKernelGGL(gemm_short_kernel<32>, grid, threads, 0, s, g);
+  hipLaunchKernelGGL(gemm_short_kernel<16>, grid, threads, 0, s, g);
   LQ_LAUNCH_CHECK("gemm_short_kernel");
   return LQ_OK;
 }
@@ -492,7 +491,7 @@ int launch_typed(GemmArgs g, hipStream_t s) {
     return LQ_OK;
   }
   if constexpr (sizeof(TA) == 4 && sizeof(TC) == 4) {
-    if (g.Kd >= 1 && g.Kd <= 32 && g.N <= 128) {
+    if (g.Kd >= 1 && g.Kd <= 16 && g.N <= 128) {
       const int rc = launch_short(g, s);
       if (rc >= 0) return rc;
     }
