@@ -154,6 +154,7 @@ template <typename T> class Array {
   ~Array() { delete[] more_; }
   Array(const Array&) = delete;
   Array& operator=(const Array&) = delete;
+  int size() const { return n_; }
   T* data() { return more_ ? more_ : own_; }
   T& operator[](int i) { return data()[i]; }
   operator T*() { return data(); }
@@ -165,7 +166,8 @@ template <typename T> class Array {
   T own_[N] = {};
 };
 
-void mats(const Seq& s, lq_mat* out) {
+void mats(const Seq& s, Array<lq_mat>& out) {
+  if (s.size() > out.size()) raise(PyExc_ValueError, "more matrices than there is room for");
   for (int j = 0; j < s.size(); ++j) out[j] = mat(s[j]);
 }
 
@@ -314,7 +316,8 @@ PyObject* project_dims(PyObject* const* a) {
   const void* no_bias = nullptr;
   const lq_model model{1, &w, &no_bias};
   const int K = star.dims_seq.size();
-  Array<lq_mat> P(K);
+  // (a caller's list may be longer than the dimensions: the library reads the first K entries)
+  Array<lq_mat> P(a[3] != Py_None ? std::max(K, Seq(a[3]).size()) : K);
   PyObject* out;
   if (a[3] != Py_None) {
     mats(Seq(a[3]), P);

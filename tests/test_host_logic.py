@@ -387,3 +387,14 @@ def test_tree_mask_rows_have_an_even_number_of_words_from_three_on():
     b = _binding()
     got = [b.lq_tree_mask_words(l) for l in (0, 1, 64, 65, 128, 129, 192, 193, 256, 257, 1_024, 1_025)]
     assert got == [0, 1, 1, 2, 2, 4, 4, 4, 4, 6, 16, 18]
+
+
+@pytest.mark.parametrize("extra", [1, 8, 64])
+def test_project_dims_takes_a_longer_list_of_tables_than_there_are_dimensions(extra):
+    """The library reads the first entries of P; here the first one has the wrong row count, so the call is refused."""
+    import torch
+    from types import SimpleNamespace
+    b = _binding()
+    dims, W = [torch.zeros(5, 3)], torch.zeros(3, 4)
+    with pytest.raises(b.LQError, match=r"P\[0\] is 6 x 4, expected 5 x 4"):
+        b.lq_project_dims(dims, W, 0, P=[torch.zeros(6, 4)] * (1 + extra), stream=SimpleNamespace(cuda_stream=0))
