@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <exception>
+#include <optional>
 #include <vector>
 
 #include "lq.h"
@@ -286,13 +287,14 @@ struct DimStar {
 
 struct Model {
   Seq weights;
+  std::optional<Seq> biases;
   Array<lq_mat> W;
   Array<const void*> bias;
   lq_model c{};
   Model(PyObject* w, PyObject* b) : weights(w), W(weights.size()), bias(weights.size()) {
     mats(weights, W);
     if (b != Py_None) {
-      Seq bs(b);
+      const Seq& bs = biases.emplace(b);
       for (int j = 0; j < std::min(bs.size(), weights.size()); ++j) bias[j] = data_of<void>(bs[j]);
     }
     c.n_layers = weights.size();
@@ -434,11 +436,13 @@ PyObject* materialized_join_predict(PyObject* const* a) {
 
 // ------------------------------------------------------------------ group-by ------------
 
-// Masks or group codes of the dimensions: None, or one tensor or None per dimension.
+// Masks or group codes of the dimensions: None, or one tensor or None per dimension.  `keep` holds them until the call is
+// made: an iterator's tensors belong to nobody else, and the outputs and workspace allocated after this would be
+// given their memory.
 template <typename T> void dim_arrays(PyObject* o, int K, const Array<int64_t>* rows, at::ScalarType st, const char* dtype_name,
-                                      const char* what, const char* length_error, const T** out) {
+                                      const char* what, const char* length_error, std::optional<Seq>& keep, const T** out) {
   if (o == Py_None) return;
-  Seq s(o);
+  const Seq& s = keep.emplace(o);
   if (s.size() < K) raise(PyExc_IndexError, "list index out of range");
   for (int k = 0; k < K; ++k) {
     if (s[k] == Py_None) continue;
@@ -457,6 +461,7 @@ struct GroupShape {
   Array<int32_t> card, effective;    // effective: 1 where the dimension does not group
   Array<const uint8_t*> mask;
   Array<const int32_t*> code;
+  std::optional<Seq> masks, codes;   // what `mask` and `code` point into
   int64_t G = 1;
   GroupShape(int K, PyObject* dim_rows, PyObject* dim_mask, PyObject* dim_code, PyObject* group_card, bool checked)
       : rows(K), card(K), effective(K), mask(K), code(K) {
@@ -467,9 +472,9 @@ struct GroupShape {
       card[k] = static_cast<int32_t>(integer(c[k]));
     }
     dim_arrays(dim_mask, K, checked ? &rows : nullptr, at::kByte, "torch.uint8", "dimension mask", "mask length differs from dim_rows",
-               mask.data());
+               masks, mask.data());
     dim_arrays(dim_code, K, checked ? &rows : nullptr, at::kInt, "torch.int32", "dimension group code",
-               "code length differs from dim_rows", code.data());
+               "code length differs from dim_rows", codes, code.data());
     for (int k = 0; k < K; ++k) {
       effective[k] = code[k] ? card[k] : 1;
       G *= effective[k];

@@ -447,3 +447,20 @@ def test_grouping_attributes_of_more_than_255_values_on_the_specialised_scan(lq,
         s, c = _gpu(lq, w, **kw)
         np.testing.assert_array_equal(s, ws_)
         np.testing.assert_array_equal(c, wc_)
+
+
+@pytest.mark.parametrize("rows,card", [((300, 40, 2_500), (7, 1, 5)), ((4_000, 2_556, 200_000), (7, 1, 25))])
+def test_masks_and_codes_from_an_iterator_stay_alive_through_the_call(lq, rows, card):
+    """The tensors that an iterator yields belong to the call: outputs and workspace must not get their memory."""
+    w = _random_groupby(71, 50_003, rows, card)
+    ws, wc = _oracle(w)
+    w = to_dev(w)
+    fresh = lambda ts: (None if t is None else t.clone() for t in ts)
+    for _ in range(3):
+        s, c = lq.lq_masked_groupby_sum(w.fks, w.dim_rows, fresh(w.dim_mask), fresh(w.dim_code), w.group_card, w.fact_mask, w.measures)
+        np.testing.assert_array_equal(s.cpu().numpy(), ws)
+        np.testing.assert_array_equal(c.cpu().numpy(), wc)
+        out = lq.lq_groupby_agg(w.fks, w.dim_rows, fresh(w.dim_mask), fresh(w.dim_code), w.group_card, [(w.fact_mask.int(), 1, 1)],
+                                [("col", m, None) for m in w.measures])
+        np.testing.assert_array_equal(out["sum"].cpu().numpy(), ws)
+        np.testing.assert_array_equal(out["count"].cpu().numpy(), wc)
