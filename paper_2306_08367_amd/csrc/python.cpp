@@ -126,16 +126,31 @@ int64_t integer(PyObject* o) {
   return v;
 }
 
+// Number of values of a grouping attribute, and of groups over several.
+int32_t cardinality(PyObject* o) {
+  const int64_t v = integer(o);
+  if (v != static_cast<int32_t>(v)) raise(PyExc_ValueError, "a group cardinality does not fit 32 bits");
+  return static_cast<int32_t>(v);
+}
+int64_t product(int64_t groups, int32_t card) {
+  int64_t r;
+  if (__builtin_mul_overflow(groups, static_cast<int64_t>(card), &r)) raise(PyExc_ValueError, "the number of groups does not fit 64 bits");
+  return r;
+}
+
 bool truth(PyObject* o) {
   const int v = PyObject_IsTrue(o);
   if (v < 0) throw PyErrorSet{};
   return v != 0;
 }
 
-// A list or tuple (or any sequence) of Python objects.
+// A list or tuple (or any other collection) of Python objects.  An iterator is refused where `any_iterable` is not set:
+// most arguments are gone through more than once.
 class Seq {
  public:
-  explicit Seq(PyObject* o) : s_(PySequence_Fast(o, "expected a sequence")) {
+  explicit Seq(PyObject* o, bool any_iterable = false) {
+    if (!any_iterable && PyObject_Size(o) < 0) throw PyErrorSet{};
+    s_ = PySequence_Fast(o, "expected a sequence");
     if (!s_) throw PyErrorSet{};
   }
   ~Seq() { Py_DECREF(s_); }
@@ -442,7 +457,7 @@ PyObject* materialized_join_predict(PyObject* const* a) {
 template <typename T> void dim_arrays(PyObject* o, int K, const Array<int64_t>* rows, at::ScalarType st, const char* dtype_name,
                                       const char* what, const char* length_error, std::optional<Seq>& keep, const T** out) {
   if (o == Py_None) return;
-  const Seq& s = keep.emplace(o);
+  const Seq& s = keep.emplace(o, true);
   if (s.size() < K) raise(PyExc_IndexError, "list index out of range");
   for (int k = 0; k < K; ++k) {
     if (s[k] == Py_None) continue;
@@ -467,9 +482,12 @@ struct GroupShape {
       : rows(K), card(K), effective(K), mask(K), code(K) {
     Seq r(dim_rows), c(group_card);
     if (r.size() < K || c.size() < K) raise(PyExc_IndexError, "list index out of range");
+    // more rows or cardinalities than key columns: a column was forgotten, and the result would not be filtered by it
+    if (r.size() > std::max(K, 1) || c.size() > std::max(K, 1))
+      raise(PyExc_IndexError, "dim_rows and group_card have an entry for every foreign-key column");
     for (int k = 0; k < K; ++k) {
       rows[k] = integer(r[k]);
-      card[k] = static_cast<int32_t>(integer(c[k]));
+      card[k] = cardinality(c[k]);
     }
     dim_arrays(dim_mask, K, checked ? &rows : nullptr, at::kByte, "torch.uint8", "dimension mask", "mask length differs from dim_rows",
                masks, mask.data());
@@ -477,7 +495,7 @@ struct GroupShape {
                "code length differs from dim_rows", codes, code.data());
     for (int k = 0; k < K; ++k) {
       effective[k] = code[k] ? card[k] : 1;
-      G *= effective[k];
+      G = product(G, effective[k]);
     }
   }
 };
@@ -603,8 +621,8 @@ PyObject* order_groups(PyObject* const* a) {
   Array<int32_t> card(cards.size());
   int64_t prod = 1;
   for (int k = 0; k < cards.size(); ++k) {
-    card[k] = static_cast<int32_t>(integer(cards[k]));
-    prod *= card[k];
+    card[k] = cardinality(cards[k]);
+    prod = product(prod, card[k]);
   }
   if (prod != G) raise(PyExc_ValueError, "counts length differs from the product of group_card");
   Array<lq_sort_key> ka(keys.size());

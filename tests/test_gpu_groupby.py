@@ -464,3 +464,20 @@ def test_masks_and_codes_from_an_iterator_stay_alive_through_the_call(lq, rows, 
                                 [("col", m, None) for m in w.measures])
         np.testing.assert_array_equal(out["sum"].cpu().numpy(), ws)
         np.testing.assert_array_equal(out["count"].cpu().numpy(), wc)
+
+
+def test_more_dimensions_than_key_columns_and_counts_past_64_bits_are_refused(lq):
+    """A forgotten key column must not give a result that ignores its dimension."""
+    w = to_dev(_random_groupby(72, 1_003, (30, 20, 10), (3, 1, 5)))
+    agg = [("col", w.measures[0], None)]
+    for rows, card in ((w.dim_rows, w.group_card[:2]), (w.dim_rows[:2], w.group_card)):
+        with pytest.raises(IndexError):
+            lq.lq_masked_groupby_sum(w.fks[:2], rows, None, None, card, None, w.measures)
+        with pytest.raises(IndexError):
+            lq.lq_groupby_agg(w.fks[:2], rows, None, None, card, [], agg)
+    codes = [torch.zeros(10, dtype=torch.int32, device="cuda")] * 4
+    for card in ([65_536] * 4, [2**32 + 2, 1, 1, 1]):
+        with pytest.raises((ValueError, RuntimeError)):
+            lq.lq_masked_groupby_sum([w.fks[2]] * 4, [10] * 4, None, codes, card, None, w.measures)
+        with pytest.raises(ValueError):
+            lq.lq_order_groups(card, None, torch.ones(2, dtype=torch.int64, device="cuda"), [])

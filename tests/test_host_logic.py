@@ -398,3 +398,18 @@ def test_project_dims_takes_a_longer_list_of_tables_than_there_are_dimensions(ex
     dims, W = [torch.zeros(5, 3)], torch.zeros(3, 4)
     with pytest.raises(b.LQError, match=r"P\[0\] is 6 x 4, expected 5 x 4"):
         b.lq_project_dims(dims, W, 0, P=[torch.zeros(6, 4)] * (1 + extra), stream=SimpleNamespace(cuda_stream=0))
+
+
+def test_iterators_are_refused_where_an_argument_is_gone_through_more_than_once():
+    import torch
+    b = _binding()
+    D, W, X = [torch.zeros(5, 3)], torch.zeros(3, 4), torch.zeros(5, 3)
+    once = lambda ts: (t for t in ts)
+    calls = [lambda: b.lq_project_dims(once(D), W, 0), lambda: b.lq_project_dims(D, W, 0, P=once([torch.zeros(6, 4)])),
+             lambda: b.lq_fused_join_predict(X, once([]), [], [W]), lambda: b.lq_fused_join_predict(X, [], [], once([W])),
+             lambda: b.lq_fused_join_predict(X, [], [], [W], once([None])),
+             lambda: b.lq_masked_groupby_sum(once([]), [], None, None, [], None, [torch.zeros(4, dtype=torch.int32)]),
+             lambda: b.lq_groupby_agg(once([]), [], None, None, [], [], [("col", torch.zeros(4, dtype=torch.int32), None)])]
+    for call in calls:
+        with pytest.raises(TypeError, match="has no len"):
+            call()
