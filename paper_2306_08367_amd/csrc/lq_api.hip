@@ -75,20 +75,25 @@ int launch_group_avg(int32_t M, int64_t G, const int64_t* sums, const int64_t* c
 
 namespace {
 
-// `index` >= 0: the message names entry `index` of the array `what` (written only when something is wrong: a call
-// checks up to a dozen matrices, and formatting their names cost it most of a microsecond).
+// What is wrong with a matrix that check_mat() refuses.  Out of line: a call checks up to a dozen matrices, and formatting
+// their names cost it most of a microsecond.
+[[gnu::cold, gnu::noinline]] int mat_error(const lq_mat& m, const char* what, int index) {
+  char name[32];
+  if (index >= 0) snprintf(name, sizeof(name), "%s[%d]", what, index);
+  else snprintf(name, sizeof(name), "%s", what);
+  if (m.rows < 0 || m.cols < 0) return fail(LQ_ERR_SHAPE, "%s: negative size %lld x %d", name, (long long)m.rows, m.cols);
+  if (!dtype_ok(m.dtype)) return fail(LQ_ERR_DTYPE, "%s: unknown dtype %d", name, m.dtype);
+  if (m.ld < m.cols) return fail(LQ_ERR_SHAPE, "%s: ld %lld < cols %d", name, (long long)m.ld, m.cols);
+  if (!m.data) return fail(LQ_ERR_NULL, "%s: data is NULL", name);
+  return fail(LQ_ERR_SHAPE, "%s: data is not aligned to its element size", name);
+}
+
+// `index` >= 0: the message names entry `index` of the array `what`.
 int check_mat(const lq_mat& m, const char* what, int index, bool need_data) {
-  const char* wrong = nullptr;
-  int code = LQ_ERR_SHAPE;
-  if (m.rows < 0 || m.cols < 0) wrong = "negative size";
-  else if (!dtype_ok(m.dtype)) { wrong = "unknown dtype"; code = LQ_ERR_DTYPE; }
-  else if (m.rows > 0 && m.cols > 0) {
-    if (m.ld < m.cols) wrong = "ld smaller than cols";
-    else if (need_data && !m.data) { wrong = "data is NULL"; code = LQ_ERR_NULL; }
-    else if (m.data && !aligned(m.data, dtype_size(m.dtype))) wrong = "data is not aligned to its element size";
-  }
-  if (!wrong) return LQ_OK;
-  return index >= 0 ? fail(code, "%s[%d]: %s", what, index, wrong) : fail(code, "%s: %s", what, wrong);
+  bool good = m.rows >= 0 && m.cols >= 0 && dtype_ok(m.dtype);
+  if (good && m.rows > 0 && m.cols > 0)
+    good = m.ld >= m.cols && (m.data ? aligned(m.data, dtype_size(m.dtype)) : !need_data);
+  return good ? LQ_OK : mat_error(m, what, index);
 }
 
 // Validates star + model (+ optional P) and works out the common dtype and the joined width.

@@ -413,3 +413,17 @@ def test_iterators_are_refused_where_an_argument_is_gone_through_more_than_once(
     for call in calls:
         with pytest.raises(TypeError, match="has no len"):
             call()
+
+
+@pytest.mark.parametrize("field,value,code,message", [
+    ("rows", -5, 2, "dims[0]: negative size -5 x 3"), ("dtype", 7, 3, "dims[0]: unknown dtype 7"),
+    ("ld", 2, 2, "dims[0]: ld 2 < cols 3"), ("data", None, 1, "dims[0]: data is NULL"),
+    ("data", FAKE + 2, 2, "dims[0]: data is not aligned to its element size"),
+])
+def test_a_refused_matrix_is_named_with_the_numbers_that_are_wrong(field, value, code, message):
+    b = _binding()
+    star, model, keep = _star_model(b)
+    setattr(keep[0][0], field, value)
+    P = (b.lq_mat * 1)(b.lq_mat(FAKE, 5, 4, 4, 0))
+    assert b._lib.lq_project_dims(ctypes.byref(star), ctypes.byref(model), P, None) == code
+    assert b.lq_last_error() == message
