@@ -90,8 +90,11 @@ __device__ __forceinline__ v4u load_chunk(const T* p, int valid, bool vec_ok) {
   return r;
 }
 
+// Workgroups per compute unit that the accumulators leave room for: three (128 columns) and four (64).  Without the bound
+// the compiler takes more registers for the fp32 forms and one workgroup less fits (64 columns: 600,000 x 85 87 us with
+// three workgroups, 81 with four); the bf16 forms keep the three and four that they have anyway.
 template <typename TA, typename TC, int BN>
-__global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch batch) {
+__global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_kernel(GemmBatch batch) {
   int problem = 0;
   while (problem + 1 < batch.count && static_cast<int32_t>(blockIdx.x) >= batch.first_tile[problem + 1]) ++problem;
   const GemmArgs g = batch.g[problem];
@@ -178,8 +181,9 @@ __global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch 
   // loads do.  A whole k-tile needs no test per element: the tile's corner stays in scalar registers and each
   // thread keeps one 32-bit byte offset per 16-byte piece.  Columns past N are never stored, so a piece that lies
   // past N repeats the tile's first one.  The last part of k, column counts that end inside a piece of a tile and
-  // row strides whose offsets would pass 32 bits go through fetch().  16,555 x 683 -> 2,048 columns: 462 -> 437 us
-  // (100 -> 106 TFLOP/s; 153 is what these instructions reach alone), with operands read a step ahead.
+  // row strides whose offsets would pass 32 bits go through fetch().  16,555 x 683 -> 2,048 columns in three
+  // problems: 457 us with fetch() and multiply() for every tile, 414 so (112 TFLOP/s; 153 is what these instructions
+  // reach alone).
   const bool whole = F32 && (n0 + BN <= g.N || g.N % VEC == 0) && max(g.lda, g.ldb) < (int64_t{1} << 31) / (BM * 4);
   uint32_t off_a[A_CHUNKS], off_b[B_CHUNKS];
   if constexpr (F32) {
@@ -212,31 +216,22 @@ __global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch 
     if constexpr (F32) {
       const float* As = reinterpret_cast<const float*>(smemA);
       const float* Bs = reinterpret_cast<const float*>(smemB);
-      // In halves: the second one of a last part of at most BK / 2 holds nothing but zeros (a joined table of 16
-      // columns has no other part).  The operands of a step are read one step ahead.
+      // Steps past k hold nothing but zeros and are left out, eight columns at a time.
+      const int steps = min(BK, (g.Kd - k0 + 7) & ~7);
+      for (int k8 = 0; k8 < steps; k8 += 8) {
 #pragma unroll
-      for (int half = 0; half < BK; half += BK / 2) {
-        if (half >= g.Kd - k0) break;
-        float a[2][2], b[2][TN];
-        auto read = [&](int kk, int at) {
+        for (int kk = k8; kk < k8 + 8; kk += 2) {
           const int k = kk + (lane >> 5);
+          float a[2], b[TN];
 #pragma unroll
-          for (int i = 0; i < 2; ++i) a[at][i] = As[k * (BM + PADF) + wm * 64 + i * 32 + (lane & 31)];
+          for (int i = 0; i < 2; ++i) a[i] = As[k * (BM + PADF) + wm * 64 + i * 32 + (lane & 31)];
 #pragma unroll
-          for (int j = 0; j < TN; ++j) b[at][j] = Bs[k * (BN + PADF) + wn * WN + j * 32 + (lane & 31)];
-        };
-        read(half, 0);
-#pragma unroll
-        for (int st = 0; st < BK / 4; ++st) {
-          const int at = st & 1;
-          if (st + 1 < BK / 4) read(half + 2 * st + 2, at ^ 1);
-          __builtin_amdgcn_sched_barrier(0);
+          for (int j = 0; j < TN; ++j) b[j] = Bs[k * (BN + PADF) + wn * WN + j * 32 + (lane & 31)];
 #pragma unroll
           for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[at][i], b[at][j], acc[i][j], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
         }
       }
     } else {
@@ -260,20 +255,48 @@ __global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch 
     }
   };
 
+  // A whole fp32 k-tile that another whole one follows: operands are read one step ahead of their products.
+  auto multiply_whole = [&]() {
+    const float* As = reinterpret_cast<const float*>(smemA);
+    const float* Bs = reinterpret_cast<const float*>(smemB);
+    float a[2][2], b[2][TN];
+    auto read = [&](int kk, int at) {
+      const int k = kk + (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[at][i] = As[k * (BM + PADF) + wm * 64 + i * 32 + (lane & 31)];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[at][j] = Bs[k * (BN + PADF) + wn * WN + j * 32 + (lane & 31)];
+    };
+    read(0, 0);
+#pragma unroll
+    for (int st = 0; st < BK / 2; ++st) {
+      const int at = st & 1;
+      if (st + 1 < BK / 2) read(2 * st + 2, at ^ 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[at][i], b[at][j], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
   int k0 = 0;
-  if constexpr (F32) {
-    // A loop of its own: next to fetch()'s branches the loads would be waited for before the products.
-    const int end = whole ? g.Kd / BK * BK : 0;
-    if (end > 0) fetch_whole(0);
-    for (; k0 < end; k0 += BK) {
+  if (whole && g.Kd >= 2 * BK) {
+    // A loop of its own: next to fetch()'s branches the loads would be waited for before the products.  Every tile's
+    // successor is fetched during its products; the loop ends before the last whole tile, whose successor is the rest.
+    fetch_whole(0);
+    for (; k0 + 2 * BK <= g.Kd; k0 += BK) {
       __syncthreads();          // previous tile fully consumed
       stage();
       __syncthreads();
-      fetch_whole(min(k0 + BK, end - BK));
-      multiply(k0);
+      fetch_whole(k0 + BK);
+      multiply_whole();
     }
+  } else {
+    fetch(0);
   }
-  if (k0 < g.Kd) fetch(k0);
   for (; k0 < g.Kd; k0 += BK) {
     __syncthreads();            // previous tile fully consumed
     stage();
@@ -282,9 +305,12 @@ __global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch 
     multiply(k0);
   }
 
-  // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
+  // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.  The bias goes in before the
+  // row tests: used inside them it would be waited for again in each, and such a wait is for every store before it
+  // too (rows written one after the other: 5,000 x 32 -> 128 columns 13.9 us with the waits, 7.7 without).
   TC* __restrict__ C = static_cast<TC*>(g.C);
   const TA* bias = static_cast<const TA*>(g.bias);
+  const int64_t row0 = m0 + wm * 64 + 4 * (lane >> 5);
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int col = n0 + wn * WN + j * 32 + (lane & 31);
@@ -294,12 +320,24 @@ __global__ __launch_bounds__(TILED_THREADS, 3) void gemm_tiled_kernel(GemmBatch 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t row = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (row >= g.M) continue;
-        float x = acc[i][j][v] + bv;
-        if (g.relu) x = fmaxf(x, 0.f);
-        Elem<TC>::store(C + row * g.ldc + col, x);
+        const float x = acc[i][j][v] + bv;
+        acc[i][j][v] = g.relu ? fmaxf(x, 0.f) : x;
       }
+    TC* p = C + row0 * g.ldc + col;
+    if (m0 + BM <= g.M) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) Elem<TC>::store(p + (i * 32 + 8 * (v >> 2) + (v & 3)) * g.ldc, acc[i][j][v]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int at = i * 32 + 8 * (v >> 2) + (v & 3);
+          if (row0 + at < g.M) Elem<TC>::store(p + at * g.ldc, acc[i][j][v]);
+        }
+    }
   }
 }
 

@@ -442,19 +442,23 @@ def test_materialised_chunking_does_not_change_results(lq):
     ((257, 300), (95, 65), 130, 3),        # columns that end inside a piece: the last column tile goes element by element
     ((130, 64), (40, 683), 17, 0),         # the narrow tile, columns end inside a piece
     ((200, 5), (96, 1), 60, 5),            # the narrow tile, columns end between pieces
+    ((129, 256), (63, 64), 128, 0),        # one whole k-tile and a part; two whole ones
+    ((64, 131), (96, 97), 132, 2),         # three whole k-tiles; three and one column
+    ((385, 1), (160, 8), 64, 0),           # the narrow tile; a part of one step of eight columns
 ])
-def test_projection_tile_edges_are_exact_on_small_integers(lq, rows, cols, n, pad):
-    """Small integers: every product and sum is exact in fp32.  The padding after each row holds NaN."""
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_projection_tile_edges_are_exact_on_small_integers(lq, rows, cols, n, pad, dtype):
+    """Small integers: exact in bf16, every product and sum exact in fp32.  The padding after each row holds NaN."""
     rng = torch.Generator().manual_seed(sum(rows) + n)
     ints = lambda r, c: torch.randint(-8, 9, (r, c), generator=rng).float()
     dims, W = [ints(r, c) for r, c in zip(rows, cols)], ints(2 + sum(cols), n)
 
     def strided(t):
-        buf = torch.full((t.shape[0], t.shape[1] + pad), float("nan"), device="cuda")
+        buf = torch.full((t.shape[0], t.shape[1] + pad), float("nan"), dtype=dtype, device="cuda")
         buf[:, :t.shape[1]] = t
         return buf[:, :t.shape[1]]
 
-    P = lq.lq_project_dims([strided(d) for d in dims], strided(W), 2)
+    P = lq.lq_project_dims([strided(d) for d in dims], strided(W), 2, p_dtype=torch.float32)
     off = 2
     for p, d in zip(P, dims):
         assert torch.equal(p.cpu().double(), d.double() @ W[off:off + d.shape[1]].double())
