@@ -2,7 +2,7 @@
 //
 // Used for the pre-fusion products P_k = D_k * (rows of L owned by dimension k) (underlined terms
 // of Eq. 1) and for the layer-by-layer model evaluation of the non-fused pipeline (T * L, second
-// line of Eq. 1).  Two kernels:
+// line of Eq. 1).  Four kernels:
 //   gemm_tiled_kernel  - 128 x BN tiles (BN = 64 or 128) staged through LDS, 4 wavefronts in a
 //                        2 x 2 arrangement, each owning 64 x BN/2 as 32x32 MFMA accumulators.
 //                        fp32 inputs use the 32x32x2 f32 MFMA; bf16 inputs stay bf16 in LDS and
@@ -17,6 +17,8 @@
 //   gemm_skinny_kernel - N <= 16 (linear models with a handful of outputs).  Bandwidth-shaped:
 //                        no LDS, every wavefront streams 16 rows of A at a time straight into
 //                        16x16 MFMA operands; B is tiny and comes from cache.
+//   gemm_short_kernel  - fp32, k <= 16, 17 to 128 columns: weights in registers, no LDS, the result
+//                        is nearly all of the traffic.
 #include "lq_common.h"
 
 namespace lq {
@@ -404,16 +406,19 @@ __global__ __launch_bounds__(SKINNY_THREADS) void gemm_skinny_kernel(GemmArgs g)
 // ------------------------------------------------------------------ short k ------------
 
 // fp32, at most 16 rows of weights and 17 to 128 columns (a narrow star under a wide first layer).  The result is most of
-// the traffic, so what bounds the product is how steadily it is written; a tile of the kernel above has one k-step, and
-// its two barriers and the way through LDS are then most of a workgroup's time.  Here a wavefront keeps 64 columns of the
-// weights in registers and walks over its row blocks without LDS or barriers: A goes from memory into the operand (both
-// halves of the wavefront read the same 16 bytes, which costs an L1 hit), the next block's rows are requested before
-// the products of this one.  Order of the additions as in the tiled kernel: the results are the same bits.
-// 600,000 x 16 -> 128 columns (307 MB written): 100 -> 62 us, 5.6 TB/s.
-constexpr int SHORT_THREADS = 256, SHORT_ROWS = 32, SHORT_COLS = 64, SHORT_BLOCKS = 4;   // row blocks per wavefront
+// the traffic, so what bounds the product is how soon and how steadily it is written; a tile of the kernel above has one
+// k-step, and its barriers and the way through LDS are then a good part of a workgroup's time.  Here a wavefront keeps 64
+// columns of the weights in registers and walks over its row blocks without LDS or barriers: A goes from memory into
+// the operand (both halves of the wavefront read the same 16 bytes, which costs an L1 hit), the next block's rows are
+// requested before the products of this one.  Order of the additions as in the tiled kernel: the same bits.
+// Over k = 1, 4, 8, 11, 16, 17 to 128 columns and 1,000 to 2,400,000 rows it takes 0.87 times the tiled kernel's time (0.56 to
+// 1.15).  k = 4 / 16: 5,000 rows, 128 columns 7.0 -> 4.9 / 7.4 -> 5.0 us; 100,000 rows, 64 columns 9.4 -> 9.7 / 10.2 -> 10.7;
+// 200,000 rows, 128 columns 21.2 -> 24.3 / 24.4 -> 25.9 (its worst); 2,400,000 rows, 64 columns 143 -> 122 / 145 -> 147,
+// 128 columns 223 -> 235 / 275 -> 266 (4.6 TB/s written).  With a second instance for 17 to 32 rows of weights the tiled kernel
+// was the faster one from 20,000 rows on (64 columns, k = 17: 6.5 against 7.0 us, 600,000 rows 38 against 47).
+constexpr int SHORT_THREADS = 256, SHORT_K = 16, SHORT_ROWS = 32, SHORT_COLS = 64;
 
-template <int KS>
-__global__ __launch_bounds__(SHORT_THREADS) void gemm_short_kernel(GemmArgs g) {
+__global__ __launch_bounds__(SHORT_THREADS) void gemm_short_kernel(GemmArgs g, int per_wave /*row blocks*/) {
   const float* __restrict__ A = static_cast<const float*>(g.A);
   const float* __restrict__ B = static_cast<const float*>(g.B);
   float* __restrict__ C = static_cast<float*>(g.C);
@@ -422,31 +427,33 @@ __global__ __launch_bounds__(SHORT_THREADS) void gemm_short_kernel(GemmArgs g) {
   const int64_t wave = static_cast<int64_t>(blockIdx.x) * (SHORT_THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col_groups = (g.N + SHORT_COLS - 1) / SHORT_COLS;       // neighbouring wavefronts share the rows
   const int64_t blocks = (g.M + SHORT_ROWS - 1) / SHORT_ROWS;
-  const int64_t first = wave / col_groups * SHORT_BLOCKS, last = min(first + SHORT_BLOCKS, blocks);
+  const int64_t first = wave / col_groups * per_wave, last = min(first + per_wave, blocks);
   const int n0 = static_cast<int>(wave % col_groups) * SHORT_COLS;
   if (first >= blocks) return;
 
-  float b[KS / 2][2], bv[2];
+  // (loaded with clamped indexes and cleared afterwards: loads under a test each are waited for one by one)
+  float b[SHORT_K / 2][2], bv[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int col = n0 + j * 32 + r;
-    bv[j] = bias && col < g.N ? bias[col] : 0.f;
+    const int col = min(n0 + j * 32 + r, g.N - 1);
+    bv[j] = bias ? bias[col] : 0.f;
 #pragma unroll
-    for (int s = 0; s < KS / 2; ++s) {
-      const int k = 2 * s + h;
-      b[s][j] = k < g.Kd && col < g.N ? B[k * g.ldb + col] : 0.f;
-    }
+    for (int s = 0; s < SHORT_K / 2; ++s) b[s][j] = B[min(2 * s + h, g.Kd - 1) * g.ldb + col];
   }
-  v4u a[KS / 4], next[KS / 4];
+#pragma unroll
+  for (int s = 0; s < SHORT_K / 2; ++s)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b[s][j] = 2 * s + h < g.Kd ? b[s][j] : 0.f;
+  v4u a[SHORT_K / 4], next[SHORT_K / 4];
   auto fetch = [&](int64_t block) {
     const float* row = A + min(block * SHORT_ROWS + r, g.M - 1) * g.lda;      // rows past the end repeat the last row
 #pragma unroll
-    for (int q = 0; q < KS / 4; ++q) next[q] = load_chunk<float>(row + 4 * q, g.Kd - 4 * q, g.a_vec_ok);
+    for (int q = 0; q < SHORT_K / 4; ++q) next[q] = load_chunk<float>(row + 4 * q, g.Kd - 4 * q, g.a_vec_ok);
   };
   fetch(first);
   for (int64_t block = first; block < last; ++block) {
 #pragma unroll
-    for (int q = 0; q < KS / 4; ++q) a[q] = next[q];
+    for (int q = 0; q < SHORT_K / 4; ++q) a[q] = next[q];
     if (block + 1 < last) fetch(block + 1);
     v16f acc[2];
 #pragma unroll
@@ -454,35 +461,52 @@ __global__ __launch_bounds__(SHORT_THREADS) void gemm_short_kernel(GemmArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 #pragma unroll
-    for (int s = 0; s < KS / 2; ++s) {
+    for (int s = 0; s < SHORT_K / 2; ++s) {
+      if (s >= SHORT_K / 4 && 2 * s >= g.Kd) break;               // nothing but zeros from here
       const float x = __uint_as_float(h ? a[s / 2][2 * (s & 1) + 1] : a[s / 2][2 * (s & 1)]);
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, b[s][j], acc[j], 0, 0, 0);
     }
+    // the bias before the row and column tests, as in the tiled kernel
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float x = acc[j][v] + bv[j];
+        acc[j][v] = g.relu ? fmaxf(x, 0.f) : x;
+      }
     const int64_t row0 = block * SHORT_ROWS + 4 * h;
+    const bool in0 = n0 + r < g.N, in1 = n0 + 32 + r < g.N;
+    float* p = C + row0 * g.ldc + n0 + r;
+    if (block * SHORT_ROWS + SHORT_ROWS <= g.M) {
+      if (in0) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t row = row0 + 8 * (v >> 2) + (v & 3);
-      if (row >= g.M) continue;
+        for (int v = 0; v < 16; ++v) p[(8 * (v >> 2) + (v & 3)) * g.ldc] = acc[0][v];
+      }
+      if (in1) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = n0 + j * 32 + r;
-        if (col >= g.N) continue;
-        float x = acc[j][v] + bv[j];
-        if (g.relu) x = fmaxf(x, 0.f);
-        C[row * g.ldc + col] = x;
+        for (int v = 0; v < 16; ++v) p[(8 * (v >> 2) + (v & 3)) * g.ldc + 32] = acc[1][v];
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int at = 8 * (v >> 2) + (v & 3);
+        if (row0 + at >= g.M) continue;
+        if (in0) p[at * g.ldc] = acc[0][v];
+        if (in1) p[at * g.ldc + 32] = acc[1][v];
       }
     }
   }
 }
 
 int launch_short(const GemmArgs& g, hipStream_t s) {
-  const int64_t col_groups = (g.N + SHORT_COLS - 1) / SHORT_COLS;
-  const int64_t per_wave = static_cast<int64_t>(SHORT_ROWS) * SHORT_BLOCKS;
-  const int64_t waves = (g.M + per_wave - 1) / per_wave * col_groups, wgs = (waves + 3) / 4;
+  const int64_t col_groups = (g.N + SHORT_COLS - 1) / SHORT_COLS, blocks = (g.M + SHORT_ROWS - 1) / SHORT_ROWS;
+  // up to four row blocks a wavefront once there are three wavefronts a SIMD without that (5,000 rows with four blocks
+  // each: 11 us, with one 5; 2,400,000 rows with up to eight 5 to 10 % slower than with four)
+  const int per_wave = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(4, blocks * col_groups / (int64_t{num_cus()} * 12))));
+  const int64_t waves = (blocks + per_wave - 1) / per_wave * col_groups, wgs = (waves + 3) / 4;
   if (wgs > 0x7fffff) return -1;             // (a grid's threads stay below 2^32)
-  const dim3 grid(static_cast<unsigned>(wgs)), threads(SHORT_THREADS);
-  hipLaunchKernelGGL(gemm_short_kernel<16>, grid, threads, 0, s, g);
+  hipLaunchKernelGGL(gemm_short_kernel, dim3(static_cast<unsigned>(wgs)), dim3(SHORT_THREADS), 0, s, g, per_wave);
   LQ_LAUNCH_CHECK("gemm_short_kernel");
   return LQ_OK;
 }
@@ -529,7 +553,7 @@ int launch_typed(GemmArgs g, hipStream_t s) {
     return LQ_OK;
   }
   if constexpr (sizeof(TA) == 4 && sizeof(TC) == 4) {
-    if (g.Kd >= 1 && g.Kd <= 16 && g.N <= 128) {
+    if (g.Kd >= 1 && g.Kd <= SHORT_K && g.N <= 128) {     // (17 to 128 columns: see gemm_short_kernel)
       const int rc = launch_short(g, s);
       if (rc >= 0) return rc;
     }

@@ -487,9 +487,11 @@ def test_materialised_rows_of_odd_widths(lq, n, c_f, cols, dtype):
 
 @pytest.mark.parametrize("m,cols,n,bias", [
     (1, (1,), 17, False), (31, (2, 1), 64, True),          # less than one row block; k shorter than a 16-byte piece
-    (129, (6, 5, 5), 128, False), (128, (8, 8), 65, True),  # one row past a wavefront's share; a second column group of one column
-    (1_027, (17,), 127, True), (33, (16, 15), 63, False),   # the longer form, k ends inside a piece
-    (260, (20, 12), 128, True), (260, (20, 13), 128, True), (70, (9, 7), 129, True),   # its last k; what the tiled kernel keeps
+    (129, (6, 5, 5), 128, False), (128, (8, 8), 65, True),  # one row in a last block; a second column group of one column
+    (1_027, (7, 2), 127, True), (10_001, (5, 3), 17, True),  # several workgroups; the first k of the longer half, the last of the shorter
+    (10_001, (16,), 64, False), (33, (8, 4), 65, True),
+    (200_001, (6, 5, 5), 33, True), (400_017, (3,), 96, False),   # two and four row blocks a wavefront
+    (1_027, (17,), 127, True), (260, (20, 12), 128, True), (70, (9, 7), 129, True),   # what the tiled kernel keeps: k, columns
 ])
 def test_products_of_few_columns_are_exact_on_small_integers(lq, m, cols, n, bias):
     """Small integers: every product and sum is exact in fp32.  The padding after each row of the weights holds NaN."""
@@ -504,6 +506,20 @@ def test_products_of_few_columns_are_exact_on_small_integers(lq, m, cols, n, bia
     Y = lq.lq_materialized_join_predict(None, [d.cuda() for d in dims], [f.cuda() for f in fks], [Wd[:, :n]],
                                         [b.cuda()] if bias else None)
     assert torch.equal(Y.cpu().double(), want)
+
+
+@pytest.mark.parametrize("cols,l1", [((16, 9), 128), ((5, 13), 17), ((6, 5), 65), ((1, 16), 100)])
+def test_incremental_prefusion_of_narrow_tables_gives_the_same_bits(lq, cols, l1):
+    """A few rows of a table with at most 16 columns go through the kernel for few columns, all tables together through the tiled one."""
+    rng = torch.Generator(device="cuda").manual_seed(sum(cols) * l1)
+    dims = [torch.randn(r, c, generator=rng, device="cuda") for r, c in zip((1_000, 3_001), cols)]
+    W = torch.randn(3 + sum(cols), l1, generator=rng, device="cuda")
+    want = lq.lq_project_dims(dims, W, 3)
+    P = [torch.full_like(p, float("nan")) for p in want]
+    for k, step in ((0, 333), (1, 1_500)):
+        for first in range(0, dims[k].shape[0], step):
+            lq.lq_project_dim_rows(dims, W, 3, P, k, first, min(step, dims[k].shape[0] - first))
+    assert all(torch.equal(p, w) for p, w in zip(P, want))
 
 
 def test_incremental_prefusion_refreshes_only_the_given_rows(lq):
