@@ -15,11 +15,38 @@ struct MatArgs {
   void* T; int64_t ldt; int32_t kw;  // joined width
 };
 
-// Any column counts and strides.  A workgroup takes `rb` rows, columns fastest: the writes to T are coalesced and the
+// Any column counts and strides, one element a thread, columns fastest: for joins of so few rows that the kernel below
+// leaves compute units idle and its way through LDS shows: 1,000 / 6,000 rows of 22 + 21 + 21 columns, with the layer behind
+// the join, 9.9 / 10.1 us through the kernel below, 6.8 / 7.7 so (smaller workgroups there: 7.8 / 9.7).
+template <typename E>
+__global__ __launch_bounds__(256) void materialize_each_kernel(MatArgs a, uint32_t total, uint32_t magic /*ceil(2^32 / kw), kw > 1*/) {
+  const uint32_t e = blockIdx.x * 256u + threadIdx.x, kw = static_cast<uint32_t>(a.kw);
+  if (e >= total) return;
+  uint32_t r = kw > 1 ? __umulhi(e, magic) : e;       // at most one too large (e < 2^31)
+  r -= r * kw > e;
+  const int32_t col = static_cast<int32_t>(e - r * kw);
+  const int64_t row = a.row0 + r;
+  E v;
+  if (col < a.c_f) {
+    v = static_cast<const E*>(a.X)[row * a.ldx + col];
+  } else {
+    const int32_t* fk = a.fk[0];
+    const void* D = a.D[0];
+    int64_t ld = a.ldd[0];
+    int32_t off = a.off[0];
+#pragma unroll
+    for (int q = 1; q < LQ_MAX_DIMS; ++q)
+      if (q < a.K && col >= a.off[q]) { fk = a.fk[q]; D = a.D[q]; ld = a.ldd[q]; off = a.off[q]; }
+    v = static_cast<const E*>(D)[fk[row] * ld + (col - off)];
+  }
+  static_cast<E*>(a.T)[r * a.ldt + col] = v;
+}
+
+// The same for more rows.  A workgroup takes `rb` rows, columns fastest: the writes to T are coalesced and the
 // reads of one dimension row are contiguous across lanes.  The row's keys and the segments (fact columns, dimension
 // 0, ..) come from LDS and the row of an element from a 32-bit product; U elements of a thread are in flight, since
 // what bounds the kernel is the latency of key, then element.
-constexpr int MAT_ROWS = 64;
+constexpr int MAT_ROWS = 256;
 template <typename E>
 __global__ __launch_bounds__(256) void materialize_kernel(MatArgs a, int rb, uint32_t magic /*ceil(2^32 / kw), kw > 1*/) {
   constexpr int U = 4;
@@ -190,9 +217,21 @@ int launch_materialize(const lq_star& star, void* T, int64_t ldt, int64_t row0, 
       return LQ_OK;
     }
   }
-  const int rb = std::max(1, std::min(MAT_ROWS, 4096 / off));     // wide rows: enough workgroups for short chunks too
+  // Rows a workgroup: 64, of wide rows as many as make 4,096 elements, of rows of up to 5 columns 1,024 elements (64 of those
+  // leave threads without work: 2,400,000 rows of 3 columns 109 us with 64 rows, 73 with 256).
+  const int rb = off <= 5 ? std::min(MAT_ROWS, 1024 / off) : std::max(1, std::min(64, 4096 / off));
   const uint32_t magic = off > 1 ? static_cast<uint32_t>(((uint64_t{1} << 32) + off - 1) / off) : 0u;
   const int32_t dt = a.c_f > 0 ? star.fact.dtype : star.dims[0].dtype;
+  // Few rows: one element a thread.  The lines lie where the two kernels meet (with the layer behind the join): 16, 64 and 100
+  // columns between 20,000 rows (7.1 against 7.3 us, 11.1 / 11.9, 13.7 / 16.0) and 40,000 (8.8 / 8.2, 15.0 / 14.5, 22.1 / 22.4);
+  // 3 and 5 columns at 200,000 (11.5 / 12.0, 12.6 / 13.0); 2,048 columns between 1,000 rows (21.7 / 24.4) and 6,000 (51.6 / 49.8).
+  if (rows < int64_t{num_cus()} * (off <= 5 ? 768 : 96) && total < (1 << 23)) {
+    const dim3 grid(static_cast<unsigned>((total + 255) / 256));
+    if (dt == LQ_BF16) hipLaunchKernelGGL(materialize_each_kernel<uint16_t>, grid, dim3(256), 0, s, a, static_cast<uint32_t>(total), magic);
+    else hipLaunchKernelGGL(materialize_each_kernel<float>, grid, dim3(256), 0, s, a, static_cast<uint32_t>(total), magic);
+    LQ_LAUNCH_CHECK("materialize_each_kernel");
+    return LQ_OK;
+  }
   const int64_t most = int64_t{0x7fffff} * rb;  // rows of one grid (its threads stay below 2^32)
   for (; a.rows > 0; a.row0 += most, a.T = static_cast<char*>(a.T) + most * a.ldt * dtype_size(dt), a.rows -= most) {
     const dim3 grid(static_cast<unsigned>((std::min(a.rows, most) + rb - 1) / rb));

@@ -468,9 +468,12 @@ def test_projection_tile_edges_are_exact_on_small_integers(lq, rows, cols, n, pa
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n,c_f,cols", [
     (1, 0, (1,)), (64, 0, (1,)),                 # one joined column
-    (65, 3, (5, 2, 1)), (1_027, 0, (6, 5, 5)),   # a last workgroup of one row; several steps of one
+    (65, 3, (5, 2, 1)), (1_027, 0, (6, 5, 5)),   # a last workgroup of a few elements
     (130, 1, (1,) * 8),                          # every segment of the fact table and eight dimensions
-    (9, 7, (2_049, 2_050)),                      # joined rows wider than a workgroup's share
+    (9, 7, (2_049, 2_050)), (4_200, 0, (683, 683, 682)),   # wide rows: under and over what one element a thread takes
+    (24_575, 0, (7, 4)), (24_577, 0, (7, 4)),    # the last row count of one element a thread, the next one (256 compute units)
+    (30_001, 3, (5, 2, 1)), (30_001, 1, (1,) * 8), (24_641, 0, (65, 64)),   # the kernel for more rows, a last workgroup of one row
+    (196_607, 0, (2, 1)), (196_609, 1, (2, 2)), (262_145, 0, (1,)),   # narrow rows: both sides, 256 rows a workgroup
 ])
 def test_materialised_rows_of_odd_widths(lq, n, c_f, cols, dtype):
     """An identity operator returns the joined table itself."""
