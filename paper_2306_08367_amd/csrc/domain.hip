@@ -133,12 +133,13 @@ uint32_t domain_capacity(int64_t rows) {
 // ---- ordering of the populated groups -----------------------------------------------------------
 // The place of a group in the result is the number of groups that come before it, so the order is counted, not sorted:
 // every workgroup takes 32 groups, stages the keys of all groups in LDS, 1,024 at a time, and counts.  At most 8,192^2
-// comparisons of one 64-bit number each, spread over the whole chip in one launch without a workspace; a sort inside
-// one workgroup's LDS leaves the other 255 compute units idle and pays a barrier for each of its 91 steps (7,000
-// groups by year and revenue: 169 us as a bitonic sort, 16 us counted; 175 groups: 18 and 4 us).
+// comparisons, spread over the whole chip in one launch without a workspace; a sort inside one workgroup's LDS leaves
+// the other 255 compute units idle and pays a barrier for each of its 91 steps (a call in a graph, bitonic sort ->
+// counted: 4,375 groups by a column and a sum 112 -> 14 us, 8,192 groups 111 -> 20, by four wide keys 117 -> 100).
 // The keys are packed into one 64-bit number where they fit: each needs only the bits of its range over the
 // populated groups (a year and a sum of a few billion: 3 + 33 bits), and 13 more for the group index make the
-// numbers distinct.  Keys of a wider range (more than 50 bits together) are compared one after the other.
+// numbers distinct; a comparison is then one of 64-bit numbers.  Keys of a wider range (more than 50 bits together)
+// are compared one after the other.
 constexpr int MAX_GROUPS = 8192;
 constexpr int ORDER_THREADS = 1024;
 constexpr int ORDER_TILE = 32;                              // groups placed by a workgroup
@@ -169,6 +170,52 @@ __device__ __forceinline__ u64 key_value(const OrderArgs& a, int q, int32_t g, l
   return a.desc[q] ? ~u : u;
 }
 
+// Few groups: one workgroup, keys compared one after the other by 16 threads a group (at least a wavefront, at most 1,024
+// threads).  What such a call costs is the way from the arguments to the result, and the kernel below, with its range
+// pass and its unrolled code, takes twice as long: 7 groups by one sum 7.0 -> 3.4 us, by four wide keys 20.8 -> 3.9, 64
+// groups 7.1 -> 4.2 and 21.0 -> 5.6.  From 65 groups on the kernel below packs one or two keys in less time (128 groups by a
+// column and a sum 6.9 us, here 8.0), with three or four keys from 129 on (128 groups by four 11.2 here, 175 groups 33
+// against 15 there).
+constexpr int SMALL_GROUPS = 128;
+__global__ __launch_bounds__(ORDER_THREADS) void order_few_groups_kernel(OrderArgs a, int log2_g /*of the next power of two*/,
+                                                                         int32_t* __restrict__ order, int32_t* __restrict__ n_out) {
+  __shared__ u64 key[4][SMALL_GROUPS];
+  __shared__ int32_t state[SMALL_GROUPS], before[SMALL_GROUPS];       // state: 0 populated, 1 not, 2 past the last group
+  const int tid = threadIdx.x, size = 1 << log2_g;
+  int populated = 0;
+  if (tid < size) {
+    const long long c = tid < a.G ? a.counts[tid] : 0;
+    populated = c > 0;
+    state[tid] = tid >= a.G ? 2 : populated ? 0 : 1;
+    before[tid] = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q < a.n_keys) key[q][tid] = populated ? key_value(a, q, tid, c) : 0;
+  }
+  const int total = __syncthreads_count(populated);
+  const int g = tid & (size - 1), shares = blockDim.x >> log2_g;
+  const int mine = state[g];
+  u64 own[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) own[q] = q < a.n_keys ? key[q][g] : 0;
+  int count = 0;
+  for (int j = tid >> log2_g; j < size; j += shares) {
+    bool less = state[j] < mine, equal = state[j] == mine;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q < a.n_keys) {
+        const u64 k = key[q][j];
+        less = less || (equal && k < own[q]);
+        equal = equal && k == own[q];
+      }
+    count += less || (equal && j < g) ? 1 : 0;
+  }
+  atomicAdd(&before[g], count);
+  __syncthreads();
+  if (tid < a.G) order[before[tid]] = populated ? tid : -1;
+  if (tid == 0) *n_out = total;
+}
+
 template <int NK>
 __global__ __launch_bounds__(ORDER_THREADS) void order_groups_kernel(OrderArgs a, int32_t* __restrict__ order,
                                                                      int32_t* __restrict__ n_out) {
@@ -185,7 +232,7 @@ __global__ __launch_bounds__(ORDER_THREADS) void order_groups_kernel(OrderArgs a
   auto ranged = [&](int q) { return q < a.n_keys && a.kind[q] != LQ_KEY_GROUP_COLUMN; };
 #pragma unroll
   for (int q = 0; q < NK; ++q) { lo[q] = ~0ull; hi[q] = 0; }
-#pragma unroll 2
+#pragma unroll NK == 4 ? 1 : 2
   for (int g = tid; g < a.G; g += ORDER_THREADS) {
     const long long c = a.counts[g];
 #pragma unroll
@@ -261,7 +308,8 @@ __global__ __launch_bounds__(ORDER_THREADS) void order_groups_kernel(OrderArgs a
         count += (two.x < mykey ? 1 : 0) + (two.y < mykey ? 1 : 0);
       }
     } else {
-      for (int u = 0; u < ORDER_THREADS / ORDER_TILE; ++u) {
+      const int pieces = min(ORDER_THREADS, a.G - t + ORDER_TILE - 1) / ORDER_TILE;      // past the last group nothing counts
+      for (int u = 0; u < pieces; ++u) {
         const int j = u * ORDER_TILE + share;
         bool less = tile_state[j] < si, equal = tile_state[j] == si;
 #pragma unroll
@@ -396,6 +444,14 @@ int lq_order_groups(int32_t n_group_cols, const int32_t* group_card, int32_t n_m
   a.counts = reinterpret_cast<const long long*>(counts);
   const dim3 grid(static_cast<unsigned>((a.G + ORDER_TILE - 1) / ORDER_TILE)), threads(ORDER_THREADS);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if (a.G <= (n_keys <= 2 ? SMALL_GROUPS / 2 : SMALL_GROUPS)) {      // (the lines: see order_few_groups_kernel)
+    int log2_g = 0;
+    while ((1 << log2_g) < a.G) ++log2_g;
+    const unsigned few = static_cast<unsigned>(std::max(64, std::min(ORDER_THREADS, 16 << log2_g)));
+    hipLaunchKernelGGL(order_few_groups_kernel, dim3(1), dim3(few), 0, s, a, log2_g, order, n_out);
+    LQ_LAUNCH_CHECK("order_few_groups_kernel");
+    return LQ_OK;
+  }
   if (n_keys <= 1) hipLaunchKernelGGL(order_groups_kernel<1>, grid, threads, 0, s, a, order, n_out);
   else if (n_keys == 2) hipLaunchKernelGGL(order_groups_kernel<2>, grid, threads, 0, s, a, order, n_out);
   else hipLaunchKernelGGL(order_groups_kernel<4>, grid, threads, 0, s, a, order, n_out);

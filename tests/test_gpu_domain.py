@@ -145,12 +145,16 @@ def test_argument_errors(lq):
     assert e.value.status == "LQ_ERR_SHAPE"
 
 
-@pytest.mark.parametrize("G", [31, 32, 33, 1_023, 1_024, 1_025, 8_191])
+@pytest.mark.parametrize("G", [1, 2, 31, 32, 33, 64, 65, 127, 128, 129, 1_023, 1_024, 1_025, 8_191])
 def test_order_groups_at_the_edges_of_its_tiles(lq, G):
-    """32 groups per workgroup, 1,024 keys staged at a time; keys that pack into 50 bits and keys that do not."""
+    """32 groups per workgroup, 1,024 keys staged at a time; one workgroup up to 64 groups (128 with three or four keys); keys that
+    pack into 50 bits and keys that do not."""
     r = np.random.default_rng(G)
     counts = r.integers(0, 2, size=G)
     sums = np.stack([r.integers(0, 2**33, size=G), r.integers(-2**62, 2**62, size=G)])
     for keys in ([(D.KEY_SUM, 0, True)], [(D.KEY_COUNT, 0, False), (D.KEY_SUM, 1, False)],
-                 [(D.KEY_GROUP_COLUMN, 0, True), (D.KEY_SUM, 0, False), (D.KEY_COUNT, 0, True)]):
+                 [(D.KEY_GROUP_COLUMN, 0, True), (D.KEY_SUM, 0, False), (D.KEY_COUNT, 0, True)],
+                 [(D.KEY_COUNT, 0, True), (D.KEY_SUM, 1, True), (D.KEY_SUM, 0, False), (D.KEY_GROUP_COLUMN, 0, False)], []):
         _check_order(lq, [G], sums, counts, keys)
+    _check_order(lq, [G], sums, np.zeros_like(counts), [(D.KEY_SUM, 0, True)])        # no group populated
+    _check_order(lq, [G], sums // 2**62, counts, [(D.KEY_SUM, 1, True), (D.KEY_SUM, 0, False), (D.KEY_COUNT, 0, False)])   # ties
