@@ -462,7 +462,8 @@ size_t lq_tree_workspace_bytes(const lq_star* star, const lq_tree* tree, int64_t
  * Key -> row mapping (the "domain generation" of the MM-Join, Algorithm 1, and the domain
  * caching proposed with it): turns key VALUES of a fact column into row numbers of a dimension
  * table, i.e. builds the row-matching matrix I of Section 2.3 in the form the calls above take.
- * The cached domain is a hash table over the dimension keys kept in a caller-owned buffer.
+ * The cached domain is a hash table over the dimension keys kept in a caller-owned buffer.  What the
+ * buffer holds belongs to the library that built it (it is no file format): rebuild it for another one.
  * ------------------------------------------------------------------------------------- */
 
 /* Bytes of a key map that can hold max_keys keys (256-byte aligned buffer; 0 if out of range). */

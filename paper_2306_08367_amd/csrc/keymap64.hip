@@ -26,15 +26,30 @@ struct Header64 {
   i64 min_key, max_key;      // of the keys given to the build
 };
 
-__device__ __forceinline__ uint32_t slot_of(i64 key, uint32_t shift) {
-  return static_cast<uint32_t>((static_cast<u64>(key) * 0x9E3779B97F4A7C15ull) >> shift);
-}
-
-// Distance to the next bucket on a key's path, in slots: an odd number of buckets that depends on the key (with a
-// fixed distance full buckets grow into runs).
-__device__ __forceinline__ uint32_t step_of(i64 key) {
-  return 2u * (static_cast<uint32_t>((static_cast<u64>(key) * 0xC2B2AE3D27D4EB4Full) >> 40) | 1u);
-}
+// Where a key's path through a table of a power of two of slots begins (`shift` of the slots, 64 - log2), and the distance to
+// its next bucket in slots: an odd number of buckets that depends on the key, because with a fixed distance full buckets
+// grow into runs.
+// The map itself mixes the key's halves before and after the product: a product alone lays the multiples of one number out
+// in a lattice that may favour some buckets (a million multiples of 1,000,003: 40 % of the keys past their first bucket
+// and a longest path of 84 buckets, 10 % and 14 so).
+struct MapPath {
+  static __device__ __forceinline__ uint32_t mixed(i64 key) {
+    u64 h = static_cast<u64>(key);
+    h = (h ^ (h >> 29)) * 0x9E3779B97F4A7C15ull;
+    return (static_cast<uint32_t>(h) ^ static_cast<uint32_t>(h >> 32)) * 0x85EBCA6Bu;
+  }
+  static __device__ __forceinline__ uint32_t slot(i64 key, uint32_t shift) { return mixed(key) >> (shift - 32); }
+  static __device__ __forceinline__ uint32_t step(i64 key) { return 2u * (mixed(key) | 1u); }
+};
+// A map spread in LDS is at most a quarter full, and a further bucket there costs little: one product.
+struct SpreadPath {
+  static __device__ __forceinline__ uint32_t slot(i64 key, uint32_t shift) {
+    return static_cast<uint32_t>((static_cast<u64>(key) * 0x9E3779B97F4A7C15ull) >> shift);
+  }
+  static __device__ __forceinline__ uint32_t step(i64 key) {
+    return 2u * (static_cast<uint32_t>((static_cast<u64>(key) * 0xC2B2AE3D27D4EB4Full) >> 40) | 1u);
+  }
+};
 
 // Slot s of the table: its bucket is s / 2.
 __device__ __forceinline__ i64* key_at(char* buckets, uint32_t s) {
@@ -98,13 +113,13 @@ __global__ __launch_bounds__(256) void keymap64_insert_kernel(char* buckets, uin
   }
   if (key == EMPTY_KEY) { atomicOr(&header->flags, FLAG_RESERVED); return; }
   // first slot of the bucket, second slot, next bucket: a bucket's second slot is only taken when its first one is
-  uint32_t s = slot_of(key, shift) & mask & ~1u;
+  uint32_t s = MapPath::slot(key, shift) & mask & ~1u;
   for (uint32_t probes = 0; probes <= mask; ++probes) {           // bounded: at most one sweep of the table
     const i64 old = static_cast<i64>(atomicCAS(reinterpret_cast<u64*>(key_at(buckets, s)), static_cast<u64>(EMPTY_KEY),
                                                static_cast<u64>(key)));
     if (old == EMPTY_KEY) { *row_at(buckets, s) = static_cast<int32_t>(row0 + i); return; }
     if (old == key) { atomicOr(&header->flags, FLAG_DUPLICATE); return; }
-    s = (probes & 1) ? ((s & ~1u) + step_of(key)) & mask : s + 1;
+    s = (probes & 1) ? ((s & ~1u) + MapPath::step(key)) & mask : s + 1;
   }
   atomicOr(&header->flags, FLAG_FULL);
 }
@@ -118,14 +133,14 @@ struct Bucket { v2l key; v2i row; };
 
 // Rows of N keys: all first probes together, then only the keys whose bucket is full of other keys (see keymap.hip).
 // `at(slot)` fetches the bucket of an even slot.
-template <int N, typename AT>
+template <typename PATH, int N, typename AT>
 __device__ __forceinline__ void find64(AT&& at, uint32_t mask, uint32_t shift, const i64 (&key)[N], int32_t (&row)[N]) {
   uint32_t s[N];
   Bucket b[N];
   bool open = false, more[N];
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    s[q] = slot_of(key[q], shift) & mask & ~1u;
+    s[q] = PATH::slot(key[q], shift) & mask & ~1u;
     b[q] = at(s[q]);
   }
   auto resolve = [&](int q) {
@@ -142,7 +157,7 @@ __device__ __forceinline__ void find64(AT&& at, uint32_t mask, uint32_t shift, c
 #pragma unroll
     for (int q = 0; q < N; ++q)
       if (more[q]) {
-        s[q] = (s[q] + step_of(key[q])) & mask;
+        s[q] = (s[q] + PATH::step(key[q])) & mask;
         b[q] = at(s[q]);
       }
 #pragma unroll
@@ -168,30 +183,30 @@ __device__ __forceinline__ void find64_in_buffer(const char* buckets, bool direc
     for (int q = 0; q < N; ++q) row[q] = in[q] ? v[q] : -1;
     return;
   }
-  find64<N>([&](uint32_t s) {
+  find64<MapPath, N>([&](uint32_t s) {
     const char* p = buckets + 24 * static_cast<size_t>(s >> 1);
     return Bucket{*reinterpret_cast<const v2l_a8*>(p), *reinterpret_cast<const v2i*>(p + 16)};
   }, mask, shift, key, row);
 }
 
-// Four keys per thread (two 16-byte loads, one 16-byte store) when the columns allow it; the last few one by one.
+// Two keys per thread (one 16-byte load) when the columns allow it; the odd last key one by one.  With four keys a thread
+// direct maps past LDS took 4 to 12 % longer from 2.5e6 keys on (less than that up to 2^20), hashed ones 2 to 10 %.
 __global__ __launch_bounds__(256) void keymap64_lookup_kernel(const Header64* __restrict__ header, const char* __restrict__ buckets,
                                                               uint32_t mask, uint32_t shift, const i64* __restrict__ keys,
                                                               int64_t n, int32_t* __restrict__ fk, int vec_ok) {
   const bool direct = header->direct != 0;
   const i64 base = header->base;
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t n4 = vec_ok ? n / 4 : 0;
-  if (t < n4) {
-    const v2l* kp = reinterpret_cast<const v2l*>(keys) + 2 * t;
-    const v2l a = __builtin_nontemporal_load(kp), b = __builtin_nontemporal_load(kp + 1);
-    const i64 k[4] = {a[0], a[1], b[0], b[1]};
-    int32_t r[4];
-    find64_in_buffer<4>(buckets, direct, base, mask, shift, k, r);
-    const v4i out = {r[0], r[1], r[2], r[3]};
-    __builtin_nontemporal_store(out, reinterpret_cast<v4i*>(fk) + t);
-  } else if (t - n4 < n - 4 * n4) {
-    const int64_t i = 4 * n4 + (t - n4);
+  const int64_t n2 = vec_ok ? n / 2 : 0;
+  if (t < n2) {
+    const v2l a = __builtin_nontemporal_load(reinterpret_cast<const v2l*>(keys) + t);
+    const i64 k[2] = {a[0], a[1]};
+    int32_t r[2];
+    find64_in_buffer<2>(buckets, direct, base, mask, shift, k, r);
+    const v2i out = {r[0], r[1]};
+    __builtin_nontemporal_store(out, reinterpret_cast<v2i*>(fk) + t);
+  } else if (t - n2 < n - 2 * n2) {
+    const int64_t i = 2 * n2 + (t - n2);
     const i64 k[1] = {keys[i]};
     int32_t r[1];
     find64_in_buffer<1>(buckets, direct, base, mask, shift, k, r);
@@ -199,10 +214,12 @@ __global__ __launch_bounds__(256) void keymap64_lookup_kernel(const Header64* __
   }
 }
 
-// Small maps, as in keymap.hip: every workgroup spreads the hash table over LDS64_SLOTS slots of LDS (or copies the
-// cells of a direct map there) and serves a slice of the fact keys from it, the first keys in flight meanwhile.
+// Small maps, as in keymap.hip: every workgroup spreads the hash table over LDS64_SLOTS slots of LDS (SPREAD; a table of that
+// many slots is copied as it is) or copies the cells of a direct map there, and serves a slice of the fact keys from
+// it, four at a time, the first ones in flight meanwhile.
 constexpr int LDS64_THREADS = 1024;
 constexpr uint32_t LDS64_SLOTS = 8192;              // 96 KB; a direct map of as many slots has 64 KB of cells
+template <bool SPREAD>
 __global__ __launch_bounds__(LDS64_THREADS) void keymap64_lookup_lds_kernel(const Header64* __restrict__ header,
                                                                             const char* __restrict__ buckets, uint32_t slots,
                                                                             uint32_t lds_shift, const i64* __restrict__ keys,
@@ -223,7 +240,7 @@ __global__ __launch_bounds__(LDS64_THREADS) void keymap64_lookup_lds_kernel(cons
   const uint32_t direct_mask = slots - 1;
   if (direct) {
     for (uint32_t i = threadIdx.x; i < slots; i += LDS64_THREADS) lkey[i] = reinterpret_cast<const i64*>(buckets)[i];   // two cells
-  } else {
+  } else if constexpr (SPREAD) {
     for (uint32_t i = threadIdx.x; i < LDS64_SLOTS; i += LDS64_THREADS) lkey[i] = EMPTY_KEY;
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < slots; i += LDS64_THREADS) {
@@ -231,15 +248,21 @@ __global__ __launch_bounds__(LDS64_THREADS) void keymap64_lookup_lds_kernel(cons
       const i64 key = *reinterpret_cast<const i64*>(p + 8 * (i & 1u));
       if (key == EMPTY_KEY) continue;
       const int32_t row = *reinterpret_cast<const int32_t*>(p + 16 + 4 * (i & 1u));
-      uint32_t s = slot_of(key, lds_shift) & mask & ~1u;
+      uint32_t s = SpreadPath::slot(key, lds_shift) & mask & ~1u;
       for (uint32_t probes = 0; probes <= mask; ++probes) {          // (there is room: at most `slots` keys)
         if (atomicCAS(reinterpret_cast<u64*>(&lkey[s]), static_cast<u64>(EMPTY_KEY), static_cast<u64>(key)) ==
             static_cast<u64>(EMPTY_KEY)) {
           lrow[s] = row;
           break;
         }
-        s = (probes & 1) ? ((s & ~1u) + step_of(key)) & mask : s + 1;
+        s = (probes & 1) ? ((s & ~1u) + SpreadPath::step(key)) & mask : s + 1;
       }
+    }
+  } else {
+    for (uint32_t i = threadIdx.x; i < LDS64_SLOTS / 2; i += LDS64_THREADS) {
+      const char* p = buckets + 24 * static_cast<size_t>(i);
+      *reinterpret_cast<v2l*>(&lkey[2 * i]) = *reinterpret_cast<const v2l_a8*>(p);
+      *reinterpret_cast<v2i*>(&lrow[2 * i]) = *reinterpret_cast<const v2i*>(p + 16);
     }
   }
   __syncthreads();
@@ -248,7 +271,7 @@ __global__ __launch_bounds__(LDS64_THREADS) void keymap64_lookup_lds_kernel(cons
     if (direct)
       find64_in_buffer<N>(reinterpret_cast<const char*>(lkey), true, base, direct_mask, 0, k, r);
     else
-      find64<N>([&](uint32_t s) {
+      find64<std::conditional_t<SPREAD, SpreadPath, MapPath>, N>([&](uint32_t s) {
         return Bucket{*reinterpret_cast<const v2l*>(&lkey[s]), *reinterpret_cast<const v2i*>(&lrow[s])};
       }, mask, lds_shift, k, r);
   };
@@ -362,20 +385,20 @@ int lq_keymap64_lookup(const void* table, size_t table_bytes, const int64_t* fac
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const Header64* header = static_cast<const Header64*>(table);
   const char* buckets = static_cast<const char*>(table) + HEADER;
-  const int vec_ok = aligned(fact_keys, 16) && aligned(fk, 16);
-  if (vec_ok && g.capacity <= LDS64_SLOTS && n >= (1 << 20)) {
+  if (aligned(fact_keys, 16) && aligned(fk, 16) && g.capacity <= LDS64_SLOTS && n >= (1 << 20)) {
     constexpr int lds_bytes = static_cast<int>(LDS64_SLOTS) * 12;
     const int64_t n4 = n / 4;
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n4 + LDS64_THREADS - 1) / LDS64_THREADS, num_cus()));
-    LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&keymap64_lookup_lds_kernel),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
-    hipLaunchKernelGGL(keymap64_lookup_lds_kernel, dim3(static_cast<unsigned>(blocks)), dim3(LDS64_THREADS), lds_bytes, s, header,
-                       buckets, static_cast<uint32_t>(g.capacity), 64u - 13u, reinterpret_cast<const i64*>(fact_keys), n, fk,
+    const auto kernel = g.capacity == LDS64_SLOTS ? keymap64_lookup_lds_kernel<false> : keymap64_lookup_lds_kernel<true>;
+    LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(LDS64_THREADS), lds_bytes, s, header, buckets,
+                       static_cast<uint32_t>(g.capacity), 64u - 13u, reinterpret_cast<const i64*>(fact_keys), n, fk,
                        (n4 + blocks - 1) / blocks);
     LQ_LAUNCH_CHECK("keymap64_lookup_lds_kernel");
     return LQ_OK;
   }
-  const int64_t threads = vec_ok ? n / 4 + n % 4 : n;
+  const int vec_ok = aligned(fact_keys, 16) && aligned(fk, 8);
+  const int64_t threads = vec_ok ? n / 2 + n % 2 : n;
   const int64_t blocks = (threads + 255) / 256;
   if (blocks > 0x7fffffffLL) return fail(LQ_ERR_UNSUPPORTED, "too many rows for one launch");
   hipLaunchKernelGGL(keymap64_lookup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, header, buckets, g.mask, g.shift,

@@ -243,3 +243,32 @@ def test_small_maps_in_lds(lq, r, dense, wide):
     build, lookup = (lq.lq_keymap64_build, lq.lq_keymap64_lookup) if wide else (lq.lq_keymap_build, lq.lq_keymap_lookup)
     table = build(torch.from_numpy(key_S).cuda(), flags=lq.LQ_CHECK_KEYS)
     np.testing.assert_array_equal(lookup(table, torch.from_numpy(key_R).cuda()).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("r", [9, 40_000, 262_144, 262_145, 600_000])
+def test_hashed_maps_in_memory(lq, r, off, wide):
+    """Hashed maps that lookups read in place: 2^19 slots (262,144 keys) and from 2^20 on, where a 32-bit path takes the neighbouring
+    bucket first.  Keys of one common factor and -1, present and absent; columns at 16 bytes and one element past it, more
+    than 2^20 fact keys and few; half of the dimension inserted later.  Whole numbers, exact."""
+    g = np.random.default_rng(r + off)
+    dt = np.int64 if wide else np.int32
+    step = dt(1_000_003 if wide else 101)
+    pool = np.unique(np.concatenate([g.permutation(8 * r)[:2 * r].astype(dt) * step, np.array([-1, -2, step + 1], dtype=dt)]))
+    g.shuffle(pool)
+    key_S = np.concatenate([pool[:r - 1][pool[:r - 1] != -1], np.array([-1], dtype=dt)])
+    order = np.argsort(key_S)
+    dev = lambda a: torch.from_numpy(np.concatenate([np.zeros(off, dtype=a.dtype), a])).cuda()[off:]
+    build, insert, lookup = ((lq.lq_keymap64_build, lq.lq_keymap64_insert, lq.lq_keymap64_lookup) if wide else
+                             (lq.lq_keymap_build, lq.lq_keymap_insert, lq.lq_keymap_lookup))
+    half = len(key_S) // 2
+    whole, grown = build(dev(key_S), flags=lq.LQ_CHECK_KEYS), build(dev(key_S[:half]), max_keys=r)
+    insert(grown, dev(key_S[half:]), half, flags=lq.LQ_CHECK_KEYS)
+    for n in ((1 << 20) + 1_027, 5_003):
+        key_R = g.choice(pool, size=n)
+        at = np.minimum(np.searchsorted(key_S[order], key_R), len(key_S) - 1)
+        want = np.where(key_S[order][at] == key_R, order[at], -1)
+        for table in (whole, grown):
+            fk = torch.empty(n + off, dtype=torch.int32, device="cuda")[off:]
+            np.testing.assert_array_equal(lookup(table, dev(key_R), fk=fk).cpu().numpy(), want)
