@@ -46,6 +46,21 @@ __device__ __forceinline__ uint32_t step_of(int32_t key) {
   return 2u * ((static_cast<uint32_t>(key) * 0x85EBCA6Bu >> 8) | 1u);
 }
 
+// The bucket after the visit-th (0, 1, ..) on a key's path, `s` and the result even slots.
+struct MapPath {
+  // A map past an XCD's L2 (2^20 slots are 8 MB) goes to the other bucket of the same 32 bytes first: what bounds its lookups
+  // is the lines that cross the fabric.  With smaller maps the jump costs the same, and paths stay shorter.
+  // (6e6 keys of 1,000,000 rows, with two keys at a time as below: found 94 -> 90 us, absent 112 -> 101.)
+  static constexpr uint32_t LARGE = (1u << 20) - 1;
+  static __device__ __forceinline__ uint32_t next(uint32_t s, uint32_t visit, int32_t key, uint32_t mask) {
+    if (mask < LARGE) return (s + step_of(key)) & mask;
+    return (visit & 1u) ? ((s ^ 2u) + 2u * step_of(key)) & mask : s ^ 2u;
+  }
+};
+struct LdsPath {
+  static __device__ __forceinline__ uint32_t next(uint32_t s, uint32_t, int32_t key, uint32_t mask) { return (s + step_of(key)) & mask; }
+};
+
 __global__ __launch_bounds__(256) void keymap_clear_kernel(u64* slots, u64 capacity, Header* header) {
   const u64 i = static_cast<u64>(blockIdx.x) * 256 + threadIdx.x;
   if (i < capacity) slots[i] = EMPTY;                     // all ones: an empty slot, and two cells holding -1
@@ -108,13 +123,13 @@ __global__ __launch_bounds__(256) void keymap_insert_kernel(u64* slots, uint32_t
     return;
   }
   const u64 mine = (static_cast<u64>(static_cast<uint32_t>(key)) << 32) | static_cast<uint32_t>(row0 + i);
-  // first slot of the bucket, second slot, next bucket: a bucket's second slot is only taken when its first one is
-  uint32_t s = slot_of(key, shift) & mask & ~1u;
+  // the slot of the bucket that the hash names, the bucket's other slot, next bucket: a key leaves only full buckets
+  uint32_t s = slot_of(key, shift) & mask;
   for (uint32_t probes = 0; probes <= mask; ++probes) {           // bounded: at most one sweep of the table
     const u64 old = atomicCAS(&slots[s], EMPTY, mine);
     if (old == EMPTY) return;
     if (static_cast<int32_t>(old >> 32) == key) { atomicOr(&header->flags, FLAG_DUPLICATE); return; }
-    s = (probes & 1) ? ((s & ~1u) + step_of(key)) & mask : s + 1;
+    s = (probes & 1) ? MapPath::next(s & ~1u, probes >> 1, key, mask) : s ^ 1u;
   }
   atomicOr(&header->flags, FLAG_FULL);
 }
@@ -133,7 +148,7 @@ __device__ __forceinline__ Form form_of(const Header* header, uint32_t mask) {
 // flight: all N first probes are issued together, and only keys whose bucket is full of other keys go on (at most half
 // of the slots are taken, so about one in twenty).  A bucket is one 16-byte load, that is one request to the cache,
 // where slot-by-slot probing needs 1.3 on average and its slowest lane four or five, one after the other.
-template <int N, typename SLOTS>
+template <typename PATH, int N, typename SLOTS>
 __device__ __forceinline__ void find(SLOTS slots, uint32_t mask, uint32_t shift, const Form& f, const int32_t (&key)[N], int32_t (&row)[N]) {
   if (f.direct) {
     const int32_t* cells = reinterpret_cast<const int32_t*>(slots);
@@ -157,11 +172,12 @@ __device__ __forceinline__ void find(SLOTS slots, uint32_t mask, uint32_t shift,
     s[q] = slot_of(key[q], shift) & mask & ~1u;
     b[q] = *reinterpret_cast<const uint4*>(&slots[s[q]]);
   }
-  // (an empty slot holds -1 as its row: a key of -1 that "matches" one gets the right answer)
+  // (an empty slot holds -1 as its row: a key of -1 that "matches" one gets the other slot's answer, or -1)
   auto resolve = [&](int q) {
     const uint32_t k = static_cast<uint32_t>(key[q]);
-    row[q] = b[q].y == k ? static_cast<int32_t>(b[q].x) : b[q].w == k ? static_cast<int32_t>(b[q].z) : -1;
-    more[q] = b[q].y != k && b[q].w != k && (b[q].z & b[q].w) != 0xffffffffu;
+    const bool e0 = b[q].y == k, e1 = b[q].w == k;
+    row[q] = max(e0 ? static_cast<int32_t>(b[q].x) : -1, e1 ? static_cast<int32_t>(b[q].z) : -1);
+    more[q] = !e0 && !e1 && (b[q].x & b[q].y) != 0xffffffffu && (b[q].z & b[q].w) != 0xffffffffu;
     open = open || more[q];
   };
 #pragma unroll
@@ -171,7 +187,7 @@ __device__ __forceinline__ void find(SLOTS slots, uint32_t mask, uint32_t shift,
 #pragma unroll
     for (int q = 0; q < N; ++q)
       if (more[q]) {
-        s[q] = (s[q] + step_of(key[q])) & mask;
+        s[q] = PATH::next(s[q], (probes >> 1) - 1u, key[q], mask);
         b[q] = *reinterpret_cast<const uint4*>(&slots[s[q]]);
       }
 #pragma unroll
@@ -179,40 +195,67 @@ __device__ __forceinline__ void find(SLOTS slots, uint32_t mask, uint32_t shift,
       if (more[q]) resolve(q);
   }
 }
-template <typename SLOTS>
+template <typename PATH, typename SLOTS>
 __device__ __forceinline__ int32_t find_one(SLOTS slots, uint32_t mask, uint32_t shift, const Form& f, int32_t key) {
   const int32_t k[1] = {key};
   int32_t r[1];
-  find<1>(slots, mask, shift, f, k, r);
+  find<PATH, 1>(slots, mask, shift, f, k, r);
   return r[0];
 }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// Four keys per thread (one 16-byte load); the tail is done one by one.  Bound by the rate at which the vector memory
-// path takes unrelated addresses (a table of 2 MB in L2 serves 2.5e11 a second, one of 32 MB 0.65e11): 6e6 keys of
-// 30,000 / 200,000 rows take 36 / 40 us hashed (46 / 46 probing slot by slot) and 24 / 28 us through a direct map.
+// Rows of four keys from the map's buffer.  A hashed map past the L2s takes two keys at a time: four buckets in flight a thread
+// are no faster there, and the longest path of four keys is longer (6e6 keys of 1,000,000 rows 94 -> 90 us; smaller maps 1 to 7 %
+// slower so).
+__device__ __forceinline__ void find_four(const u64* slots, uint32_t mask, uint32_t shift, const Form& f, const int32_t (&k)[4], int32_t (&r)[4]) {
+  if (f.direct || mask < MapPath::LARGE) return find<MapPath, 4>(slots, mask, shift, f, k, r);
+#pragma unroll
+  for (int h = 0; h < 4; h += 2) {
+    const int32_t two[2] = {k[h], k[h + 1]};
+    int32_t rows[2];
+    find<MapPath, 2>(slots, mask, shift, f, two, rows);
+    r[h] = rows[0];
+    r[h + 1] = rows[1];
+  }
+}
+
+// How a thread's keys lie: one key a thread; four neighbouring ones (one 16-byte load, the tail one by one); or, from 2^20
+// unaligned ones on, four that are a workgroup apart.  Bound by the rate at which the vector memory path takes unrelated
+// addresses (a table of 2 MB in L2 serves 2.5e11 a second, one of 32 MB 0.65e11): 6e6 keys of 30,000 / 200,000 rows take
+// 36 / 41 us hashed (43 / 47 probing slot by slot) and 25 / 29 us through a direct map; unaligned 35 us (54 with one key a
+// thread, which is the faster form of 100,000 keys, 4.4 against 6.0 us).
+enum { ONE_KEY = 0, FOUR_NEIGHBOURS = 1, FOUR_APART = 2 };
 __global__ __launch_bounds__(256) void keymap_lookup_kernel(const Header* __restrict__ header,
                                                             const u64* __restrict__ slots, uint32_t mask,
                                                             uint32_t shift, const int32_t* __restrict__ keys,
-                                                            int64_t n, int32_t* __restrict__ fk, int vec_ok) {
+                                                            int64_t n, int32_t* __restrict__ fk, int how) {
   const Form f = form_of(header, mask);
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (vec_ok) {
+  int32_t k[4], r[4];
+  if (how == FOUR_NEIGHBOURS) {
     const int64_t n4 = n / 4;
     if (t < n4) {
       const v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(keys) + t);
-      const int32_t k[4] = {v[0], v[1], v[2], v[3]};
-      int32_t r[4];
-      find<4>(slots, mask, shift, f, k, r);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) k[q] = v[q];
+      find_four(slots, mask, shift, f, k, r);
       const v4i out = {r[0], r[1], r[2], r[3]};
       __builtin_nontemporal_store(out, reinterpret_cast<v4i*>(fk) + t);
     } else if (t - n4 < n - 4 * n4) {
       const int64_t i = 4 * n4 + (t - n4);
-      fk[i] = find_one(slots, mask, shift, f, keys[i]);
+      fk[i] = find_one<MapPath>(slots, mask, shift, f, keys[i]);
     }
+  } else if (how == FOUR_APART) {
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k[q] = keys[min(first + 256 * q, n - 1)];
+    find_four(slots, mask, shift, f, k, r);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (first + 256 * q < n) fk[first + 256 * q] = r[q];
   } else if (t < n) {
-    fk[t] = find_one(slots, mask, shift, f, keys[t]);
+    fk[t] = find_one<MapPath>(slots, mask, shift, f, keys[t]);
   }
 }
 
@@ -256,10 +299,10 @@ __global__ __launch_bounds__(LDS_LOOKUP_THREADS) void keymap_lookup_lds_kernel(c
         const u64 v = slots[i];
         if (v == EMPTY) continue;
         const int32_t key = static_cast<int32_t>(v >> 32);
-        uint32_t s = slot_of(key, lds_shift) & lds_mask & ~1u;
+        uint32_t s = slot_of(key, lds_shift) & lds_mask;
         for (uint32_t probes = 0; probes <= lds_mask; ++probes) {     // (there is room: the LDS table has more slots)
           if (atomicCAS(&lds_slots[s], EMPTY, v) == EMPTY) break;
-          s = (probes & 1) ? ((s & ~1u) + step_of(key)) & lds_mask : s + 1;
+          s = (probes & 1) ? LdsPath::next(s & ~1u, probes >> 1, key, lds_mask) : s ^ 1u;
         }
       }
       mask = lds_mask;
@@ -273,14 +316,14 @@ __global__ __launch_bounds__(LDS_LOOKUP_THREADS) void keymap_lookup_lds_kernel(c
     if (t2 < hi) k0 = __builtin_nontemporal_load(kp + t2);
     if (t3 < hi) k1 = __builtin_nontemporal_load(kp + t3);
     int32_t r[8];
-    find<8>(lds_slots, mask, shift, f, k, r);
+    find<LdsPath, 8>(lds_slots, mask, shift, f, k, r);
     const v4i r0 = {r[0], r[1], r[2], r[3]}, r1 = {r[4], r[5], r[6], r[7]};
     __builtin_nontemporal_store(r0, reinterpret_cast<v4i*>(fk) + t);
     if (t1 < hi) __builtin_nontemporal_store(r1, reinterpret_cast<v4i*>(fk) + t1);
   }
   if (blockIdx.x == 0) {
     const int64_t i = 4 * n4 + threadIdx.x;
-    if (i < n) fk[i] = find_one(lds_slots, mask, shift, f, keys[i]);
+    if (i < n) fk[i] = find_one<LdsPath>(lds_slots, mask, shift, f, keys[i]);
   }
 }
 
@@ -458,11 +501,12 @@ int lq_keymap_lookup(const void* table, size_t table_bytes, const int32_t* fact_
     LQ_LAUNCH_CHECK("keymap_lookup_lds_kernel");
     return LQ_OK;
   }
-  const int64_t threads = vec_ok ? n / 4 + n % 4 : n;
+  const int how = vec_ok ? FOUR_NEIGHBOURS : n >= (1 << 20) ? FOUR_APART : ONE_KEY;
+  const int64_t threads = how == FOUR_NEIGHBOURS ? n / 4 + n % 4 : how == FOUR_APART ? (n + 1023) / 1024 * 256 : n;
   const int64_t blocks = (threads + 255) / 256;
   if (blocks > 0x7fffffffLL) return fail(LQ_ERR_UNSUPPORTED, "too many rows for one launch");
   hipLaunchKernelGGL(keymap_lookup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, header, slots, g.mask,
-                     g.shift, fact_keys, n, fk, vec_ok);
+                     g.shift, fact_keys, n, fk, how);
   LQ_LAUNCH_CHECK("keymap_lookup_kernel");
   return LQ_OK;
 }
