@@ -65,6 +65,7 @@ def graph_time(fn, reps=16, iters=10, warmup=2):
     the pace of the GPU, for calls so short that the Python caller would otherwise set the pace."""
     import torch
     gs = torch.cuda.Stream()
+    gs.wait_stream(torch.cuda.current_stream())     # fn()'s inputs, and blocks freed there that it may be given
     with torch.cuda.stream(gs):
         fn()
     torch.cuda.synchronize()
