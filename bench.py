@@ -6,15 +6,16 @@ pre-fusion (lq_project_dims) followed by the join-computation stage
 (lq_fused_join_predict).  The headline workload is the 2-layer-MLP star schema
 (10M fact rows, dimensions of 1e3/1e4/1e5 rows, MLP 100 -> 64 -> 1, fp32).
 
-Prints ONE JSON line.  Besides the contract fields it carries
+Prints ONE JSON line on stdout: the contract's fields and
   roofline      - the dominant kernel (the fused gather kernel) against the HBM roof, from algorithmic
                   bytes / its own event-timed duration, next to the cache-gather yardstick that binds it
   cpu_baseline  - the fp64 CPU oracle timed on a bounded prefix of the same workload (all host threads)
+  summary       - the five named configurations in a few numbers each
+and, as one JSON line on stderr, every cell behind them with its notes:
   yardsticks    - what this GPU delivers for a plain copy, a read sweep (HBM / Infinity Cache) and random row
                   gathers: the measured roofs the per-configuration cells are quoted against
   one cell per configuration / leg (each event-timed on the launch stream: mean, median and min; the
   non-fused pipeline beside the fused one; the CPU oracle at 1 thread and at all threads under "cpu")
-  summary       - right after the contract's keys: the five named configurations in a few numbers each
 """
 from __future__ import annotations
 
@@ -886,13 +887,23 @@ def main():
             "host_threads_used_by_the_oracle": cpu_threads() if do_cpu else None,
         }
 
-    # the contract's keys and the per-configuration summary first (a reader that keeps only the head of the line still
-    # has every headline figure), the detailed cells after them
-    head = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
-            "dtype", "data", "config", "roofline", "cpu_baseline", "summary")
-    ordered = {k: out[k] for k in head if k in out}
-    ordered.update({k: v for k, v in out.items() if k not in ordered})
-    print(json.dumps(ordered))
+    # One short line on stdout: the contract's keys, the roof and the baseline in numbers and a summary of the named
+    # configurations, so that a reader that keeps only the end of the output has every headline figure.  All cells, with
+    # their notes, go to stderr (a single leg, run for profiling, has no headline: its cells are the line).
+    if "metric" not in out:
+        print(json.dumps(out))
+        return
+    print(json.dumps(out), file=sys.stderr)
+    short = lambda v: float(f"{v:.6g}") if isinstance(v, float) else v
+    line = {k: short(out[k]) for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                                       "scaling", "vs_baseline", "dtype", "data", "config")}
+    for cell, keys in (("roofline", ("bound", "achieved", "peak", "unit", "frac", "gather_frac_of_yardstick")),
+                       ("cpu_baseline", ("value", "unit", "cores", "kind"))):
+        if cell in out:
+            line[cell] = {k: short(out[cell][k]) for k in keys}
+    if "summary" in out:
+        line["summary"] = out["summary"]
+    print(json.dumps(line))
 
 
 if __name__ == "__main__":
