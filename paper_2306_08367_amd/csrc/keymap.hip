@@ -11,7 +11,7 @@
 //     one 4-byte read per fact row, no comparison, no probing;
 //   * hashed: otherwise an open-addressing table over the keys (capacity a power of two of at least
 //     twice the key count, 8-byte slots "key << 32 | row", two slots to a 16-byte bucket, double
-//     hashing over buckets): one probe for nearly every fact row instead of log2(r) dependent
+//     hashing over buckets or pairs of them): one probe for nearly every fact row instead of log2(r) dependent
 //     searches.
 // Both take inserts for incremental updates (a direct map only inside its window), and the fact
 // side streams through once.  A key that is not in the map gives -1 (the row does not appear in
@@ -46,19 +46,23 @@ __device__ __forceinline__ uint32_t step_of(int32_t key) {
   return 2u * ((static_cast<uint32_t>(key) * 0x85EBCA6Bu >> 8) | 1u);
 }
 
-// The bucket after the visit-th (0, 1, ..) on a key's path, `s` and the result even slots.
-struct MapPath {
-  // A map past an XCD's L2 (2^20 slots are 8 MB) goes to the other bucket of the same 32 bytes first: what bounds its lookups
-  // is the lines that cross the fabric.  With smaller maps the jump costs the same, and paths stay shorter.
-  // (6e6 keys of 1,000,000 rows, with two keys at a time as below: found 94 -> 90 us, absent 112 -> 101.)
-  static constexpr uint32_t LARGE = (1u << 20) - 1;
+// A key's path through the buckets.  `next`: the bucket after the visit-th (0, 1, ..) one, `s` and the result even slots.
+// `EITHER_SLOT`: a key starts at the slot of its bucket that the hash names, so an empty slot may be either one; else at the
+// bucket's first slot, and a bucket's second slot is only taken when its first one is.
+struct NearPath {                     // maps that an L2 holds, and copies in LDS
+  static constexpr bool EITHER_SLOT = false;
+  static __device__ __forceinline__ uint32_t next(uint32_t s, uint32_t, int32_t key, uint32_t mask) { return (s + step_of(key)) & mask; }
+};
+// What bounds larger maps is the lines that cross the fabric: the other bucket of the same 32 bytes comes first, and fewer
+// compare-and-swaps of a build find their slot taken.  With smaller maps a jump costs the same, and shorter paths and fewer
+// tests count.  (6e6 keys of 1,000,000 rows, with two keys at a time as below: found 94 -> 89 us, absent 112 -> 101; map of
+// 5e6 keys built in 289 -> 269; the same form for 30,000 and 200,000 rows 1 to 3 % slower.)
+struct FarPath {
+  static constexpr uint32_t MASK = (1u << 20) - 1;        // 8 MB of slots: twice an L2
+  static constexpr bool EITHER_SLOT = true;
   static __device__ __forceinline__ uint32_t next(uint32_t s, uint32_t visit, int32_t key, uint32_t mask) {
-    if (mask < LARGE) return (s + step_of(key)) & mask;
     return (visit & 1u) ? ((s ^ 2u) + 2u * step_of(key)) & mask : s ^ 2u;
   }
-};
-struct LdsPath {
-  static __device__ __forceinline__ uint32_t next(uint32_t s, uint32_t, int32_t key, uint32_t mask) { return (s + step_of(key)) & mask; }
 };
 
 __global__ __launch_bounds__(256) void keymap_clear_kernel(u64* slots, u64 capacity, Header* header) {
@@ -96,7 +100,7 @@ __device__ __forceinline__ bool range_fits(int32_t lo, int32_t hi, u64 capacity)
 
 // BUILD: called right after the min / max pass; every thread derives the form of the map from the
 // key range and the first one records it.  Otherwise (incremental insert) the recorded form is used.
-template <bool BUILD>
+template <bool BUILD, typename PATH>
 __global__ __launch_bounds__(256) void keymap_insert_kernel(u64* slots, uint32_t mask, uint32_t shift,
                                                             const int32_t* __restrict__ keys, int64_t r,
                                                             int64_t row0, Header* header) {
@@ -123,13 +127,13 @@ __global__ __launch_bounds__(256) void keymap_insert_kernel(u64* slots, uint32_t
     return;
   }
   const u64 mine = (static_cast<u64>(static_cast<uint32_t>(key)) << 32) | static_cast<uint32_t>(row0 + i);
-  // the slot of the bucket that the hash names, the bucket's other slot, next bucket: a key leaves only full buckets
-  uint32_t s = slot_of(key, shift) & mask;
+  // one slot of the bucket, its other slot, next bucket: a key leaves only full buckets
+  uint32_t s = slot_of(key, shift) & (PATH::EITHER_SLOT ? mask : mask & ~1u);
   for (uint32_t probes = 0; probes <= mask; ++probes) {           // bounded: at most one sweep of the table
     const u64 old = atomicCAS(&slots[s], EMPTY, mine);
     if (old == EMPTY) return;
     if (static_cast<int32_t>(old >> 32) == key) { atomicOr(&header->flags, FLAG_DUPLICATE); return; }
-    s = (probes & 1) ? MapPath::next(s & ~1u, probes >> 1, key, mask) : s ^ 1u;
+    s = (probes & 1) ? PATH::next(s & ~1u, probes >> 1, key, mask) : s ^ 1u;
   }
   atomicOr(&header->flags, FLAG_FULL);
 }
@@ -176,8 +180,13 @@ __device__ __forceinline__ void find(SLOTS slots, uint32_t mask, uint32_t shift,
   auto resolve = [&](int q) {
     const uint32_t k = static_cast<uint32_t>(key[q]);
     const bool e0 = b[q].y == k, e1 = b[q].w == k;
-    row[q] = max(e0 ? static_cast<int32_t>(b[q].x) : -1, e1 ? static_cast<int32_t>(b[q].z) : -1);
-    more[q] = !e0 && !e1 && (b[q].x & b[q].y) != 0xffffffffu && (b[q].z & b[q].w) != 0xffffffffu;
+    more[q] = !e0 && !e1 && (b[q].z & b[q].w) != 0xffffffffu;
+    if constexpr (PATH::EITHER_SLOT) {
+      row[q] = max(e0 ? static_cast<int32_t>(b[q].x) : -1, e1 ? static_cast<int32_t>(b[q].z) : -1);
+      more[q] = more[q] && (b[q].x & b[q].y) != 0xffffffffu;
+    } else {
+      row[q] = e0 ? static_cast<int32_t>(b[q].x) : e1 ? static_cast<int32_t>(b[q].z) : -1;
+    }
     open = open || more[q];
   };
 #pragma unroll
@@ -205,19 +214,24 @@ __device__ __forceinline__ int32_t find_one(SLOTS slots, uint32_t mask, uint32_t
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// Rows of four keys from the map's buffer.  A hashed map past the L2s takes two keys at a time: four buckets in flight a thread
-// are no faster there, and the longest path of four keys is longer (6e6 keys of 1,000,000 rows 94 -> 90 us; smaller maps 1 to 7 %
-// slower so).
+// Rows of four keys from the map's buffer.  A hashed map past an L2 takes two keys at a time: four buckets in flight a thread
+// are no faster there, and the longest path of four keys is longer (smaller and direct maps are 3 to 6 % slower so).
+template <typename PATH>
 __device__ __forceinline__ void find_four(const u64* slots, uint32_t mask, uint32_t shift, const Form& f, const int32_t (&k)[4], int32_t (&r)[4]) {
-  if (f.direct || mask < MapPath::LARGE) return find<MapPath, 4>(slots, mask, shift, f, k, r);
+  if constexpr (PATH::EITHER_SLOT) {
+    if (!f.direct) {
 #pragma unroll
-  for (int h = 0; h < 4; h += 2) {
-    const int32_t two[2] = {k[h], k[h + 1]};
-    int32_t rows[2];
-    find<MapPath, 2>(slots, mask, shift, f, two, rows);
-    r[h] = rows[0];
-    r[h + 1] = rows[1];
+      for (int h = 0; h < 4; h += 2) {
+        const int32_t two[2] = {k[h], k[h + 1]};
+        int32_t rows[2];
+        find<PATH, 2>(slots, mask, shift, f, two, rows);
+        r[h] = rows[0];
+        r[h + 1] = rows[1];
+      }
+      return;
+    }
   }
+  find<PATH, 4>(slots, mask, shift, f, k, r);
 }
 
 // How a thread's keys lie: one key a thread; four neighbouring ones (one 16-byte load, the tail one by one); or, from 2^20
@@ -226,6 +240,7 @@ __device__ __forceinline__ void find_four(const u64* slots, uint32_t mask, uint3
 // 36 / 41 us hashed (43 / 47 probing slot by slot) and 25 / 29 us through a direct map; unaligned 35 us (54 with one key a
 // thread, which is the faster form of 100,000 keys, 4.4 against 6.0 us).
 enum { ONE_KEY = 0, FOUR_NEIGHBOURS = 1, FOUR_APART = 2 };
+template <typename PATH>
 __global__ __launch_bounds__(256) void keymap_lookup_kernel(const Header* __restrict__ header,
                                                             const u64* __restrict__ slots, uint32_t mask,
                                                             uint32_t shift, const int32_t* __restrict__ keys,
@@ -239,23 +254,23 @@ __global__ __launch_bounds__(256) void keymap_lookup_kernel(const Header* __rest
       const v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(keys) + t);
 #pragma unroll
       for (int q = 0; q < 4; ++q) k[q] = v[q];
-      find_four(slots, mask, shift, f, k, r);
+      find_four<PATH>(slots, mask, shift, f, k, r);
       const v4i out = {r[0], r[1], r[2], r[3]};
       __builtin_nontemporal_store(out, reinterpret_cast<v4i*>(fk) + t);
     } else if (t - n4 < n - 4 * n4) {
       const int64_t i = 4 * n4 + (t - n4);
-      fk[i] = find_one<MapPath>(slots, mask, shift, f, keys[i]);
+      fk[i] = find_one<PATH>(slots, mask, shift, f, keys[i]);
     }
   } else if (how == FOUR_APART) {
     const int64_t first = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x;
 #pragma unroll
     for (int q = 0; q < 4; ++q) k[q] = keys[min(first + 256 * q, n - 1)];
-    find_four(slots, mask, shift, f, k, r);
+    find_four<PATH>(slots, mask, shift, f, k, r);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (first + 256 * q < n) fk[first + 256 * q] = r[q];
   } else if (t < n) {
-    fk[t] = find_one<MapPath>(slots, mask, shift, f, keys[t]);
+    fk[t] = find_one<PATH>(slots, mask, shift, f, keys[t]);
   }
 }
 
@@ -299,10 +314,10 @@ __global__ __launch_bounds__(LDS_LOOKUP_THREADS) void keymap_lookup_lds_kernel(c
         const u64 v = slots[i];
         if (v == EMPTY) continue;
         const int32_t key = static_cast<int32_t>(v >> 32);
-        uint32_t s = slot_of(key, lds_shift) & lds_mask;
+        uint32_t s = slot_of(key, lds_shift) & lds_mask & ~1u;
         for (uint32_t probes = 0; probes <= lds_mask; ++probes) {     // (there is room: the LDS table has more slots)
           if (atomicCAS(&lds_slots[s], EMPTY, v) == EMPTY) break;
-          s = (probes & 1) ? LdsPath::next(s & ~1u, probes >> 1, key, lds_mask) : s ^ 1u;
+          s = (probes & 1) ? NearPath::next(s & ~1u, probes >> 1, key, lds_mask) : s + 1;
         }
       }
       mask = lds_mask;
@@ -316,14 +331,14 @@ __global__ __launch_bounds__(LDS_LOOKUP_THREADS) void keymap_lookup_lds_kernel(c
     if (t2 < hi) k0 = __builtin_nontemporal_load(kp + t2);
     if (t3 < hi) k1 = __builtin_nontemporal_load(kp + t3);
     int32_t r[8];
-    find<LdsPath, 8>(lds_slots, mask, shift, f, k, r);
+    find<NearPath, 8>(lds_slots, mask, shift, f, k, r);
     const v4i r0 = {r[0], r[1], r[2], r[3]}, r1 = {r[4], r[5], r[6], r[7]};
     __builtin_nontemporal_store(r0, reinterpret_cast<v4i*>(fk) + t);
     if (t1 < hi) __builtin_nontemporal_store(r1, reinterpret_cast<v4i*>(fk) + t1);
   }
   if (blockIdx.x == 0) {
     const int64_t i = 4 * n4 + threadIdx.x;
-    if (i < n) fk[i] = find_one<LdsPath>(lds_slots, mask, shift, f, keys[i]);
+    if (i < n) fk[i] = find_one<NearPath>(lds_slots, mask, shift, f, keys[i]);
   }
 }
 
@@ -435,7 +450,8 @@ int lq_keymap_insert(void* table, size_t table_bytes, const int32_t* keys, int64
   Header* header = static_cast<Header*>(table);
   u64* slots = static_cast<u64*>(table) + HEADER / 8;
   if (n_keys > 0) {
-    hipLaunchKernelGGL(keymap_insert_kernel<false>, dim3(static_cast<unsigned>((n_keys + 255) / 256)), dim3(256), 0, s,
+    const auto kernel = g.mask >= FarPath::MASK ? keymap_insert_kernel<false, FarPath> : keymap_insert_kernel<false, NearPath>;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((n_keys + 255) / 256)), dim3(256), 0, s,
                        slots, g.mask, g.shift, keys, n_keys, first_row, header);
     LQ_LAUNCH_CHECK("keymap_insert_kernel");
   }
@@ -461,7 +477,8 @@ int lq_keymap_build(void* table, size_t table_bytes, const int32_t* keys, int64_
     const unsigned mm_blocks = static_cast<unsigned>(std::min<int64_t>((n_keys + 1023) / 1024, 256));
     hipLaunchKernelGGL(keymap_minmax_kernel, dim3(mm_blocks), dim3(256), 0, s, keys, n_keys, header);
     LQ_LAUNCH_CHECK("keymap_minmax_kernel");
-    hipLaunchKernelGGL(keymap_insert_kernel<true>, dim3(static_cast<unsigned>((n_keys + 255) / 256)), dim3(256), 0, s,
+    const auto kernel = g.mask >= FarPath::MASK ? keymap_insert_kernel<true, FarPath> : keymap_insert_kernel<true, NearPath>;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((n_keys + 255) / 256)), dim3(256), 0, s,
                        slots, g.mask, g.shift, keys, n_keys, static_cast<int64_t>(0), header);
     LQ_LAUNCH_CHECK("keymap_insert_kernel");
   }
@@ -505,7 +522,8 @@ int lq_keymap_lookup(const void* table, size_t table_bytes, const int32_t* fact_
   const int64_t threads = how == FOUR_NEIGHBOURS ? n / 4 + n % 4 : how == FOUR_APART ? (n + 1023) / 1024 * 256 : n;
   const int64_t blocks = (threads + 255) / 256;
   if (blocks > 0x7fffffffLL) return fail(LQ_ERR_UNSUPPORTED, "too many rows for one launch");
-  hipLaunchKernelGGL(keymap_lookup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, header, slots, g.mask,
+  const auto kernel = g.mask >= FarPath::MASK ? keymap_lookup_kernel<FarPath> : keymap_lookup_kernel<NearPath>;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, header, slots, g.mask,
                      g.shift, fact_keys, n, fk, how);
   LQ_LAUNCH_CHECK("keymap_lookup_kernel");
   return LQ_OK;
