@@ -26,30 +26,26 @@ struct Header64 {
   i64 min_key, max_key;      // of the keys given to the build
 };
 
-// Where a key's path through a table of a power of two of slots begins (`shift` of the slots, 64 - log2), and the distance to
-// its next bucket in slots: an odd number of buckets that depends on the key, because with a fixed distance full buckets
-// grow into runs.
-// The map itself mixes the key's halves before and after the product: a product alone lays the multiples of one number out
-// in a lattice that may favour some buckets (a million multiples of 1,000,003: 40 % of the keys past their first bucket
-// and a longest path of 84 buckets, 10 % and 14 so).
-struct MapPath {
-  static __device__ __forceinline__ uint32_t mixed(i64 key) {
-    u64 h = static_cast<u64>(key);
-    h = (h ^ (h >> 29)) * 0x9E3779B97F4A7C15ull;
-    return (static_cast<uint32_t>(h) ^ static_cast<uint32_t>(h >> 32)) * 0x85EBCA6Bu;
-  }
-  static __device__ __forceinline__ uint32_t slot(i64 key, uint32_t shift) { return mixed(key) >> (shift - 32); }
-  static __device__ __forceinline__ uint32_t step(i64 key) { return 2u * (mixed(key) | 1u); }
-};
-// A map spread in LDS is at most a quarter full, and a further bucket there costs little: one product.
-struct SpreadPath {
-  static __device__ __forceinline__ uint32_t slot(i64 key, uint32_t shift) {
-    return static_cast<uint32_t>((static_cast<u64>(key) * 0x9E3779B97F4A7C15ull) >> shift);
-  }
-  static __device__ __forceinline__ uint32_t step(i64 key) {
-    return 2u * (static_cast<uint32_t>((static_cast<u64>(key) * 0xC2B2AE3D27D4EB4Full) >> 40) | 1u);
-  }
-};
+// The key is folded into one half, and that twice into itself, before the product.  One product alone lays evenly spaced
+// keys out in a lattice: mostly an even one, but some spacings fill a few buckets over and over, and with a second product of
+// the key as the distance to the next bucket the paths of such keys run into each other (400,000 keys 8 apart: map built in
+// 30 ms, 3e6 lookups 13.2 ms; folded 46 and 48 us.  8,192 keys 101 apart, spread in LDS: 925 -> 17 and 630 -> 27 us.
+// 2,500,000 scattered keys of 500 and 2,000 rows in LDS 2 % slower, of 4,096 rows 17.2 -> 13.3 us).  Over 48 spacings of 8 to
+// 2^44 the longest path of 500 to 200,000 keys has 12 buckets, as with a 64-bit product between folds, which costs
+// lookups in LDS up to a sixth.
+__device__ __forceinline__ uint32_t mixed(i64 key) {
+  uint32_t h = static_cast<uint32_t>(key) ^ static_cast<uint32_t>(key >> 32) * 0x85EBCA6Bu;
+  h ^= h >> 9;
+  return (h ^ (h >> 4)) * 0x9E3779B1u;
+}
+__device__ __forceinline__ uint32_t slot_of(i64 key, uint32_t shift) { return mixed(key) >> shift; }
+
+// Distance to the next bucket on a key's path, in slots: an odd number of buckets that depends on the key (with a
+// fixed distance full buckets grow into runs).
+__device__ __forceinline__ uint32_t step_of(i64 key) {
+  const uint32_t h = mixed(key);
+  return 2u * (((h ^ (h >> 15)) * 0x85EBCA6Bu >> 8) | 1u);
+}
 
 // Slot s of the table: its bucket is s / 2.
 __device__ __forceinline__ i64* key_at(char* buckets, uint32_t s) {
@@ -113,13 +109,13 @@ __global__ __launch_bounds__(256) void keymap64_insert_kernel(char* buckets, uin
   }
   if (key == EMPTY_KEY) { atomicOr(&header->flags, FLAG_RESERVED); return; }
   // first slot of the bucket, second slot, next bucket: a bucket's second slot is only taken when its first one is
-  uint32_t s = MapPath::slot(key, shift) & mask & ~1u;
+  uint32_t s = slot_of(key, shift) & mask & ~1u;
   for (uint32_t probes = 0; probes <= mask; ++probes) {           // bounded: at most one sweep of the table
     const i64 old = static_cast<i64>(atomicCAS(reinterpret_cast<u64*>(key_at(buckets, s)), static_cast<u64>(EMPTY_KEY),
                                                static_cast<u64>(key)));
     if (old == EMPTY_KEY) { *row_at(buckets, s) = static_cast<int32_t>(row0 + i); return; }
     if (old == key) { atomicOr(&header->flags, FLAG_DUPLICATE); return; }
-    s = (probes & 1) ? ((s & ~1u) + MapPath::step(key)) & mask : s + 1;
+    s = (probes & 1) ? ((s & ~1u) + step_of(key)) & mask : s + 1;
   }
   atomicOr(&header->flags, FLAG_FULL);
 }
@@ -133,14 +129,14 @@ struct Bucket { v2l key; v2i row; };
 
 // Rows of N keys: all first probes together, then only the keys whose bucket is full of other keys (see keymap.hip).
 // `at(slot)` fetches the bucket of an even slot.
-template <typename PATH, int N, typename AT>
+template <int N, typename AT>
 __device__ __forceinline__ void find64(AT&& at, uint32_t mask, uint32_t shift, const i64 (&key)[N], int32_t (&row)[N]) {
   uint32_t s[N];
   Bucket b[N];
   bool open = false, more[N];
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    s[q] = PATH::slot(key[q], shift) & mask & ~1u;
+    s[q] = slot_of(key[q], shift) & mask & ~1u;
     b[q] = at(s[q]);
   }
   auto resolve = [&](int q) {
@@ -157,7 +153,7 @@ __device__ __forceinline__ void find64(AT&& at, uint32_t mask, uint32_t shift, c
 #pragma unroll
     for (int q = 0; q < N; ++q)
       if (more[q]) {
-        s[q] = (s[q] + PATH::step(key[q])) & mask;
+        s[q] = (s[q] + step_of(key[q])) & mask;
         b[q] = at(s[q]);
       }
 #pragma unroll
@@ -183,7 +179,7 @@ __device__ __forceinline__ void find64_in_buffer(const char* buckets, bool direc
     for (int q = 0; q < N; ++q) row[q] = in[q] ? v[q] : -1;
     return;
   }
-  find64<MapPath, N>([&](uint32_t s) {
+  find64<N>([&](uint32_t s) {
     const char* p = buckets + 24 * static_cast<size_t>(s >> 1);
     return Bucket{*reinterpret_cast<const v2l_a8*>(p), *reinterpret_cast<const v2i*>(p + 16)};
   }, mask, shift, key, row);
@@ -248,14 +244,14 @@ __global__ __launch_bounds__(LDS64_THREADS) void keymap64_lookup_lds_kernel(cons
       const i64 key = *reinterpret_cast<const i64*>(p + 8 * (i & 1u));
       if (key == EMPTY_KEY) continue;
       const int32_t row = *reinterpret_cast<const int32_t*>(p + 16 + 4 * (i & 1u));
-      uint32_t s = SpreadPath::slot(key, lds_shift) & mask & ~1u;
+      uint32_t s = slot_of(key, lds_shift) & mask & ~1u;
       for (uint32_t probes = 0; probes <= mask; ++probes) {          // (there is room: at most `slots` keys)
         if (atomicCAS(reinterpret_cast<u64*>(&lkey[s]), static_cast<u64>(EMPTY_KEY), static_cast<u64>(key)) ==
             static_cast<u64>(EMPTY_KEY)) {
           lrow[s] = row;
           break;
         }
-        s = (probes & 1) ? ((s & ~1u) + SpreadPath::step(key)) & mask : s + 1;
+        s = (probes & 1) ? ((s & ~1u) + step_of(key)) & mask : s + 1;
       }
     }
   } else {
@@ -271,7 +267,7 @@ __global__ __launch_bounds__(LDS64_THREADS) void keymap64_lookup_lds_kernel(cons
     if (direct)
       find64_in_buffer<N>(reinterpret_cast<const char*>(lkey), true, base, direct_mask, 0, k, r);
     else
-      find64<std::conditional_t<SPREAD, SpreadPath, MapPath>, N>([&](uint32_t s) {
+      find64<N>([&](uint32_t s) {
         return Bucket{*reinterpret_cast<const v2l*>(&lkey[s]), *reinterpret_cast<const v2i*>(&lrow[s])};
       }, mask, lds_shift, k, r);
   };
@@ -303,7 +299,7 @@ bool geometry64(size_t table_bytes, Geometry64* g) {
   while (HEADER + cap * 2 * 12 <= table_bytes && cap < (1ull << 31)) cap <<= 1;
   int log2 = 0;
   while ((1ull << log2) < cap) ++log2;
-  g->capacity = cap; g->mask = static_cast<uint32_t>(cap - 1); g->shift = static_cast<uint32_t>(64 - log2);
+  g->capacity = cap; g->mask = static_cast<uint32_t>(cap - 1); g->shift = static_cast<uint32_t>(32 - log2);
   return true;
 }
 
@@ -392,7 +388,7 @@ int lq_keymap64_lookup(const void* table, size_t table_bytes, const int64_t* fac
     const auto kernel = g.capacity == LDS64_SLOTS ? keymap64_lookup_lds_kernel<false> : keymap64_lookup_lds_kernel<true>;
     LQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(LDS64_THREADS), lds_bytes, s, header, buckets,
-                       static_cast<uint32_t>(g.capacity), 64u - 13u, reinterpret_cast<const i64*>(fact_keys), n, fk,
+                       static_cast<uint32_t>(g.capacity), 32u - 13u, reinterpret_cast<const i64*>(fact_keys), n, fk,
                        (n4 + blocks - 1) / blocks);
     LQ_LAUNCH_CHECK("keymap64_lookup_lds_kernel");
     return LQ_OK;

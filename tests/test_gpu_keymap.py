@@ -274,13 +274,16 @@ def test_hashed_maps_in_memory(lq, r, off, wide):
             np.testing.assert_array_equal(lookup(table, dev(key_R), fk=fk).cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("r,spacing", [(2_000, 1_000), (2_000, 5_000), (100_000, 16), (100_000, 1_003), (400_000, 101)])
-def test_evenly_spaced_keys_do_not_crowd(lq, r, spacing):
+@pytest.mark.parametrize("wide,r,spacing", [(False, 2_000, 1_000), (False, 2_000, 5_000), (False, 100_000, 16), (False, 100_000, 1_003),
+                                            (False, 400_000, 101), (True, 2_000, 5_000), (True, 4_096, 101), (True, 400_000, 8)])
+def test_evenly_spaced_keys_do_not_crowd(lq, r, spacing, wide):
     """Dimension keys at one spacing: exact, and map and 3e6 lookups take at most three times what as many scattered keys take
     (they take 0.9 to 1.3 times; a hash that lays spaced keys out unevenly takes 4 to 700 times)."""
     g = np.random.default_rng(r)
-    scattered = torch.from_numpy((g.choice(2**31 - 1, size=r, replace=False) + 1).astype(np.int32)).cuda()
-    spaced = torch.from_numpy(((g.permutation(r) + 1) * spacing).astype(np.int32)).cuda()
+    dt = np.int64 if wide else np.int32
+    build, lookup = (lq.lq_keymap64_build, lq.lq_keymap64_lookup) if wide else (lq.lq_keymap_build, lq.lq_keymap_lookup)
+    scattered = torch.from_numpy((g.choice(2**31 - 1, size=r, replace=False) + 1).astype(dt)).cuda()
+    spaced = torch.from_numpy(((g.permutation(r) + 1) * spacing).astype(dt)).cuda()
     row = torch.from_numpy(g.integers(0, r, 3_000_000)).cuda()
     fk = torch.empty(len(row), dtype=torch.int32, device="cuda")
 
@@ -298,8 +301,8 @@ def test_evenly_spaced_keys_do_not_crowd(lq, r, spacing):
 
     took = []
     for keys in (scattered, spaced):
-        table, probe = lq.lq_keymap_build(keys, flags=lq.LQ_CHECK_KEYS), keys[row]
-        assert torch.equal(lq.lq_keymap_lookup(table, probe, fk=fk).long(), row)
-        took.append((fastest(lambda: lq.lq_keymap_build(keys)), fastest(lambda: lq.lq_keymap_lookup(table, probe, fk=fk))))
+        table, probe = build(keys, flags=lq.LQ_CHECK_KEYS), keys[row]
+        assert torch.equal(lookup(table, probe, fk=fk).long(), row)
+        took.append((fastest(lambda: build(keys)), fastest(lambda: lookup(table, probe, fk=fk))))
     (b0, l0), (b1, l1) = took
     assert b1 < 3 * b0 and l1 < 3 * l0, took
