@@ -722,7 +722,7 @@ def main():
             big = res["200000"]["lookup_ms"]
             out["keymap_ssb_sf1"]["hashed_lookups_frac_of_gather_yardstick"] = (nk / (big * 1e-3) / 1e9) / gy
             out["keymap_ssb_sf1"]["note"] = ("hashed_lookups_frac_of_gather_yardstick: keys per second into the 200,000-key map "
-                                             "(3.2 MB of slots at load factor 1/2, 1.5 probes on average) over random 16-byte "
+                                             "(3.2 MB of slots at load factor 1/2, 1.1 buckets read on average) over random 16-byte "
                                              "reads per second from a 2 MB table")
     if want("keymap"):
         guarded("keymap_ssb_sf1", leg_keymap)

@@ -554,13 +554,14 @@ typedef struct {
  * the result is unique.  Group g decomposes as a mixed-radix number over group_card, last column
  * fastest, exactly as the group-by builds it.
  *   group_card  host array of the n_group_cols (0..LQ_MAX_DIMS) cardinalities of the grouping
- *               dimensions, in dimension order; G = their product <= 8192 (this limit is final: the
- *               sort runs in one workgroup's LDS; a larger result is ordered by the caller)
+ *               dimensions, in dimension order; G = their product <= 8192 (this limit is final: a
+ *               packed key keeps 13 bits for the group, and every group is compared with all
+ *               others; a larger result is ordered by the caller)
  *   sums        device int64 [n_measures x G] (may be NULL if no key uses it); counts device int64 [G]
  *   keys        host array of n_keys (0..4) sort keys
  *   order       device int32 [G]: out, the populated groups in order, then -1s
  *   n_out       device int32: out, the number of populated groups
- * Asynchronous; one small workgroup.
+ * Asynchronous, no workspace; one launch: one workgroup for few groups, else one per 32 groups.
  */
 int lq_order_groups(int32_t n_group_cols, const int32_t* group_card, int32_t n_measures,
                     const int64_t* sums, const int64_t* counts, int32_t n_keys,
