@@ -187,7 +187,9 @@ int lq_fusion_advice(const lq_star* star, const lq_model* model, double queries_
  *       stores ReLU(z) for a chunk of rows, then the later layers as dense products on the matrix cores, chunk by
  *       chunk (lq_workspace_bytes(LQ_CALL_FUSED, star, model, chunk_rows) sizes it for a chunk; more rows per
  *       chunk, fewer launches).  Without that room the general kernels run: same results, tens of times slower on
- *       such models
+ *       such models.  For bf16 models of two or three layers with a first layer of 129 to 256 columns over tables of
+ *       more than 10 MB, bytes 256 to 1,279 hold counters that keep the workgroups of a chip die in step (a
+ *       workspace of 1,280 bytes or more; without it the same results, up to 1.25 times as long)
  * star->dims may be NULL here: only n_dims, fks and the row counts in P are used.
  */
 int lq_fused_join_predict(const lq_star* star, const lq_model* model, const lq_mat* P,

@@ -344,6 +344,7 @@ int try_vec(const PredictArgs& a, hipStream_t s) {
 int try_rowbatch64(const PredictArgs& a, hipStream_t s);
 int try_rowbatch_wide(const PredictArgs& a, hipStream_t s);
 int try_fused_bf16(const PredictArgs& a, hipStream_t s);
+int try_fused_slab_bf16(const PredictArgs& a, hipStream_t s);
 int try_fused_tile(const PredictArgs& a, hipStream_t s);
 int try_fused_deep(const PredictArgs& a, hipStream_t s);
 int try_fused_deep_bf16(const PredictArgs& a, hipStream_t s);
@@ -356,7 +357,9 @@ int launch_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
 
 int launch_fused(const PredictArgs& a, hipStream_t s) {
   if (a.n == 0) return LQ_OK;
-  int rc = try_rowbatch64(a, s);
+  int rc = try_fused_slab_bf16(a, s);   // bf16 MLPs on many fact rows
+  if (rc >= 0) return rc;
+  rc = try_rowbatch64(a, s);
   if (rc >= 0) return rc;
   rc = try_fused_deep(a, s);          // three to eight layers, or a second layer of 5..128 outputs
   if (rc >= 0) return rc;
