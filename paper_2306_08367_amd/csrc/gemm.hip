@@ -48,6 +48,13 @@ struct GemmBatch {
   int32_t count;
 };
 
+// The problem this workgroup works on.
+__device__ __forceinline__ int problem_of(const GemmBatch& b) {
+  int p = 0;
+  while (p + 1 < b.count && static_cast<int>(blockIdx.x) >= b.first_tile[p + 1]) ++p;
+  return p;
+}
+
 // ------------------------------------------------------------------ tiled --------------
 
 constexpr int BM = 128;
@@ -352,15 +359,17 @@ constexpr int SKINNY_THREADS = 256;
 // MFMAs whose B operand holds the matching rows of the weight matrix (which rows of k a slot
 // means is irrelevant as long as A and B agree, and they are built from the same index).
 template <typename TA, typename TC>
-__global__ __launch_bounds__(SKINNY_THREADS) void gemm_skinny_kernel(GemmArgs g) {
+__global__ __launch_bounds__(SKINNY_THREADS) void gemm_skinny_kernel(GemmBatch batch) {
+  const int p = problem_of(batch);
+  const GemmArgs& g = batch.g[p];
   constexpr int VEC = Tile<TA>::VEC;
   constexpr bool F32 = sizeof(TA) == 4;
   constexpr int KSTEP = 4 * VEC;             // k covered by one 16-byte load per lane
   const TA* __restrict__ A = static_cast<const TA*>(g.A);
   const TA* __restrict__ B = static_cast<const TA*>(g.B);
   const int lane = threadIdx.x & 63, grp = lane >> 4, i = lane & 15;
-  const int64_t wave = static_cast<int64_t>(blockIdx.x) * (SKINNY_THREADS / 64) + (threadIdx.x >> 6);
-  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * (SKINNY_THREADS / 64);
+  const int64_t wave = static_cast<int64_t>(blockIdx.x - batch.first_tile[p]) * (SKINNY_THREADS / 64) + (threadIdx.x >> 6);
+  const int64_t nwaves = static_cast<int64_t>(batch.first_tile[p + 1] - batch.first_tile[p]) * (SKINNY_THREADS / 64);
   const int64_t npass = (g.M + 15) / 16;
   const float bv = (g.bias && i < g.N) ? Elem<TA>::load(static_cast<const TA*>(g.bias) + i) : 0.f;
 
@@ -536,21 +545,31 @@ int launch_tiled_batch(GemmBatch& b, hipStream_t s) {
   return LQ_OK;
 }
 
+// All problems of the batch have up to 16 columns and the same element types.
+template <typename TA, typename TC>
+int launch_skinny_batch(GemmBatch& b, hipStream_t s) {
+  int64_t blocks = 0;
+  for (int p = 0; p < b.count; ++p) {
+    GemmArgs& g = b.g[p];
+    g.a_vec_ok = aligned(g.A, 16) && (g.lda * sizeof(TA)) % 16 == 0;
+    b.first_tile[p] = static_cast<int32_t>(blocks);
+    blocks += std::min<int64_t>(((g.M + 15) / 16 + 3) / 4, static_cast<int64_t>(num_cus()) * 8);
+  }
+  b.first_tile[b.count] = static_cast<int32_t>(blocks);
+  if (blocks == 0) return LQ_OK;
+  hipLaunchKernelGGL((gemm_skinny_kernel<TA, TC>), dim3(static_cast<unsigned>(blocks)), dim3(SKINNY_THREADS), 0, s, b);
+  LQ_LAUNCH_CHECK("gemm_skinny_kernel");
+  return LQ_OK;
+}
+
 template <typename TA, typename TC>
 int launch_typed(GemmArgs g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return LQ_OK;
-  const size_t es = sizeof(TA);
-  constexpr int VEC = Tile<TA>::VEC;
-  g.a_vec_ok = aligned(g.A, 16) && (g.lda * es) % 16 == 0;
-  g.b_vec_ok = aligned(g.B, 16) && (g.ldb * es) % 16 == 0;
-  (void)VEC;
   if (g.N <= 16) {
-    const int64_t npass = (g.M + 15) / 16;
-    const int64_t blocks = std::min<int64_t>((npass + 3) / 4, static_cast<int64_t>(num_cus()) * 8);
-    hipLaunchKernelGGL((gemm_skinny_kernel<TA, TC>), dim3(static_cast<unsigned>(blocks)), dim3(SKINNY_THREADS),
-                       0, s, g);
-    LQ_LAUNCH_CHECK("gemm_skinny_kernel");
-    return LQ_OK;
+    GemmBatch b{};
+    b.g[0] = g;
+    b.count = 1;
+    return launch_skinny_batch<TA, TC>(b, s);
   }
   if constexpr (sizeof(TA) == 4 && sizeof(TC) == 4) {
     if (g.Kd >= 1 && g.Kd <= SHORT_K && g.N <= 128) {     // (17 to 128 columns: see gemm_short_kernel)
@@ -571,26 +590,64 @@ constexpr int RS_THREADS = 256;
 template <int CTRL> __device__ __forceinline__ float rs_dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
-// Sum over groups of LPR adjacent lanes (8, 16, 32 or 64), result in every lane of the group.
-template <int LPR> __device__ __forceinline__ float rs_allreduce(float y) {
-  y += rs_dpp<0xB1>(y);                  // quad_perm [1,0,3,2]
-  y += rs_dpp<0x4E>(y);                  // quad_perm [2,3,0,1]
-  y += rs_dpp<0x141>(y);                 // row_half_mirror
-  if (LPR >= 16) y += rs_dpp<0x140>(y);  // row_mirror
-  if (LPR >= 32) y += __shfl_xor(y, 16, 64);
-  if (LPR >= 64) y += __shfl_xor(y, 32, 64);
-  return y;
+// One step of a sum over lanes that scatters its results: the lane keeps the half of its V values that its bit selects and
+// gets the other lane's share of that half; a single value is just summed.  `other` fetches from the lane that differs in that bit.
+template <int V, typename F> __device__ __forceinline__ void rs_halve(float* y, bool upper, F other) {
+  if constexpr (V == 1) y[0] += other(y[0]);
+#pragma unroll
+  for (int i = 0; i < V / 2; ++i) {
+    const float keep = upper ? y[V / 2 + i] : y[i], send = upper ? y[i] : y[V / 2 + i];
+    y[i] = keep + other(send);
+  }
+}
+constexpr int rs_half(int v) { return v > 1 ? v / 2 : 1; }
+// Sums of V values (a power of two) over the LPR lanes of a group, V / LPR of them or one in every lane: lane c ends with
+// number rs_first(c) and the ones behind it.  (The mirrored exchanges also flip the lower lane bits, so they come before
+// those have selected anything.)
+template <int V, int LPR> __device__ __forceinline__ void rs_reduce(float (&y)[V], int lane) {
+  constexpr int V1 = LPR >= 16 ? rs_half(V) : V, V2 = rs_half(V1), V3 = rs_half(V2), V4 = rs_half(V3);
+  if constexpr (LPR >= 16) rs_halve<V>(y, lane & 8, [](float v) { return rs_dpp<0x140>(v); });    // row_mirror
+  rs_halve<V1>(y, lane & 4, [](float v) { return rs_dpp<0x141>(v); });                            // row_half_mirror
+  rs_halve<V2>(y, lane & 2, [](float v) { return rs_dpp<0x4E>(v); });                             // quad_perm [2,3,0,1]
+  rs_halve<V3>(y, lane & 1, [](float v) { return rs_dpp<0xB1>(v); });                             // quad_perm [1,0,3,2]
+  if constexpr (LPR >= 32) rs_halve<V4>(y, lane & 16, [](float v) { return __shfl_xor(v, 16, 64); });
+  if constexpr (LPR >= 64) rs_halve<rs_half(V4)>(y, lane & 32, [](float v) { return __shfl_xor(v, 32, 64); });
+}
+template <int V, int LPR> __device__ __forceinline__ int rs_first(int c) {
+  int v = V, at = 0;                        // the selecting bits in the order of the steps
+#pragma unroll
+  for (int bit = LPR >= 16 ? 8 : 4; bit; bit >>= 1)
+    if (v > 1) { v /= 2; at += c & bit ? v : 0; }
+  if (LPR >= 32 && v > 1) { v /= 2; at += c & 16 ? v : 0; }
+  return at;
+}
+// Is c the first of the lanes that end with the same outputs?
+template <int V, int LPR> __device__ __forceinline__ bool rs_stores(int c) {
+  int v = V, twins = 0;
+#pragma unroll
+  for (int bit = LPR >= 16 ? 8 : 4; bit; bit >>= 1)
+    if (v > 1) v /= 2; else twins |= bit;
+  if (LPR >= 32) { if (v > 1) v /= 2; else twins |= 16; }
+  if (LPR >= 64) twins |= 32;
+  return (c & twins) == 0;
 }
 
 // LPR lanes share a row (piece c, c + LPR, ... of its K / 4 pieces); a wavefront works on
 // U x (64 / LPR) rows per step, all loads of a step issued before the first is used.
-// NN = N rounded up to 4 or 8; the weights sit in LDS as [K][NN] with zero padding.  (With more
+// NN = N rounded up to a power of two; the weights sit in LDS as [K][NN] with zero padding.  (With more
 // outputs the products and the per-row sums outweigh the loads and the matrix-core kernel wins.)
+// Bound by reading A, 5.8 TB/s over two tables of 1e6 x 128.  The sums of a step's U x NN outputs are scattered over the
+// lanes of a row and stored by one instruction; summed into every lane and stored an output at a time by the first lane of each row
+// the same took 210 us instead of 183 with 4 outputs, 307 instead of 200 with 7, and 100,000 x 64 26 instead of 19 (with the
+// join of 100,000 rows in each).
 template <int LPR, int NN>
-__global__ __launch_bounds__(RS_THREADS) void gemm_rowsplit_kernel(GemmArgs g) {
+__global__ __launch_bounds__(RS_THREADS) void gemm_rowsplit_kernel(GemmBatch batch) {
   constexpr int RPW = 64 / LPR;             // rows per wavefront and sub-step
   constexpr int U = 4;                      // sub-steps in flight
+  constexpr int V = U * NN, LEFT = V > LPR ? V / LPR : 1;
   extern __shared__ __align__(16) float Bs[];
+  const int prob = problem_of(batch);
+  const GemmArgs& g = batch.g[prob];
   const float* __restrict__ A = static_cast<const float*>(g.A);
   const float* __restrict__ B = static_cast<const float*>(g.B);
   for (int idx = threadIdx.x; idx < g.Kd * NN; idx += RS_THREADS) {
@@ -600,19 +657,18 @@ __global__ __launch_bounds__(RS_THREADS) void gemm_rowsplit_kernel(GemmArgs g) {
   __syncthreads();
   const int lane = threadIdx.x & 63, c = lane % LPR, sub = lane / LPR;
   const int ppr = g.Kd / 4;                 // 16-byte pieces per row
-  const int64_t wave = static_cast<int64_t>(blockIdx.x) * (RS_THREADS / 64) + (threadIdx.x >> 6);
-  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * (RS_THREADS / 64);
+  const int64_t wave = static_cast<int64_t>(blockIdx.x - batch.first_tile[prob]) * (RS_THREADS / 64) + (threadIdx.x >> 6);
+  const int64_t nwaves = static_cast<int64_t>(batch.first_tile[prob + 1] - batch.first_tile[prob]) * (RS_THREADS / 64);
   const int64_t nsteps = (g.M + RPW * U - 1) / (RPW * U);
-  float bv[NN];
+  const int first = rs_first<V, LPR>(c);    // this lane's outputs of a step: sub-step first / NN, column first % NN and on
+  float bv[LEFT];
 #pragma unroll
-  for (int n = 0; n < NN; ++n) bv[n] = (g.bias && n < g.N) ? static_cast<const float*>(g.bias)[n] : 0.f;
+  for (int i = 0; i < LEFT; ++i) bv[i] = (g.bias && first % NN + i < g.N) ? static_cast<const float*>(g.bias)[first % NN + i] : 0.f;
 
   for (int64_t step = wave; step < nsteps; step += nwaves) {
-    float acc[U][NN];
+    float acc[V];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int n = 0; n < NN; ++n) acc[u][n] = 0.f;
+    for (int i = 0; i < V; ++i) acc[i] = 0.f;
     for (int p = c; p < ppr; p += LPR) {
       v4f a[U];
 #pragma unroll
@@ -621,64 +677,70 @@ __global__ __launch_bounds__(RS_THREADS) void gemm_rowsplit_kernel(GemmArgs g) {
         a[u] = v4f{0.f, 0.f, 0.f, 0.f};
         if (row < g.M) a[u] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(A + row * g.lda) + p);
       }
+      v4f w[NN];                              // the piece's four rows of B
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        float b[NN];
+      for (int q = 0; q < NN; ++q) w[q] = *reinterpret_cast<const v4f*>(Bs + 4 * (p * NN + q));
 #pragma unroll
-        for (int q = 0; q < NN / 4; ++q) {
-          const v4f bq = *reinterpret_cast<const v4f*>(Bs + (4 * p + t) * NN + 4 * q);
-          b[4 * q] = bq[0]; b[4 * q + 1] = bq[1]; b[4 * q + 2] = bq[2]; b[4 * q + 3] = bq[3];
-        }
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int n = 0; n < NN; ++n) acc[u][n] = fmaf(a[u][t], b[n], acc[u][n]);
-      }
+          for (int n = 0; n < NN; ++n) acc[u * NN + n] = fmaf(a[u][t], w[(t * NN + n) / 4][(t * NN + n) % 4], acc[u * NN + n]);
     }
+    rs_reduce<V, LPR>(acc, lane);
+    const int64_t row = (step * U + first / NN) * RPW + sub;
+    if (row < g.M && rs_stores<V, LPR>(c)) {
+      float* cr = static_cast<float*>(g.C) + row * g.ldc + first % NN;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int n = 0; n < NN; ++n) acc[u][n] = rs_allreduce<LPR>(acc[u][n]);
-      const int64_t row = (step * U + u) * RPW + sub;
-      if (c == 0 && row < g.M) {
-        float* cr = static_cast<float*>(g.C) + row * g.ldc;
-#pragma unroll
-        for (int n = 0; n < NN; ++n)
-          if (n < g.N) {
-            float x = acc[u][n] + bv[n];
-            if (g.relu) x = fmaxf(x, 0.f);
-            cr[n] = x;
-          }
-      }
+      for (int i = 0; i < LEFT; ++i)
+        if (first % NN + i < g.N) {
+          float x = acc[i] + bv[i];
+          if (g.relu) x = fmaxf(x, 0.f);
+          cr[i] = x;
+        }
     }
   }
 }
 
+// The lanes a row is split over, or 0 when the kernel does not cover the shape.  The choice depends on N, K, the row
+// stride and the alignment only, never on M, so a row computed alone equals the same row computed
+// as part of the whole table.
+int rowsplit_lanes(const GemmArgs& g) {
+  if (g.N > 8 || g.Kd < 32 || g.Kd % 4 || g.lda % 4 || !aligned(g.A, 16) || !aligned(g.C, 4)) return 0;
+  if (static_cast<size_t>(g.Kd) * 8 * sizeof(float) > 64 * 1024) return 0;
+  const int ppr = g.Kd / 4;
+  return ppr <= 8 ? 8 : ppr <= 16 ? 16 : ppr <= 32 ? 32 : 64;
+}
+
+// All problems of the batch have the same number of columns and lanes a row.
 template <int LPR>
-int launch_rowsplit_n(const GemmArgs& g, hipStream_t s) {
-  const int nn = g.N <= 4 ? 4 : 8;
-  const size_t lds = static_cast<size_t>(g.Kd) * nn * sizeof(float);
+int launch_rowsplit_batch(GemmBatch& b, hipStream_t s) {
+  const int N = b.g[0].N, nn = N <= 2 ? N : N <= 4 ? 4 : 8;
+  size_t lds = 0;
   const int rows_per_step = (64 / LPR) * 4;
-  const int64_t nsteps = (g.M + rows_per_step - 1) / rows_per_step;
-  const int64_t blocks = std::min<int64_t>((nsteps + 3) / 4, static_cast<int64_t>(num_cus()) * 16);
+  int64_t blocks = 0;
+  for (int p = 0; p < b.count; ++p) {
+    const GemmArgs& g = b.g[p];
+    lds = std::max(lds, static_cast<size_t>(g.Kd) * nn * sizeof(float));
+    b.first_tile[p] = static_cast<int32_t>(blocks);
+    blocks += std::min<int64_t>(((g.M + rows_per_step - 1) / rows_per_step + 3) / 4, static_cast<int64_t>(num_cus()) * 16);
+  }
+  b.first_tile[b.count] = static_cast<int32_t>(blocks);
   const dim3 grid(static_cast<unsigned>(blocks)), block(RS_THREADS);
-  if (nn == 4) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 4>), grid, block, lds, s, g);
-  else hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 8>), grid, block, lds, s, g);
+  if (nn == 1) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 1>), grid, block, lds, s, b);
+  else if (nn == 2) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 2>), grid, block, lds, s, b);
+  else if (nn == 4) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 4>), grid, block, lds, s, b);
+  else hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 8>), grid, block, lds, s, b);
   LQ_LAUNCH_CHECK("gemm_rowsplit_kernel");
   return LQ_OK;
 }
-
-// Returns -1 when the shape is not one this kernel covers.  The choice depends on N, K, the row
-// stride and the alignment only, never on M, so a row computed alone equals the same row computed
-// as part of the whole table.
-int try_rowsplit(const GemmArgs& g, hipStream_t s) {
-  if (g.N > 8 || g.Kd < 32 || g.Kd % 4 || g.lda % 4 || !aligned(g.A, 16) || !aligned(g.C, 4)) return -1;
-  if (static_cast<size_t>(g.Kd) * 8 * sizeof(float) > 64 * 1024) return -1;
-  const int ppr = g.Kd / 4;
-  if (ppr <= 8) return launch_rowsplit_n<8>(g, s);
-  if (ppr <= 16) return launch_rowsplit_n<16>(g, s);
-  if (ppr <= 32) return launch_rowsplit_n<32>(g, s);
-  return launch_rowsplit_n<64>(g, s);
+int launch_rowsplit(int lanes, GemmBatch& b, hipStream_t s) {
+  switch (lanes) {
+    case 8: return launch_rowsplit_batch<8>(b, s);
+    case 16: return launch_rowsplit_batch<16>(b, s);
+    case 32: return launch_rowsplit_batch<32>(b, s);
+    default: return launch_rowsplit_batch<64>(b, s);
+  }
 }
 
 }  // namespace
@@ -691,9 +753,12 @@ int launch_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.bias = bias;
   g.M = M; g.N = N; g.Kd = Kd; g.relu = relu;
   if (in_dtype == LQ_F32 && out_dtype == LQ_F32) {
-    if (M > 0 && N > 0) {
-      const int rc = try_rowsplit(g, s);
-      if (rc >= 0) return rc;
+    const int lanes = M > 0 && N > 0 ? rowsplit_lanes(g) : 0;
+    if (lanes) {
+      GemmBatch b{};
+      b.g[0] = g;
+      b.count = 1;
+      return launch_rowsplit(lanes, b, s);
     }
     return launch_typed<float, float>(g, s);
   }
@@ -704,13 +769,14 @@ int launch_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
 
 int launch_project_dims(const lq_mat& D, const lq_mat& W, int32_t row_off, const lq_mat& P, hipStream_t s);
 
-// P_k = D_k W[off_k .. off_k + c_k) for all K dimensions; one launch when the tiled kernel serves them.
+// P_k = D_k W[off_k .. off_k + c_k) for all K dimensions: one launch for all tables that the same kernel serves (a launch
+// on a small table is 2 to 3 us whatever it does).
 int launch_project_dims_all(int32_t K, const lq_mat* D, const lq_mat& W, int32_t first_off, const lq_mat* P,
                             hipStream_t s) {
   const size_t es = dtype_size(W.dtype);
-  bool batch = K > 1 && W.cols > 16;
-  for (int k = 0; k < K && batch; ++k) batch = D[k].dtype == D[0].dtype && P[k].dtype == P[0].dtype;
-  if (!batch) {
+  bool same_types = K > 1;
+  for (int k = 0; k < K; ++k) same_types = same_types && D[k].dtype == D[0].dtype && P[k].dtype == P[0].dtype;
+  if (!same_types) {
     int32_t off = first_off;
     for (int k = 0; k < K; ++k) {
       const int rc = launch_project_dims(D[k], W, off, P[k], s);
@@ -719,23 +785,38 @@ int launch_project_dims_all(int32_t K, const lq_mat* D, const lq_mat& W, int32_t
     }
     return LQ_OK;
   }
-  GemmBatch b{};
+  const int32_t in = D[0].dtype, out = P[0].dtype;
+  GemmBatch all{};
   int32_t off = first_off;
   for (int k = 0; k < K; ++k) {
-    GemmArgs& g = b.g[b.count];
+    GemmArgs& g = all.g[all.count];
     g.A = D[k].data; g.lda = D[k].ld;
     g.B = static_cast<const char*>(W.data) + static_cast<size_t>(off) * W.ld * es; g.ldb = W.ld;
     g.C = P[k].data; g.ldc = P[k].ld;
     g.M = D[k].rows; g.N = W.cols; g.Kd = D[k].cols;
     off += D[k].cols;
-    if (g.M > 0) ++b.count;
+    if (g.M > 0) ++all.count;
   }
-  if (b.count == 0) return LQ_OK;
-  const int32_t in = D[0].dtype, out = P[0].dtype;
-  if (in == LQ_F32 && out == LQ_F32) return launch_tiled_batch<float, float>(b, s);
-  if (in == LQ_BF16 && out == LQ_F32) return launch_tiled_batch<bf16_t, float>(b, s);
-  if (in == LQ_BF16 && out == LQ_BF16) return launch_tiled_batch<bf16_t, bf16_t>(b, s);
-  return fail(LQ_ERR_DTYPE, "gemm: f32 inputs cannot produce a bf16 result");
+  if (all.count == 0 || W.cols < 1) return LQ_OK;
+  const bool f32 = in == LQ_F32 && out == LQ_F32, mixed = in == LQ_BF16 && out == LQ_F32, bf16 = in == LQ_BF16 && out == LQ_BF16;
+  if (!f32 && !mixed && !bf16) return fail(LQ_ERR_DTYPE, "gemm: f32 inputs cannot produce a bf16 result");
+  if (W.cols <= 16) {
+    int lanes[LQ_MAX_DIMS];
+    for (int p = 0; p < all.count; ++p) lanes[p] = f32 ? rowsplit_lanes(all.g[p]) : 0;
+    for (const int l : {0, 8, 16, 32, 64}) {
+      GemmBatch b{};
+      for (int p = 0; p < all.count; ++p)
+        if (lanes[p] == l) b.g[b.count++] = all.g[p];
+      if (b.count == 0) continue;
+      const int rc = l ? launch_rowsplit(l, b, s) : f32 ? launch_skinny_batch<float, float>(b, s)
+                     : mixed ? launch_skinny_batch<bf16_t, float>(b, s) : launch_skinny_batch<bf16_t, bf16_t>(b, s);
+      if (rc) return rc;
+    }
+    return LQ_OK;
+  }
+  if (f32) return launch_tiled_batch<float, float>(all, s);
+  if (mixed) return launch_tiled_batch<bf16_t, float>(all, s);
+  return launch_tiled_batch<bf16_t, bf16_t>(all, s);
 }
 
 int launch_project_dims(const lq_mat& D, const lq_mat& W, int32_t row_off, const lq_mat& P,
