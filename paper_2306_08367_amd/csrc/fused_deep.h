@@ -114,38 +114,86 @@ __device__ __forceinline__ void store_rows(const PredictArgs& a, const v4f (&y)[
   }
 }
 
+// Stages a layer's weights as TOUT x TIN tiles (tile ot TIN + kt: 64 lanes x 4 floats).  What bounds calls of few rows is
+// how long a workgroup takes to stage the model: instructions on one wavefront a SIMD, and loads that wait for one another.
+// A wavefront takes whole tiles, so that only the tile number changes from one to the next, a lane's four values leave in
+// one 16-byte store, and the loads of up to four tiles are in flight (none sits behind a branch).  4,099 rows, element by element with
+// the indices worked out anew -> so: 64 -> 32 -> 1 7.8 -> 6.8 us, 64 -> 64 -> 64 -> 1 13.2 -> 9.9, 200 -> 64 -> 1 22.7 -> 15.7.
+template <int THREADS, int TIN, int TOUT>
+__device__ __forceinline__ void stage_tiles(float* dst, const float* W, int64_t ldw, int win, int wout, int tid) {
+  constexpr int WAVES = THREADS / 64, N = TIN * TOUT, U = N / WAVES >= 4 ? 4 : (N / WAVES >= 2 ? 2 : 1);
+  static_assert(N < WAVES || N % (U * WAVES) == 0, "whole rounds of tiles");
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int f0 = 4 * (lane >> 4), c0 = lane & 15;
+  for (int t0 = wave; t0 < N; t0 += U * WAVES) {
+    v4f v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int tile = t0 + u * WAVES, f = 16 * (tile % TIN) + f0, c = 16 * (tile / TIN) + c0;
+      const float* p = W + f * ldw + c;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = f + e < win && c < wout;
+        const float x = *(in ? p + e * ldw : W);
+        v[u][e] = in ? x : 0.f;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) *reinterpret_cast<v4f*>(dst + (t0 + u * WAVES) * 256 + 4 * lane) = v[u];
+  }
+}
+
 // Stages the model in LDS in operand order (THREADS threads of the workgroup call this; the caller
 // synchronises afterwards).  TALL: 16-unit tiles of the first hidden layer, TH: of the later ones.
-template <int THREADS, int NL>
-__device__ __forceinline__ void stage_model(const PredictArgs& a, const DeepLds& L, float* lds, int tid, int TALL, int TH) {
-  const int l1 = a.wout[0];
-  for (int i = tid; i < TALL * L.kc * 64; i += THREADS) {
-    const int ln = i & 63, tk = i >> 6, t = tk / L.kc, kc = tk - t * L.kc;
-    const int q = 4 * kc + (ln >> 4), c = 16 * t + (ln & 15);
-    lds[L.wf + i] = (q < a.c_f && c < l1) ? static_cast<const float*>(a.W[0])[static_cast<int64_t>(q) * a.ldw[0] + c] : 0.f;
-  }
-  for (int i = tid; i < 16 * TALL; i += THREADS)
-    lds[L.b1 + i] = (i < l1 && a.bias[0]) ? static_cast<const float*>(a.bias[0])[i] : 0.f;
-  const int nl = NL == 4 ? a.n_layers : NL;
-  for (int layer = 1; layer < nl; ++layer) {
-    const int tin = layer == 1 ? TALL : TH;
-    const int tout = (layer == nl - 1 && NL > 2 && a.wout[nl - 1] <= 16) ? 1 : TH;   // a narrow output layer is one tile
-    const int win = a.win[layer], wout = a.wout[layer];
-    const float* W = static_cast<const float*>(a.W[layer]);
-    const int64_t ldw = a.ldw[layer];
-    for (int i = tid; i < tout * tin * 256; i += THREADS) {
-      const int v = i & 3, ln = (i >> 2) & 63, tile = i >> 8, ot = tile / tin, kt = tile - ot * tin;
-      const int f = 16 * kt + 4 * (ln >> 4) + v, c = 16 * ot + (ln & 15);
-      lds[L.w[layer - 1] + i] = (f < win && c < wout) ? W[static_cast<int64_t>(f) * ldw + c] : 0.f;
+template <int THREADS, int NL, int TALL, int TH>
+__device__ __forceinline__ void stage_model(const PredictArgs& a, const DeepLds& L, float* lds, int tid) {
+  static_assert(16 * TALL <= THREADS && 16 * TH <= THREADS, "a bias is one value a thread");
+  constexpr int MOST = NL == 4 ? LQ_MAX_LAYERS : NL;
+  const int l1 = a.wout[0], nl = NL == 4 ? a.n_layers : NL;
+  // biases and the last layer as a vector: requested first, stored last
+  auto entry = [&](const void* v, int64_t stride, int n) {
+    const bool in = v && tid < n;
+    float x = 0.f;
+    if (in) x = static_cast<const float*>(v)[tid * stride];
+    return x;
+  };
+  float bias[MOST];
+#pragma unroll
+  for (int j = 0; j < MOST; ++j) bias[j] = j < nl ? entry(a.bias[j], 1, a.wout[j]) : 0.f;
+  const float last = NL > 2 ? entry(a.W[nl - 1], a.ldw[nl - 1], a.win[nl - 1]) : 0.f;
+
+  if (L.kc > 0) {
+    const float* W = static_cast<const float*>(a.W[0]);
+    const int64_t ldw = a.ldw[0];
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int WAVES = THREADS / 64, PER = (TALL + WAVES - 1) / WAVES;       // tiles of 16 units a wavefront
+    for (int kc = 0; kc < L.kc; ++kc) {
+      const int q = 4 * kc + (lane >> 4);
+      float v[PER];
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const int c = 16 * (wave + u * WAVES) + (lane & 15);
+        const bool in = q < a.c_f && c < l1;
+        const float x = *(in ? W + q * ldw + c : W);
+        v[u] = in ? x : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (wave + u * WAVES < TALL) lds[L.wf + ((wave + u * WAVES) * L.kc + kc) * 64 + lane] = v[u];
     }
-    for (int i = tid; i < 16 * tout; i += THREADS)
-      lds[L.b[layer - 1] + i] = (i < wout && a.bias[layer]) ? static_cast<const float*>(a.bias[layer])[i] : 0.f;
   }
-  if (NL > 2) {
-    const int win = a.win[nl - 1];
-    for (int i = tid; i < 16 * TH; i += THREADS)
-      lds[L.wvec + i] = i < win ? static_cast<const float*>(a.W[nl - 1])[static_cast<int64_t>(i) * a.ldw[nl - 1]] : 0.f;
+  auto W = [&](int layer) { return static_cast<const float*>(a.W[layer]); };
+  auto narrow = [&](int layer) { return NL > 2 && layer == nl - 1 && a.wout[layer] <= 16; };    // a narrow output layer is one tile
+  stage_tiles<THREADS, TALL, TH>(lds + L.w[0], W(1), a.ldw[1], a.win[1], a.wout[1], tid);
+  for (int j = 2; j < nl; ++j) {
+    if (narrow(j)) stage_tiles<THREADS, TH, 1>(lds + L.w[j - 1], W(j), a.ldw[j], a.win[j], a.wout[j], tid);
+    else stage_tiles<THREADS, TH, TH>(lds + L.w[j - 1], W(j), a.ldw[j], a.win[j], a.wout[j], tid);
   }
+  if (tid < 16 * TALL) lds[L.b1 + tid] = bias[0];
+#pragma unroll
+  for (int j = 1; j < MOST; ++j)
+    if (j < nl && tid < (narrow(j) ? 16 : 16 * TH)) lds[L.b[j - 1] + tid] = bias[j];
+  if (NL > 2 && tid < 16 * TH) lds[L.wvec + tid] = last;
 }
 
 // Everything after the second layer for the 16 rows of a step (lane l: row `row`, units 4 (l / 16) .. + 3
@@ -215,13 +263,9 @@ __global__ __launch_bounds__(DEEP_THREADS, (DeepRegs<T1, TH, KMAX>::MIN_WAVES)) 
   const int r16 = lane & 15, q4 = lane >> 4;
   const int l1 = a.wout[0];
 
-  stage_model<DEEP_THREADS, NL>(a, L, lds, tid, TALL, TH);
   const int nl = NL == 4 ? a.n_layers : NL;
-  __syncthreads();
-
   const int64_t n_steps = (a.n + 15) / 16;
   int64_t step = static_cast<int64_t>(blockIdx.x) * DEEP_WAVES + wave;
-  if (step >= n_steps) return;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * DEEP_WAVES;
   const int l_out = a.wout[nl - 1];
   const float* X = static_cast<const float*>(a.X);
@@ -295,6 +339,12 @@ __global__ __launch_bounds__(DEEP_THREADS, (DeepRegs<T1, TH, KMAX>::MIN_WAVES)) 
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) key0[k] = key[k];
   }
+
+  // The model is staged while the first keys and gathers are on their way (wavefronts without a step of their own, whose
+  // row numbers were clamped, take part in it and leave then).
+  stage_model<DEEP_THREADS, NL, TALL, TH>(a, L, lds, tid);
+  __syncthreads();
+  if (step >= n_steps) return;
 
   for (;;) {
     // The staged model is read from LDS where it is used: without this the loads are hoisted out of
