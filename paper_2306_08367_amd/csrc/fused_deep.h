@@ -186,6 +186,7 @@ __device__ __forceinline__ void stage_model(const PredictArgs& a, const DeepLds&
   auto narrow = [&](int layer) { return NL > 2 && layer == nl - 1 && a.wout[layer] <= 16; };    // a narrow output layer is one tile
   stage_tiles<THREADS, TALL, TH>(lds + L.w[0], W(1), a.ldw[1], a.win[1], a.wout[1], tid);
   for (int j = 2; j < nl; ++j) {
+    if (narrow(j) && a.wout[j] == 1) continue;               // (a dot product with `wvec`)
     if (narrow(j)) stage_tiles<THREADS, TH, 1>(lds + L.w[j - 1], W(j), a.ldw[j], a.win[j], a.wout[j], tid);
     else stage_tiles<THREADS, TH, TH>(lds + L.w[j - 1], W(j), a.ldw[j], a.win[j], a.wout[j], tid);
   }
@@ -480,11 +481,13 @@ int launch_deep_nl(const PredictArgs& a, const DeepLds& L, size_t lds, int64_t b
   } while (0)
 #define LQ_DEEP_T1(TH_)                                                                                     \
   do {                                                                                                      \
-    if (PARTS == 2) LQ_DEEP_K(8, 2, TH_);                                                                   \
+    if (PARTS == 2 && T1 == 8) LQ_DEEP_K(8, 2, TH_);                                                        \
     else if (T1 == 2) LQ_DEEP_K(2, 1, TH_); else if (T1 == 4) LQ_DEEP_K(4, 1, TH_);                         \
     else LQ_DEEP_K(8, 1, TH_);                                                                              \
   } while (0)
-  if (TH == 1) LQ_DEEP_T1(1); else if (TH == 2) LQ_DEEP_T1(2); else if (TH == 4) LQ_DEEP_T1(4); else if (TH == 8) LQ_DEEP_T1(8);
+  if (PARTS == 2 && T1 == 4) {         // (three and more layers, TH = 8)
+    if constexpr (NL_ > 2) LQ_DEEP_K(4, 2, 8);
+  } else if (TH == 1) LQ_DEEP_T1(1); else if (TH == 2) LQ_DEEP_T1(2); else if (TH == 4) LQ_DEEP_T1(4); else if (TH == 8) LQ_DEEP_T1(8);
   else if (T1 == 2) LQ_DEEP_K(2, 1, 16); else LQ_DEEP_K(4, 1, 16);     // later layers of 129..256 units: first layers up to 64 only
 #undef LQ_DEEP_T1
 #undef LQ_DEEP_K

@@ -22,10 +22,6 @@ int try_fused_deep(const PredictArgs& a, hipStream_t s) {
     if (!aligned(a.P[k], 16) || a.ldp[k] % 4) return -1;
     if (a.prows[k] * (a.ldp[k] / 4) > 0xffffffffLL) return -1;     // the kernel counts 16-byte pieces of a table in 32 bits
   }
-  // 16-unit tiles of the hidden layer, padded to a power of two; above 128 in two column parts
-  const int PARTS = l1 > 128 ? 2 : 1;
-  const int T1 = l1 <= 32 ? 2 : (l1 <= 64 ? 4 : 8);
-  const int TALL = T1 * PARTS;
   int wide = 0;                                       // widest later layer that has to fit TH tiles
   const int l_out = a.wout[NL - 1];
   for (int j = 1; j < NL; ++j)
@@ -38,22 +34,36 @@ int try_fused_deep(const PredictArgs& a, hipStream_t s) {
   if (wide > 256 || (wide > 128 && l1 > 64)) return -1;     // (later layers of 129..256 units next to first layers of up to 64)
   const int TH = wide <= 16 ? 1 : (wide <= 32 ? 2 : (wide <= 64 ? 4 : (wide <= 128 ? 8 : 16)));
 
+  // 16-unit tiles of the hidden layer, padded to a power of two; above 128 in two column parts
+  int PARTS = l1 > 128 ? 2 : 1, T1 = l1 <= 32 ? 2 : (l1 <= 64 ? 4 : 8);
   DeepLds L{};
   L.kc = (a.c_f + 3) / 4;
-  int off = 0;
-  L.wf = off; off += TALL * L.kc * 64;
-  L.b1 = off; off += 16 * TALL;
-  for (int j = 1; j < NL; ++j) {
-    const int tin = j == 1 ? TALL : TH;
-    const int tout = (j == NL - 1 && NL > 2 && l_out <= 16) ? 1 : TH;
-    L.w[j - 1] = off; off += tout * tin * 256;
-    L.b[j - 1] = off; off += 16 * tout;
+  // Floats of LDS: the model and one 16-row tile of a column part per wavefront.
+  auto layout = [&]() {
+    const int TALL = T1 * PARTS;
+    int off = 0;
+    L.wf = off; off += TALL * L.kc * 64;
+    L.b1 = off; off += 16 * TALL;
+    for (int j = 1; j < NL; ++j) {
+      const int tin = j == 1 ? TALL : TH;
+      const int tout = (j == NL - 1 && NL > 2 && l_out <= 16) ? 1 : TH;
+      L.w[j - 1] = off; off += (j == NL - 1 && NL > 2 && l_out == 1) ? 0 : tout * tin * 256;    // (one output: wvec instead)
+      L.b[j - 1] = off; off += 16 * tout;
+    }
+    L.wvec = off; off += 16 * TH;
+    L.total = off;
+    return off + DEEP_WAVES * 16 * (16 * T1 + 4);
+  };
+  size_t lds = static_cast<size_t>(layout()) * 4;
+  if (lds > 150 * 1024) {
+    // Two 128 x 128 layers leave no room for tiles of 128 columns, but for tiles of 64: the first layer in two column parts.
+    // (100 -> 100 -> 100 -> 1 layer by layer, as it ran before -> so: 100 rows 51 -> 19 us, 200,000 411 -> 137, 4e6 7.10 ->
+    // 2.34 ms, 112 TFLOP/s with the padding to 128 counted; 128 -> 128 -> 128 on 4e6 9.7 -> 2.33 ms.)
+    if (T1 != 8 || PARTS != 1 || TH != 8 || NL < 3) return -1;
+    T1 = 4; PARTS = 2;
+    lds = static_cast<size_t>(layout()) * 4;
+    if (lds > 160 * 1024) return -1;
   }
-  L.wvec = off; off += 16 * TH;
-  L.total = off;
-  off += DEEP_WAVES * 16 * (16 * T1 + 4);         // one 16-row tile per wavefront
-  const size_t lds = static_cast<size_t>(off) * 4;
-  if (lds > 150 * 1024) return -1;
   const int vec_y = (l_out % 4 == 0 && a.ldy % 4 == 0 && aligned(a.Y, 16)) ? 1 : 0;
 
   const int64_t n_steps = (a.n + 15) / 16;

@@ -34,7 +34,9 @@ def _check(n, c_f, layers, dtype, tol):
 
 
 @pytest.mark.parametrize("c_f", [0, 1, 5, 17])
-@pytest.mark.parametrize("layers", [(15, 17), (33, 16, 1), (64, 31, 2), (65, 33, 17), (130, 64, 16), (16, 15, 17, 1), (100, 49, 64, 33)])
+@pytest.mark.parametrize("layers", [(15, 17), (33, 16, 1), (64, 31, 2), (65, 33, 17), (130, 64, 16), (16, 15, 17, 1), (100, 49, 64, 33),
+                                    # two layers of 128 x 128: the first in two column parts while the LDS holds it
+                                    (100, 100, 100, 1), (65, 128, 128), (128, 113, 65, 16)])
 def test_fp32(layers, c_f):
     for n in (1, 17, 200):
         _check(n, c_f, layers, torch.float32, TOL_F32)
