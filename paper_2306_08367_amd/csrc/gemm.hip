@@ -42,15 +42,23 @@ struct GemmArgs {
 
 // Up to LQ_MAX_DIMS independent products of the same type in one launch (the projections of all
 // dimension tables): workgroup b works on problem p where first_tile[p] <= b < first_tile[p + 1].
-struct GemmBatch {
-  GemmArgs g[LQ_MAX_DIMS];
-  int32_t first_tile[LQ_MAX_DIMS + 1];
+// A launch of one problem (MOST = 1) passes and looks up that one only: the arguments of eight and the search among
+// them cost a small launch about half a microsecond (one table of 15,338 x 8 onto 4 outputs with the join of 1.6e6 rows: 18.2 us,
+// 17.6 so).
+template <int MOST>
+struct GemmBatchOf {
+  GemmArgs g[MOST];
+  int32_t first_tile[MOST + 1];
   int32_t count;
 };
+typedef GemmBatchOf<LQ_MAX_DIMS> GemmBatch;
+inline GemmBatchOf<1> only_problem(const GemmBatch& b) { return {{b.g[0]}, {b.first_tile[0], b.first_tile[1]}, 1}; }
 
 // The problem this workgroup works on.
-__device__ __forceinline__ int problem_of(const GemmBatch& b) {
+template <int MOST>
+__device__ __forceinline__ int problem_of(const GemmBatchOf<MOST>& b) {
   int p = 0;
+  if constexpr (MOST == 1) return p;
   while (p + 1 < b.count && static_cast<int>(blockIdx.x) >= b.first_tile[p + 1]) ++p;
   return p;
 }
@@ -358,8 +366,8 @@ constexpr int SKINNY_THREADS = 256;
 // pieces of row i at k = kc + VEC*g and feeds them element by element as the K-slices of 16x16
 // MFMAs whose B operand holds the matching rows of the weight matrix (which rows of k a slot
 // means is irrelevant as long as A and B agree, and they are built from the same index).
-template <typename TA, typename TC>
-__global__ __launch_bounds__(SKINNY_THREADS) void gemm_skinny_kernel(GemmBatch batch) {
+template <typename TA, typename TC, int MOST>
+__global__ __launch_bounds__(SKINNY_THREADS) void gemm_skinny_kernel(GemmBatchOf<MOST> batch) {
   const int p = problem_of(batch);
   const GemmArgs& g = batch.g[p];
   constexpr int VEC = Tile<TA>::VEC;
@@ -557,7 +565,9 @@ int launch_skinny_batch(GemmBatch& b, hipStream_t s) {
   }
   b.first_tile[b.count] = static_cast<int32_t>(blocks);
   if (blocks == 0) return LQ_OK;
-  hipLaunchKernelGGL((gemm_skinny_kernel<TA, TC>), dim3(static_cast<unsigned>(blocks)), dim3(SKINNY_THREADS), 0, s, b);
+  const dim3 grid(static_cast<unsigned>(blocks)), block(SKINNY_THREADS);
+  if (b.count == 1) hipLaunchKernelGGL((gemm_skinny_kernel<TA, TC, 1>), grid, block, 0, s, only_problem(b));
+  else hipLaunchKernelGGL((gemm_skinny_kernel<TA, TC, LQ_MAX_DIMS>), grid, block, 0, s, b);
   LQ_LAUNCH_CHECK("gemm_skinny_kernel");
   return LQ_OK;
 }
@@ -640,8 +650,8 @@ template <int V, int LPR> __device__ __forceinline__ bool rs_stores(int c) {
 // lanes of a row and stored by one instruction; summed into every lane and stored an output at a time by the first lane of each row
 // the same took 210 us instead of 183 with 4 outputs, 307 instead of 200 with 7, and 100,000 x 64 26 instead of 19 (with the
 // join of 100,000 rows in each).
-template <int LPR, int NN>
-__global__ __launch_bounds__(RS_THREADS) void gemm_rowsplit_kernel(GemmBatch batch) {
+template <int LPR, int NN, int MOST>
+__global__ __launch_bounds__(RS_THREADS) void gemm_rowsplit_kernel(GemmBatchOf<MOST> batch) {
   constexpr int RPW = 64 / LPR;             // rows per wavefront and sub-step
   constexpr int U = 4;                      // sub-steps in flight
   constexpr int V = U * NN, LEFT = V > LPR ? V / LPR : 1;
@@ -727,10 +737,13 @@ int launch_rowsplit_batch(GemmBatch& b, hipStream_t s) {
   }
   b.first_tile[b.count] = static_cast<int32_t>(blocks);
   const dim3 grid(static_cast<unsigned>(blocks)), block(RS_THREADS);
-  if (nn == 1) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 1>), grid, block, lds, s, b);
-  else if (nn == 2) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 2>), grid, block, lds, s, b);
-  else if (nn == 4) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 4>), grid, block, lds, s, b);
-  else hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, 8>), grid, block, lds, s, b);
+#define LQ_ROWSPLIT(NN_)                                                                                          \
+  do {                                                                                                           \
+    if (b.count == 1) hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, NN_, 1>), grid, block, lds, s, only_problem(b)); \
+    else hipLaunchKernelGGL((gemm_rowsplit_kernel<LPR, NN_, LQ_MAX_DIMS>), grid, block, lds, s, b);              \
+  } while (0)
+  if (nn == 1) LQ_ROWSPLIT(1); else if (nn == 2) LQ_ROWSPLIT(2); else if (nn == 4) LQ_ROWSPLIT(4); else LQ_ROWSPLIT(8);
+#undef LQ_ROWSPLIT
   LQ_LAUNCH_CHECK("gemm_rowsplit_kernel");
   return LQ_OK;
 }
