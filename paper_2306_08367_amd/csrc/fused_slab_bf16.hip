@@ -151,6 +151,8 @@ __global__ __launch_bounds__(SLAB_THREADS) void fused_slab_bf16_kernel(PredictAr
   // Register v of tile (pair p, half h, outputs ot) is element (2 p + h) TH + ot of acc[v]: output 16 ot + 4 g + v of row j.
   typename SlabSums<CF>::vec acc[4];
   int parity = 0, phase = 0, polls = SLAB_PACE_POLLS;
+  float zero = 0.f;
+  asm volatile("" : "+s"(zero));
   Step st[4];
   if (b < sa.batches)
 #pragma unroll
@@ -254,10 +256,12 @@ __global__ __launch_bounds__(SLAB_THREADS) void fused_slab_bf16_kernel(PredictAr
             const v4u wa = TH == 1 ? w2r[0] : w2[ot * 64], wb = TH == 1 ? w2r[TH == 1 ? 1 : 0] : w2[(TH + ot) * 64];
             y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa), __builtin_bit_cast(bf16x8, h0), y, 0, 0, 0);
             y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wb), __builtin_bit_cast(bf16x8, h1), y, 0, 0, 0);
-            // (the sums are put away from a vector instruction: indexed moves straight behind the matrix instruction
-            // were seen to take the old value of its first result)
+            // The sums are put away from the result of a vector addition, never straight from the matrix instruction: the
+            // compiler counts the s_set_gpr_idx_on ahead of an indexed move as one of the 8 wait states that the move has to
+            // keep, and the first move was then seen to take the register's old value.  The addend is zero, but only the
+            // program knows, so that no optimisation drops the addition.
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v][t0 + ot] = y[v] + 0.f;
+            for (int v = 0; v < 4; ++v) acc[v][t0 + ot] = y[v] + zero;
           }
         }
         if (stage)

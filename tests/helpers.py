@@ -36,3 +36,29 @@ def to_dev(w, device="cuda"):
 
 def cpu_list(ts):
     return [None if t is None else t.cpu() for t in ts]
+
+
+def kernel_names(call):
+    """The (mangled) names of the kernels that `call` launches, from a HIP graph that captures it (nothing is run)."""
+    import ctypes
+
+    class KernelNode(ctypes.Structure):
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                    ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    hip.hipKernelNameRefByPtr.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        call()
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    names = []
+    for node in nodes:
+        kernel = KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(kernel)) == 0
+        names.append(hip.hipKernelNameRefByPtr(kernel.func, None).decode())
+    return names

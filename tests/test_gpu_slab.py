@@ -4,6 +4,8 @@ the bound that the two roundings to bf16 allow."""
 import pytest
 import torch
 
+from tests.helpers import kernel_names
+
 pytestmark = pytest.mark.gpu
 
 CHIP_PAIR = 65_536       # two 16-row tiles on each of 8 wavefronts of 256 compute units: the fewest rows the kernel takes
@@ -106,3 +108,22 @@ def test_replays_of_a_graph():
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
         assert torch.equal(lq.lq_fused_join_predict(X, fks, P, W, b), want)
+
+
+@pytest.mark.parametrize("bias", [False, True], ids=["", "bias"])
+@pytest.mark.parametrize("c_f", [0, 4])
+@pytest.mark.parametrize("outputs", [16, 32, 64])
+@pytest.mark.parametrize("tables", [1, 2, 3, 4])
+def test_every_instance(tables, outputs, c_f, bias):
+    """One kernel for each number of tables, tiles of outputs, and with and without fact columns and a first bias: two slabs, several
+    rounds of rows, a ragged end."""
+    import paper_2306_08367_amd as lq
+    n = 500_003
+    X, fks, P, W, b = _model(n, (900, 5_000, 70, 2_000)[:tables], (128, outputs), c_f, bias, 0, seed=tables)
+    got = lq.lq_fused_join_predict(X, fks, P, W, b, y_dtype=torch.float32)
+    instance = f"fused_slab_bf16_kernelILi{tables}ELi{outputs // 16}ELi{c_f}ELb{int(bias)}E"
+    assert any(instance in name for name in kernel_names(lambda: lq.lq_fused_join_predict(X, fks, P, W, b, Y=got)))
+    for first in range(0, n, 100_000):
+        part = slice(first, min(first + 100_000, n))
+        want, err = _reference(None if X is None else X[part], [f[part] for f in fks], P, W, b)
+        assert bool(((got[part].double() - want).abs() <= err).all())
