@@ -18,8 +18,10 @@
  *     row of each dimension (Section 2.3.3: one 1 per materialised row),
  *     I_k is the int32 column fks[k][i] in [0, r_k), already mapped from key
  *     values to 0-based dimension row numbers.
- *   - The library owns no memory.  Inputs are read-only, outputs and
- *     workspaces are caller-allocated, and nothing is kept between calls.
+ *   - The library allocates no memory (its image holds the array of
+ *     lq_masked_groupby_sum_static and 64 KB of counters that keep workgroups
+ *     of a call in step).  Inputs are read-only, outputs and workspaces are
+ *     caller-allocated, and nothing is kept between calls.
  *   - Calls validate on the host, enqueue kernels on `hip_stream` (a
  *     hipStream_t passed as void*, NULL = the default stream) and return
  *     without waiting; outputs are valid once the stream has been
@@ -187,9 +189,7 @@ int lq_fusion_advice(const lq_star* star, const lq_model* model, double queries_
  *       stores ReLU(z) for a chunk of rows, then the later layers as dense products on the matrix cores, chunk by
  *       chunk (lq_workspace_bytes(LQ_CALL_FUSED, star, model, chunk_rows) sizes it for a chunk; more rows per
  *       chunk, fewer launches).  Without that room the general kernels run: same results, tens of times slower on
- *       such models.  For bf16 models of two or three layers with a first layer of 129 to 256 columns over tables of
- *       more than 10 MB, bytes 256 to 1,279 hold counters that keep the workgroups of a chip die in step (a
- *       workspace of 1,280 bytes or more; without it the same results, up to 1.25 times as long)
+ *       such models
  * star->dims may be NULL here: only n_dims, fks and the row counts in P are used.
  */
 int lq_fused_join_predict(const lq_star* star, const lq_model* model, const lq_mat* P,

@@ -12,12 +12,14 @@
 //     layer's sums of up to 512 rows in registers and goes over the rows once for each slab, so that at any time the
 //     chip reads one slab of every table: four tables of 10,000 x 256 are 20 MB, which every one of the eight 4 MB L2s
 //     would have to fetch over the fabric, but 5 MB a slab.  That only works while the workgroups of an XCD are in the
-//     same slab: `pace` counts the workgroups that are nearly through a slab, and one that is through waits for the
-//     others before it goes on.  The wait is bounded and nothing depends on it but the time.
+//     same slab: a counter for each XCD counts the workgroups that are nearly through a slab, and one that is through
+//     waits for the others before it goes on.  The wait is bounded and nothing depends on it but the time.
 // 50e6 rows, four such tables, 256 -> 16: 11.5 ms row by row in the matrix layout (10.6 for the bare gathers of whole rows,
 // side by side), here 6.2 (4.9 for the bare gathers in paced slabs); 5e6 rows 256 -> 64 -> 16 2.58 -> 1.08; 256 -> 16 with four
 // fact columns and three tables of 2,000 rows 1.87 -> 0.81 ms.  What is left besides the gathers is vector instructions: 145 a
 // tile and slab with three tables, and the issue of instructions 88 % busy where the tables are small.
+#include <atomic>
+
 #include "lq_common.h"
 
 namespace lq {
@@ -35,6 +37,12 @@ constexpr int SLAB_THREADS = 64 * SLAB_WAVES;
 constexpr int SLAB_XCDS = 8;                      // workgroups are dealt to the XCDs in turn
 constexpr int SLAB_PACE_STRIDE = 32;              // counters 128 bytes apart
 constexpr int SLAB_PACE_POLLS = 128;              // about 100 us
+constexpr int SLAB_PACE_SLOTS = 64;
+
+// The counters of the paced calls in flight, 1 KB a call, in the library image (a caller's workspace may hold what another
+// call of it still needs).  Calls take the slots in turn; more than 64 at once share some and wait longer or less, no more.
+__device__ unsigned slab_pace[SLAB_PACE_SLOTS * SLAB_XCDS * SLAB_PACE_STRIDE];
+__device__ __forceinline__ unsigned* pace_counter(int slot, int xcd) { return slab_pace + (slot * SLAB_XCDS + xcd) * SLAB_PACE_STRIDE; }
 
 struct SlabArgs {
   int32_t slabs;        // slabs of 64 hidden units
@@ -42,7 +50,7 @@ struct SlabArgs {
   int32_t keys_cap;     // rows of a wavefront's key buffer, pairs * 32 rounded up to 64
   int32_t vec_y;        // four outputs of a row can be stored at once
   int64_t batches;      // of 8 x 32 x pairs rows
-  unsigned* pace;       // one counter for each XCD, or NULL
+  int32_t pace_slot;    // of the call's counters, or -1
   int32_t xch, keys, w2, b2, w3, b3, b1;   // byte offsets in LDS
 };
 
@@ -97,6 +105,8 @@ __global__ __launch_bounds__(SLAB_THREADS) void fused_slab_bf16_kernel(PredictAr
   }
   __syncthreads();
 
+  const bool paced = sa.pace_slot >= 0;
+  unsigned* const pace = pace_counter(paced ? sa.pace_slot : 0, blockIdx.x % SLAB_XCDS);
   const int pairs = sa.pairs, rows = 32 * pairs;
   unsigned char* const xch = smem + sa.xch + w * 2048;
   uint32_t* const keys0 = reinterpret_cast<uint32_t*>(smem + sa.keys) + w * (2 * KP) * sa.keys_cap;   // two buffers
@@ -166,13 +176,12 @@ __global__ __launch_bounds__(SLAB_THREADS) void fused_slab_bf16_kernel(PredictAr
     parity ^= 1;
     int it = 0;
     for (int sl = 0; sl < sa.slabs; ++sl) {
-      if (sa.pace && phase) {              // wait until the XCD's workgroups are nearly through the slab before
+      if (paced && phase) {                // wait until the XCD's workgroups are nearly through the slab before
         __syncthreads();
         if (threadIdx.x == 0) {
           const unsigned peers = (gridDim.x - blockIdx.x % SLAB_XCDS + SLAB_XCDS - 1) / SLAB_XCDS;
-          const unsigned* ctr = sa.pace + (blockIdx.x % SLAB_XCDS) * SLAB_PACE_STRIDE;
           int i = 0;
-          while (i < polls && __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < peers * phase) {
+          while (i < polls && __hip_atomic_load(pace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < peers * phase) {
             __builtin_amdgcn_s_sleep(2);
             ++i;
           }
@@ -190,8 +199,8 @@ __global__ __launch_bounds__(SLAB_THREADS) void fused_slab_bf16_kernel(PredictAr
 
       for (int p = 0; p < pairs; ++p, ++it) {
         asm volatile("" ::: "memory");       // the staged model is read where it is used: held in registers it would not fit
-        if (sa.pace && p == pairs - 1 - (pairs >> 3) && threadIdx.x == 0)
-          __hip_atomic_fetch_add(sa.pace + (blockIdx.x % SLAB_XCDS) * SLAB_PACE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (paced && p == pairs - 1 - (pairs >> 3) && threadIdx.x == 0)
+          __hip_atomic_fetch_add(pace, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // keys of the next batch, 64 rows at a time (the request for its first pair comes in the batch's last iteration,
         // so there are at least two)
         int fresh[K];
@@ -326,16 +335,16 @@ __global__ __launch_bounds__(SLAB_THREADS) void fused_slab_bf16_kernel(PredictAr
     }
   }
   // a workgroup with fewer batches than others counts as through for the rest
-  if (sa.pace && threadIdx.x == 0) {
+  if (paced && threadIdx.x == 0) {
     const int64_t rounds = (sa.batches + gridDim.x - 1) / gridDim.x;
     const unsigned missing = static_cast<unsigned>(rounds * sa.slabs - phase);
     if (missing)
-      __hip_atomic_fetch_add(sa.pace + (blockIdx.x % SLAB_XCDS) * SLAB_PACE_STRIDE, missing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(pace, missing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-__global__ void slab_pace_clear_kernel(unsigned* pace) {
-  if (threadIdx.x < SLAB_XCDS) pace[threadIdx.x * SLAB_PACE_STRIDE] = 0u;
+__global__ void slab_pace_clear_kernel(int slot) {
+  if (threadIdx.x < SLAB_XCDS) *pace_counter(slot, threadIdx.x) = 0u;
 }
 
 template <int K, int TH, int CF, bool BIAS>
@@ -343,9 +352,8 @@ int launch_inst(const PredictArgs& a, SlabArgs sa, size_t lds, int grid, hipStre
   const void* fn = reinterpret_cast<const void*>(&fused_slab_bf16_kernel<K, TH, CF, BIAS>);
   if (lds > 64 * 1024)
     LQ_HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-  if (sa.pace) {
-    static_assert(SLAB_XCDS * SLAB_PACE_STRIDE * 4 == LQ_PACE_BYTES, "room for the counters");
-    hipLaunchKernelGGL(slab_pace_clear_kernel, dim3(1), dim3(64), 0, s, sa.pace);
+  if (sa.pace_slot >= 0) {
+    hipLaunchKernelGGL(slab_pace_clear_kernel, dim3(1), dim3(64), 0, s, sa.pace_slot);
     LQ_LAUNCH_CHECK("slab_pace_clear_kernel");
   }
   hipLaunchKernelGGL((fused_slab_bf16_kernel<K, TH, CF, BIAS>), dim3(static_cast<unsigned>(grid)), dim3(SLAB_THREADS), lds, s, a, sa);
@@ -414,7 +422,8 @@ int try_fused_slab_bf16(const PredictArgs& a, hipStream_t s) {
   // 394 -> 356; 9,000 rows (4.4 MB) 300 -> 301; rows of 128 265 -> 250 and, in tables of 2 x 20,000, 183 -> 183;
   // 256 -> 64 -> 16 4 x 10,000 649 -> 576, 2 x 20,000 382 -> 404, 4 x 6,000 542 -> 552.
   const bool paced = sa.slabs >= 3 && a.n >= 1000000 && bytes > (TH == 1 ? 10 << 20 : 16 << 20) && (TH == 1 || a.K >= 3);
-  sa.pace = paced ? a.pace : nullptr;
+  static std::atomic<unsigned> next_slot{0};
+  sa.pace_slot = paced ? static_cast<int32_t>(next_slot.fetch_add(1, std::memory_order_relaxed) % SLAB_PACE_SLOTS) : -1;
   switch (a.K) {
     case 1: return pick_th<1>(TH, a, sa, static_cast<size_t>(off), grid, s);
     case 2: return pick_th<2>(TH, a, sa, static_cast<size_t>(off), grid, s);

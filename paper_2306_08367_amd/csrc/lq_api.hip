@@ -393,8 +393,6 @@ int lq_fused_join_predict(const lq_star* star, const lq_model* model, const lq_m
   if (a.n_layers >= 2 && (widest > 128 || a.c_f > 16) && a.n > 0 && ws && aligned(ws, 256) &&
       ws_bytes >= 256 + fused_layered_bytes_per_256(a) && !fused_kernel_covers(a))
     return launch_fused_layered(a, static_cast<uint8_t*>(ws) + 256, ws_bytes - 256, s);
-  if (ws && aligned(ws, 256) && ws_bytes >= 256 + LQ_PACE_BYTES)
-    a.pace = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(ws) + 256);
   return launch_fused(a, s);
 }
 

@@ -48,8 +48,6 @@ int num_cus();
 // one resident set only start when earlier ones end, at whatever occupancy is then left.
 int resident_per_cu(const void* kernel, int threads, size_t lds);
 
-constexpr size_t LQ_PACE_BYTES = 1024;
-
 // Everything a predict kernel needs, passed by value as the kernel argument.
 struct PredictArgs {
   int64_t n;
@@ -76,7 +74,6 @@ struct PredictArgs {
                          // products (honoured by the wide row-batch, column-tiled and shape-agnostic kernels only)
   int32_t accumulate_y;  // a one-layer call adds what Y already holds to z (x W_f + b_1 put there by a dense product when the
                          // fact table has more columns of its own than the kernel takes); same three kernels
-  uint32_t* pace;        // LQ_PACE_BYTES of the caller's workspace for a kernel that paces its workgroups, or NULL
   int32_t probe;         // a specialised kernel that would take the shape returns LQ_OK without launching
 };
 

@@ -21,9 +21,13 @@ SHAPES = [
     (150_001, (800, 60, 10), (104, 20, 3), 4, True, 128),               # three layers, fact columns
     (70_001, (100, 80), (256, 64, 16), 0, False, 0),
     (1_100_003, (10_000, 8_000, 9_000), (256, 16), 0, False, 0),        # paced, second batch shorter than the first
-    (1_000_000, (12_000, 11_000, 20_000, 7), (192, 64, 1), 0, True, 0),  # paced, three slabs, three layers
+    (1_000_000, (14_000, 11_000, 20_000, 7), (192, 64, 1), 0, True, 0),  # paced, three slabs, three layers
+    (1_000_003, (14_000, 16_000, 16_000), (192, 40), 0, False, 0),      # paced, two layers with four tiles of outputs
+    (1_300_001, (14_000, 11_000, 20_000), (256, 32), 4, False, 0),      # paced, two tiles of outputs, fact columns
+    (1_000_000, (14_000, 27_000), (256, 64), 0, True, 0),               # two tables with four tiles of outputs: not paced
     (2_500_000, (9_000, 9_000, 9_000, 500), (256, 16), 4, True, 0),     # paced, several batches, fact columns
 ]
+PACED = [s for s in SHAPES if s[0] >= 1_000_000 and s[2] != (256, 64)]
 
 
 def _model(n, rows, layers, c_f, bias, ld, seed=3):
@@ -70,7 +74,10 @@ def test_against_float64(shape):
     want, err = _reference(X, fks, P, W, b)
     got = lq.lq_fused_join_predict(X, fks, P, W, b, y_dtype=torch.float32)
     assert bool(((got.double() - want).abs() <= err).all())
-    # the plain form of a caller without room for the pace counters, and bf16 outputs in a strided tensor
+    # workgroups kept in step where the shape says so
+    names = kernel_names(lambda: lq.lq_fused_join_predict(X, fks, P, W, b, Y=got))
+    assert any("slab_pace_clear_kernel" in name for name in names) == (shape in PACED), names
+    # a caller with a small workspace, and bf16 outputs in a strided tensor
     plain = lq.lq_fused_join_predict(X, fks, P, W, b, y_dtype=torch.float32, ws=torch.empty(256, dtype=torch.uint8, device="cuda"))
     assert torch.equal(plain, got)
     Y = torch.full((shape[0], shape[2][-1] + 3), 7.0, device="cuda", dtype=torch.bfloat16)
@@ -88,6 +95,25 @@ def test_not_a_number_stays_with_its_fact_rows():
     assert torch.equal(got[~hit], clean[~hit])
     general = lq.lq_fused_join_predict(X, fks, P, W, b, flags=lq.LQ_FORCE_GENERIC)
     assert torch.equal(got[hit].isinf(), general[hit].isinf()) and torch.equal(got[hit].isnan(), general[hit].isnan())
+
+
+def test_workspace_of_a_group_by_is_left_alone():
+    """A paced call with the workspace that holds a group-by's side tables for LQ_REUSE_SIDE_TABLES."""
+    import paper_2306_08367_amd as lq
+    X, fks, P, W, b = _model(1_000_000, (12_000, 9_000, 2_000), (256, 16), 0, False, 0)
+    rows, card = [12_000, 9_000, 2_000], [5, 1, 7]
+    codes = [torch.arange(r, device="cuda", dtype=torch.int32) % c if c > 1 else None for r, c in zip(rows, card)]
+    masks = [None, (torch.arange(9_000, device="cuda") % 3 > 0).to(torch.uint8), None]
+    measure = [torch.arange(1_000_000, device="cuda", dtype=torch.int32)]
+    ws = torch.zeros(max(lq.lq_groupby_workspace_bytes(rows, card, 1), 4_096), dtype=torch.uint8, device="cuda")
+    want = lq.lq_masked_groupby_sum(fks, rows, masks, codes, card, None, measure, ws=ws)
+    kept = ws.clone()
+    call = lambda: lq.lq_fused_join_predict(X, fks, P, W, b, ws=ws)
+    assert any("slab_pace_clear_kernel" in name for name in kernel_names(call))
+    call()
+    assert torch.equal(ws, kept)
+    got = lq.lq_masked_groupby_sum(fks, rows, masks, codes, card, None, measure, ws=ws, flags=lq.LQ_REUSE_SIDE_TABLES)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
 
 
 def test_replays_of_a_graph():
