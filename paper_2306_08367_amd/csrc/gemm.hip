@@ -462,10 +462,11 @@ __global__ __launch_bounds__(SHORT_THREADS) void gemm_short_kernel(GemmArgs g, i
 #pragma unroll
     for (int j = 0; j < 2; ++j) b[s][j] = 2 * s + h < g.Kd ? b[s][j] : 0.f;
   v4u a[SHORT_K / 4], next[SHORT_K / 4];
+  // (16 bytes at a time whatever the alignment: 600,000 x 16 -> 128 79.8 to 80.4 us so, 80.2 to 80.9 with aligned loads)
   auto fetch = [&](int64_t block) {
     const float* row = A + min(block * SHORT_ROWS + r, g.M - 1) * g.lda;      // rows past the end repeat the last row
 #pragma unroll
-    for (int q = 0; q < SHORT_K / 4; ++q) next[q] = load_chunk<float>(row + 4 * q, g.Kd - 4 * q, g.a_vec_ok);
+    for (int q = 0; q < SHORT_K / 4; ++q) next[q] = load_chunk<float>(row + 4 * q, g.Kd - 4 * q, false);
   };
   fetch(first);
   for (int64_t block = first; block < last; ++block) {
