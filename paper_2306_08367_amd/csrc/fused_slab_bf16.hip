@@ -372,6 +372,36 @@ int pick_th(int TH, const PredictArgs& a, const SlabArgs& sa, size_t lds, int gr
 
 }  // namespace
 
+// Microseconds of a call in this kernel and in the ones it would take otherwise, from about 2,400 shapes of 65,536 to 6e6 rows over
+// tables of 100 to 1e6 rows, each timed in both (half of the estimates are within 5 % here and 9 % there).  A unit is the
+// 65,536 rows that fill the chip with a pair of tiles a wavefront; this kernel works in whole units (131,149 rows take it as
+// long as 196,608) and whole slabs, which is what it loses on some calls:
+//   131,149 rows 128 -> 40 -> 8, one table of 40,000 rows and four fact columns 29 us here, 17 there; 65,536 rows 96 -> 64 -> 16, four
+//   tables of 10,000 rows 23 and 15; 2.5e6 rows 104 -> 64 -> 1, one table of 700 rows 179 and 124; against
+//   500,003 rows 256 -> 16 -> 1 with a bias, two tables of 20,000 rows, 53 and 161; 1e6 rows 128 -> 16, one table of 700 rows, 40 and 60.
+// Taken on all of these shapes this kernel is 1.42 times as fast as the others in the geometric mean and 3 % or more behind on
+// 331 of them; taken where its estimate is the smaller one, 1.45 times and on 73 (the best choice for each: 1.46).
+struct SlabCost { double here, there; };
+SlabCost slab_cost(const PredictArgs& a, int TH, int slabs, int64_t whole_units, double units) {
+  const int l1 = a.wout[0], l_out = a.wout[a.n_layers - 1];
+  const bool fact = a.c_f > 0, bias = a.bias[0] != nullptr;
+  const double stored = l_out * static_cast<double>(dtype_size(a.y_dtype)) / 64;
+  int64_t rows = 0;
+  for (int k = 0; k < a.K; ++k) rows += a.prows[k];
+  const double beyond_l2 = std::min(10.0, std::max(0.0, rows * 128.0 / (1 << 20) - 3));      // MB of a slab
+  double slab = 0.3 * a.K + 0.012 * a.K * a.K * beyond_l2 + (fact ? 1.0 : 0) + 0.35 * TH;
+  double rest = 0.9 + 0.2 * stored + (a.n_layers == 2 && l_out % 4 ? 0.2 * TH : 0);
+  SlabCost c;
+  c.here = 4.5 + 0.3 * slabs + whole_units * (rest + slabs * slab);
+  if (a.K == 4 && TH == 4 && !fact) c.here += 4.5;           // (these instances keep registers in scratch memory)
+  // there: the one-tile kernel, or the one for deeper models, whose first layer is padded to a power of two
+  const bool one_tile = a.n_layers == 2 && l_out <= 16 && !fact && (l1 == 64 || l1 == 128 || l1 == 256);
+  const int padded = l1 <= 64 ? 1 : (l1 <= 128 ? 2 : 4);
+  c.there = 2.5 + 1.25 * padded + units * (l1 / 64.0 * (0.86 * a.K + (fact ? 1.0 : 0)) + (one_tile ? 2.5 : 1.55) * stored +
+                                           padded * (0.25 + 0.17 * TH + (bias && !one_tile ? 1.7 : 0)));
+  return c;
+}
+
 // Returns -1 when the shape is not one this kernel covers.
 int try_fused_slab_bf16(const PredictArgs& a, hipStream_t s) {
   if (a.x_dtype != LQ_BF16 || a.p_dtype != LQ_BF16) return -1;
@@ -392,7 +422,6 @@ int try_fused_slab_bf16(const PredictArgs& a, hipStream_t s) {
   // A pair of tiles for every wavefront of the chip, two where there is one slab; below that the kernels below, which spread
   // 16 rows at a time: 32,000 rows 128 -> 16 8.4 us, here 8.8, 50,000 11.3 and 9.4; 64 -> 16 8.0 and 10.4, 100,000 11.3 and 10.6.
   if (a.n < cus * SLAB_WAVES * 32 * (l1 <= 64 ? 2 : 1)) return -1;
-  if (a.probe) return LQ_OK;
 
   const int TH = l2 <= 16 ? 1 : (l2 <= 32 ? 2 : 4);
   const int l_out = a.n_layers == 3 ? a.wout[2] : l2;
@@ -405,6 +434,9 @@ int try_fused_slab_bf16(const PredictArgs& a, hipStream_t s) {
   const int64_t rounds = (a.n + per_pair * max_pairs - 1) / (per_pair * max_pairs);
   sa.pairs = static_cast<int32_t>((a.n + per_pair * rounds - 1) / (per_pair * rounds));
   if (sa.slabs == 1) sa.pairs = (sa.pairs + 1) / 2 * 2;     // two iterations a batch at the least
+  const SlabCost cost = slab_cost(a, TH, sa.slabs, rounds * sa.pairs, static_cast<double>(a.n) / per_pair);
+  if (cost.here >= cost.there) return -1;
+  if (a.probe) return LQ_OK;
   sa.keys_cap = (sa.pairs * 32 + 63) / 64 * 64;
   sa.batches = (a.n + SLAB_WAVES * 32 * sa.pairs - 1) / (SLAB_WAVES * 32 * sa.pairs);
   int off = 0;

@@ -26,8 +26,15 @@ SHAPES = [
     (1_300_001, (14_000, 11_000, 20_000), (256, 32), 4, False, 0),      # paced, two tiles of outputs, fact columns
     (1_000_000, (14_000, 27_000), (256, 64), 0, True, 0),               # two tables with four tiles of outputs: not paced
     (2_500_000, (9_000, 9_000, 9_000, 500), (256, 16), 4, True, 0),     # paced, several batches, fact columns
+    (524_288 + 31, (900, 50, 70, 1), (64, 17), 4, True, 0),             # two tiles of outputs, fact columns, one slab
+    (262_145, (100, 80), (256, 64, 16), 0, True, 0),                    # three layers with four tiles of outputs
 ]
 PACED = [s for s in SHAPES if s[0] >= 1_000_000 and s[2] != (256, 64)]
+# faster in the kernels that take 16 rows at a time (by the rule's estimates): the shapes around them
+ELSEWHERE = [s for s in SHAPES if s[0] in (131_073 + 31, 70_001)] + [
+    (131_149, (40_000,), (128, 40, 8), 4, False, 0), (65_536, (10_000,) * 4, (96, 64, 16), 0, False, 128),
+    (161_073, (10_000,) * 4, (64, 64, 1), 0, False, 64), (262_221, (10_000,) * 4, (56, 16, 1), 4, False, 64),
+]
 
 
 def _model(n, rows, layers, c_f, bias, ld, seed=3):
@@ -67,7 +74,7 @@ def _reference(X, fks, P, W, b):
     return y, err
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=["-".join(map(str, (s[0],) + s[2] + (len(s[1]), s[3]))) for s in SHAPES])
+@pytest.mark.parametrize("shape", SHAPES + ELSEWHERE[2:], ids=lambda s: "-".join(map(str, (s[0],) + s[2] + (len(s[1]), s[3]))))
 def test_against_float64(shape):
     import paper_2306_08367_amd as lq
     X, fks, P, W, b = _model(*shape)
@@ -76,6 +83,7 @@ def test_against_float64(shape):
     assert bool(((got.double() - want).abs() <= err).all())
     # workgroups kept in step where the shape says so
     names = kernel_names(lambda: lq.lq_fused_join_predict(X, fks, P, W, b, Y=got))
+    assert any("fused_slab_bf16_kernel" in name for name in names) == (shape not in ELSEWHERE), names
     assert any("slab_pace_clear_kernel" in name for name in names) == (shape in PACED), names
     # a caller with a small workspace, and bf16 outputs in a strided tensor
     plain = lq.lq_fused_join_predict(X, fks, P, W, b, y_dtype=torch.float32, ws=torch.empty(256, dtype=torch.uint8, device="cuda"))
