@@ -260,7 +260,11 @@ template <int T1, int PARTS, int TH, int NL, int KMAX, bool EXTRA>
 __global__ __launch_bounds__(DEEP_THREADS, (DeepRegs<T1, TH, KMAX>::MIN_WAVES)) void fused_deep_kernel(PredictArgs a, DeepLds L, int vec_y) {
   constexpr int TALL = T1 * PARTS;                // 16-unit tiles of the whole hidden layer
   extern __shared__ __align__(16) float lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // The wavefront's number in a scalar register where the vector registers it saves make room for a third wavefront a SIMD
+  // and that pays: 64 -> 64, five tables, 1e6 rows 149.8 us without, 134 with; 256 -> 8, two tables 151.6 and 141.  (256 -> 16 -> 4, two
+  // tables 148.9 and 160.8; 64 -> 64, four tables 113.4 and 116.4.)
+  constexpr bool SCALAR = EXTRA || (PARTS == 2 && NL == 2);
+  const int tid = threadIdx.x, lane = tid & 63, wave = SCALAR ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int r16 = lane & 15, q4 = lane >> 4;
   const int l1 = a.wout[0];
 
