@@ -9,11 +9,11 @@ from tests.helpers import TOL_BF16, TOL_F32, assert_close
 pytestmark = pytest.mark.gpu
 
 
-def _check(n, c_f, layers, dtype, tol):
+def _check(n, c_f, layers, dtype, tol, rows=(7, 300, 41)):
     import paper_2306_08367_amd as lq
     gen = torch.Generator(device="cuda")
     gen.manual_seed(sum(layers) + n)
-    rows, cols = (7, 300, 41), (8, 16, 24)
+    cols = [8 * (k % 3 + 1) for k in range(len(rows))]
     normal = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
     dims = [normal(r, c).to(dtype) for r, c in zip(rows, cols)]
     fks = [torch.randint(0, r, (n,), generator=gen, device="cuda", dtype=torch.int32) for r in rows]
@@ -47,3 +47,18 @@ def test_fp32(layers, c_f):
 def test_bf16(layers, c_f):
     for n in (1, 17, 200):
         _check(n, c_f, layers, torch.bfloat16, TOL_BF16)
+
+
+@pytest.mark.parametrize("c_f", [0, 5])
+@pytest.mark.parametrize("tables", [1, 3, 4, 6])
+@pytest.mark.parametrize("layers", [(100, 100, 100, 1), (128, 128, 128),       # two layers of 128 x 128: one workgroup a compute unit
+                                    (64, 64), (200, 16)], ids=lambda l: "-".join(map(str, l)))
+def test_fp32_several_steps(layers, tables, c_f):
+    """More rows than one step of every wavefront of the chip takes (16,384 with one workgroup a compute unit): the keys and gathers that
+    one step hands to the next, and one column part to the other; a ragged end."""
+    _check(50_003 if 128 in layers or 100 in layers else 250_003, c_f, layers, torch.float32, TOL_F32, (7, 300, 41, 1_000, 5, 64)[:tables])
+
+
+@pytest.mark.parametrize("layers", [(96, 96, 4), (72, 128, 16)], ids=lambda l: "-".join(map(str, l)))
+def test_bf16_several_steps(layers):
+    _check(150_003, 3, layers, torch.bfloat16, TOL_BF16)
