@@ -199,6 +199,8 @@ def main():
                                              ("gather_256B_rows_of_2.56MB", 2_560_000, 256),      # C2's middle table: fits L2
                                              ("gather_256B_rows_of_0.256MB", 256_000, 256),       # C2's smallest table
                                              ("gather_512B_rows_of_20.5MB", 20_480_000, 512),     # C5's four tables together
+                                             ("gather_128B_rows_of_5.12MB", 5_120_000, 128),      # the same, 64 of their 256 columns
+                                             ("gather_128B_rows_of_2MB", 2_000_000, 128),         # such rows out of one L2
                                              ("gather_16B_rows_of_32MB", 32_000_000, 16),         # C4's two tables together
                                              ("gather_16B_rows_of_2MB", 2_000_000, 16)):
             tab = src[:table_bytes]
@@ -522,10 +524,11 @@ def main():
         Ym5 = torch.empty((m5, 16), dtype=torch.bfloat16, device=dev)
         mt = time_call(lambda: lq.lq_materialized_join_predict(None, w5.dims, fk5, w5.weights, None, Y=Ym5, ws=ws5), 5, 1)
         ggbps = 2048.0 * n5 / (t[2] * 1e-3) / 1e9
-        yg = yard.get("gather_512B_rows_of_20.5MB_GBps")
+        yg = yard.get("gather_128B_rows_of_5.12MB_GBps")      # (the kernel takes 64 hidden units at a time, 128 bytes of a row)
         out["fused_c5"] = {"rows_per_s": n5 / (t[2] * 1e-3), **tstats(t), "project_dims_ms": pt[2], "fact_rows": n5,
                            "dtype": "bf16", "gather_GBps": ggbps, "gather_yardstick_GBps": yg,
                            "gather_frac_of_yardstick": (ggbps / yg) if yg else None,
+                           "gather_yardstick_GBps_whole_rows": yard.get("gather_512B_rows_of_20.5MB_GBps"),
                            "hbm_GBps_algorithmic": 48.0 * n5 / (t[2] * 1e-3) / 1e9,
                            "materialized_rows_per_s": m5 / (mt[2] * 1e-3), "materialized_slice_rows": m5,
                            "fused_speedup": (mt[2] / m5) / ((t[2] + pt[2]) / n5)}

@@ -6,7 +6,7 @@
 //   * A load instruction is taken apart into pieces that lie side by side in one cache line.  The layout the matrix
 //     instruction asks for (lane (g, j): row j, 16-byte piece g) has no two such pieces in neighbouring lanes, and the
 //     gathers then run at one 16-byte piece a cycle and compute unit, 9.3 TB/s, wherever the tables are.  Here eight
-//     neighbouring lanes fetch 128 bytes of one row (24 TB/s out of L2), the sum over the tables is made where it
+//     neighbouring lanes fetch 128 bytes of one row (28 TB/s out of L2), the sum over the tables is made where it
 //     arrives, and the rectified bf16 values cross over to the matrix layout through 2 KB of LDS a wavefront.
 //   * The hidden units are taken in slabs of 64 (128 bytes of a row, a cache line).  A wavefront keeps the second
 //     layer's sums of up to 512 rows in registers and goes over the rows once for each slab, so that at any time the
@@ -14,10 +14,10 @@
 //     would have to fetch over the fabric, but 5 MB a slab.  That only works while the workgroups of an XCD are in the
 //     same slab: a counter for each XCD counts the workgroups that are nearly through a slab, and one that is through
 //     waits for the others before it goes on.  The wait is bounded and nothing depends on it but the time.
-// 50e6 rows, four such tables, 256 -> 16: 11.5 ms row by row in the matrix layout (10.6 for the bare gathers of whole rows,
-// side by side), here 6.2 (4.9 for the bare gathers in paced slabs); 5e6 rows 256 -> 64 -> 16 2.58 -> 1.08; 256 -> 16 with four
-// fact columns and three tables of 2,000 rows 1.87 -> 0.81 ms.  What is left besides the gathers is vector instructions: 145 a
-// tile and slab with three tables, and the issue of instructions 88 % busy where the tables are small.
+// 50e6 rows, four such tables, 256 -> 16: 11.5 ms row by row in the matrix layout, here 5.56, 18.4 TB/s gathered (bare gathers:
+// whole rows of 512 bytes 9.6 TB/s, 128-byte rows of one slab 22); 5e6 rows 256 -> 64 -> 16 2.58 -> 1.08; 256 -> 16 with four
+// fact columns and three tables of 2,000 rows 1.87 -> 0.81 ms.  What is left besides the gathers is vector instructions, the sums
+// over the tables above all.
 #include <atomic>
 
 #include "lq_common.h"
