@@ -2,12 +2,14 @@
 //
 // Used for the pre-fusion products P_k = D_k * (rows of L owned by dimension k) (underlined terms
 // of Eq. 1) and for the layer-by-layer model evaluation of the non-fused pipeline (T * L, second
-// line of Eq. 1).  Four kernels:
+// line of Eq. 1).  Five kernels:
 //   gemm_tiled_kernel  - 128 x BN tiles (BN = 64 or 128) staged through LDS, 4 wavefronts in a
 //                        2 x 2 arrangement, each owning 64 x BN/2 as 32x32 MFMA accumulators.
-//                        fp32 inputs use the 32x32x2 f32 MFMA; bf16 inputs stay bf16 in LDS and
-//                        use the 32x32x16 bf16 MFMA.  The next k-tile is fetched into registers
-//                        while the current one is multiplied.
+//                        bf16 inputs stay bf16 in LDS and use the 32x32x16 bf16 MFMA, the next
+//                        k-tile fetched into registers while the current one is multiplied; fp32
+//                        inputs of up to 16 k, which are one k-tile, use the 32x32x2 f32 MFMA.
+//   gemm_split_kernel  - fp32, more than 16 k: every operand as the sum of three bf16 numbers, six of
+//                        their nine products on the 32x32x16 bf16 MFMA.
 //   gemm_rowsplit_kernel - fp32, N <= 8, 32 <= K: the shape of projecting a wide dimension table
 //                        onto a handful of outputs, bound by reading A once.  The lanes of a
 //                        wavefront read A as contiguous 16-byte pieces (a row is split over 8..64
@@ -70,7 +72,7 @@ constexpr int TILED_THREADS = 256;
 
 template <typename T> struct Tile;
 template <> struct Tile<float> {
-  static constexpr int BK = 32;        // k per LDS tile
+  static constexpr int BK = 16;        // k per LDS tile
   static constexpr int VEC = 4;        // elements per 16-byte chunk
 };
 template <> struct Tile<bf16_t> {
@@ -107,9 +109,7 @@ __device__ __forceinline__ v4u load_chunk(const T* p, int valid, bool vec_ok) {
   return r;
 }
 
-// Workgroups per compute unit that the accumulators leave room for: three (128 columns) and four (64).  Without the bound
-// the compiler takes more registers for the fp32 forms and one workgroup less fits (64 columns: 600,000 x 85 87 us with
-// three workgroups, 81 with four); the bf16 forms keep the three and four that they have anyway.
+// Three (128 columns) and four (64) workgroups a compute unit, as many as the accumulators leave room for.
 template <typename TA, typename TC, int BN>
 __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_kernel(GemmBatch batch) {
   int problem = 0;
@@ -194,41 +194,6 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
     }
   };
 
-  // fp32: vector instructions delay the matrix instructions of the SIMD, so those of the fetch cost more than its
-  // loads do.  A whole k-tile needs no test per element: the tile's corner stays in scalar registers and each
-  // thread keeps one 32-bit byte offset per 16-byte piece.  Columns past N are never stored, so a piece that lies
-  // past N repeats the tile's first one.  The last part of k, column counts that end inside a piece of a tile and
-  // row strides whose offsets would pass 32 bits go through fetch().  16,555 x 683 -> 2,048 columns in three
-  // problems: 457 us with fetch() and multiply() for every tile, 414 so (112 TFLOP/s; 153 is what these instructions
-  // reach alone).
-  const bool whole = F32 && (n0 + BN <= g.N || g.N % VEC == 0) && max(g.lda, g.ldb) < (int64_t{1} << 31) / (BM * 4);
-  uint32_t off_a[A_CHUNKS], off_b[B_CHUNKS];
-  if constexpr (F32) {
-#pragma unroll
-    for (int c = 0; c < A_CHUNKS; ++c) {
-      const int id = tid + c * TILED_THREADS;
-      const int64_t r = min(static_cast<int64_t>(id / A_CPR), g.M - 1 - m0);      // rows past the end repeat the last row
-      off_a[c] = static_cast<uint32_t>((r * g.lda + id % A_CPR * VEC) * 4);
-    }
-#pragma unroll
-    for (int c = 0; c < B_CHUNKS; ++c) {
-      const int id = tid + c * TILED_THREADS;
-      const int nc = id % B_CPR * VEC;
-      off_b[c] = static_cast<uint32_t>((id / B_CPR * g.ldb + (n0 + nc < g.N ? nc : 0)) * 4);
-    }
-  }
-  auto load_whole = [](const char* p) {
-    const Words4 t = *reinterpret_cast<const Words4*>(p);
-    return v4u{t.x, t.y, t.z, t.w};
-  };
-  auto fetch_whole = [&](int k0) {
-    const char* pa = reinterpret_cast<const char*>(A + m0 * g.lda + k0);
-    const char* pb = reinterpret_cast<const char*>(B + static_cast<int64_t>(k0) * g.ldb + n0);
-#pragma unroll
-    for (int c = 0; c < A_CHUNKS; ++c) ra[c] = load_whole(pa + off_a[c]);
-#pragma unroll
-    for (int c = 0; c < B_CHUNKS; ++c) rb[c] = load_whole(pb + off_b[c]);
-  };
   auto multiply = [&](int k0) {
     if constexpr (F32) {
       const float* As = reinterpret_cast<const float*>(smemA);
@@ -272,49 +237,8 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
     }
   };
 
-  // A whole fp32 k-tile that another whole one follows: operands are read one step ahead of their products.
-  auto multiply_whole = [&]() {
-    const float* As = reinterpret_cast<const float*>(smemA);
-    const float* Bs = reinterpret_cast<const float*>(smemB);
-    float a[2][2], b[2][TN];
-    auto read = [&](int kk, int at) {
-      const int k = kk + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[at][i] = As[k * (BM + PADF) + wm * 64 + i * 32 + (lane & 31)];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) b[at][j] = Bs[k * (BN + PADF) + wn * WN + j * 32 + (lane & 31)];
-    };
-    read(0, 0);
-#pragma unroll
-    for (int st = 0; st < BK / 2; ++st) {
-      const int at = st & 1;
-      if (st + 1 < BK / 2) read(2 * st + 2, at ^ 1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[at][i], b[at][j], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  int k0 = 0;
-  if (whole && g.Kd >= 2 * BK) {
-    // A loop of its own: next to fetch()'s branches the loads would be waited for before the products.  Every tile's
-    // successor is fetched during its products; the loop ends before the last whole tile, whose successor is the rest.
-    fetch_whole(0);
-    for (; k0 + 2 * BK <= g.Kd; k0 += BK) {
-      __syncthreads();          // previous tile fully consumed
-      stage();
-      __syncthreads();
-      fetch_whole(k0 + BK);
-      multiply_whole();
-    }
-  } else {
-    fetch(0);
-  }
-  for (; k0 < g.Kd; k0 += BK) {
+  fetch(0);
+  for (int k0 = 0; k0 < g.Kd; k0 += BK) {
     __syncthreads();            // previous tile fully consumed
     stage();
     __syncthreads();
@@ -355,6 +279,290 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
           if (row0 + at < g.M) Elem<TC>::store(p + at * g.ldc, acc[i][j][v]);
         }
     }
+  }
+}
+
+// ------------------------------------------------------------------ split --------------
+
+// fp32, more than 16 k and 16 columns.  An fp32 number is exactly the sum of three bf16 numbers (24 bits in three pieces of 8, each
+// rounded to nearest, so a piece is at most 2^-9 of the one before it).  Of the nine products of two such sums the six largest go
+// through the bf16 matrix instruction, whose products are exact and whose sums are fp32; the other three are below 2^-25 of the
+// product.  Six bf16 instructions take 3/8 of the time of the fp32 instructions for the same tile.  The accumulator is rounded six times
+// per 16 k instead of eight times, so the result is a little closer to the exact one than with fp32 instructions: normal values, relative
+// error in the 2-norm for k = 32, 64, 128, 320, 683, 1,024: 1.0e-7, 1.4e-7, 2.0e-7, 3.2e-7, 4.7e-7, 5.7e-7 with those, 6.9e-8, 1.1e-7,
+// 1.6e-7, 2.7e-7, 4.0e-7, 4.9e-7 so (the small products first: they then meet an accumulator of zero in the first step).
+// What the pieces cannot hold is computed again with fp32 instructions, element by element of the result and wavefront by
+// wavefront, before it is stored:
+//  * an infinity, a NaN or a value that rounds to a bf16 infinity leaves a NaN or an infinity in its row or column, since
+//    the second piece is then inf - inf or an infinity of the other sign;
+//  * an operand below 2^-100 other than zero loses bits below 2^-134 of it.  The kernel looks for such operands; if there is one,
+//    results below 2^-30 are computed again.
+// Apart from that, the order of the sums depends on k only: a row computed alone equals the same row computed as part of a table,
+// whichever of the instances below computes it.
+//
+// A wavefront owns 32 TM rows and all 32 TN columns of the tile.  Its rows of A go from memory straight into operand layout
+// (lane: row l % 32, eight consecutive k) and are split once, in registers; only B passes through LDS, split by the workgroup,
+// in two buffers with one barrier per 16 k.  (Both operands through LDS, 64 x 64 a wavefront: 278 instead of 271 us
+// at 16,555 x 683 -> 2,048 in three problems, 2,200 instead of 2,000 at 200,000 x 1,024 -> 1,024; with fp32 instructions, one word of
+// either operand a lane from LDS, 412 and 3,250.)  The latter is 1.26 PFLOP/s in bf16 operations, the rate that a bf16 product of
+// 8,192^3 from the vendor's library reaches on this card; short tables are bound by the chain of a step: load, split, LDS, products.
+
+// Floats as sums of three bf16 numbers each, packed in pairs.
+template <int N>
+__device__ __forceinline__ void split_pairs(const float (&x)[N], unsigned int (&p)[3][N / 2]) {
+#pragma unroll
+  for (int q = 0; q < N / 2; ++q) {
+    const unsigned int h = f32x2_to_bf16x2(x[2 * q], x[2 * q + 1]);
+    const float r0 = x[2 * q] - __uint_as_float(h << 16), r1 = x[2 * q + 1] - __uint_as_float(h & 0xffff0000u);
+    const unsigned int m = f32x2_to_bf16x2(r0, r1);
+    p[0][q] = h;
+    p[1][q] = m;
+    p[2][q] = f32x2_to_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+  }
+}
+
+// The smaller of `least` and |x| as a number without its sign bit, shifted left; zero counts as the largest.
+template <int N>
+__device__ __forceinline__ uint32_t least_of(const float (&x)[N], uint32_t least) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) least = min(least, (__float_as_uint(x[q]) << 1) - 1u);
+  return least;
+}
+
+template <int TM, int TN>
+__global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split_kernel(GemmBatch batch) {
+  int problem = 0;
+  while (problem + 1 < batch.count && static_cast<int32_t>(blockIdx.x) >= batch.first_tile[problem + 1]) ++problem;
+  const GemmArgs g = batch.g[problem];
+  // Tiles are dealt to the eight XCDs in runs, columns first, so that an XCD's L2 sees an eighth of A's rows only (200,000 x 1,024 ->
+  // 1,024 1,973 us so, 2,026 dealt in turn).
+  const int32_t at = static_cast<int32_t>(blockIdx.x) - batch.first_tile[problem];
+  const int32_t tiles = batch.first_tile[problem + 1] - batch.first_tile[problem];
+  const int32_t tile = at % 8 * (tiles / 8) + min(at % 8, tiles % 8) + at / 8;
+  constexpr int BK = 16, BN = 32 * TN;
+  constexpr int BP = BN * BK / TILED_THREADS;                  // consecutive k of B in a thread
+  static_assert(TILED_THREADS % BN == 0 && BP * (TILED_THREADS / BN) == BK, "B's tile must be dealt out evenly");
+  constexpr int PLANE = BN * 2;                                // 16-byte pieces of a part: [column / 32][half of k][column % 32]
+  __shared__ __align__(16) v4u smem[2][3 * PLANE];
+  __shared__ int tiny_b[4];
+  const float* __restrict__ A = static_cast<const float*>(g.A);
+  const float* __restrict__ B = static_cast<const float*>(g.B);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+  const int64_t m0 = (static_cast<int64_t>(tile / g.tiles_n) * 4 + wave) * 32 * TM;
+  const int n0 = tile % g.tiles_n * BN;
+
+  v16f acc[TM][TN];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  };
+  clear();
+
+  // Rows past the end repeat the last row and columns past the end the last column; both are never stored.
+  float ra[TM][8], rb[BP];
+  const float* row_a[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) row_a[i] = A + min(m0 + 32 * i + (lane & 31), g.M - 1) * g.lda;
+  const int bk = tid / BN * BP, bc = tid % BN;
+  const uint32_t col_b = min(n0 + bc, g.N - 1);
+  uint32_t least_a = 0xffffffffu, least_b = 0xffffffffu;
+
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int h = 0; h < 8; h += 4) {
+        const Words4 t = *reinterpret_cast<const Words4*>(row_a[i] + k0 + 8 * half + h);
+        ra[i][h] = __uint_as_float(t.x); ra[i][h + 1] = __uint_as_float(t.y);
+        ra[i][h + 2] = __uint_as_float(t.z); ra[i][h + 3] = __uint_as_float(t.w);
+      }
+    const float* base = B + static_cast<int64_t>(k0 + (BN >= 64 ? __builtin_amdgcn_readfirstlane(bk) : bk)) * g.ldb;
+#pragma unroll
+    for (int q = 0; q < BP; ++q) rb[q] = (base + q * g.ldb)[col_b];
+  };
+  // The last step takes the last 16 k there are; those of them that the step before has had are cleared.
+  const int steps = (g.Kd + BK - 1) / BK, last_k = g.Kd - BK, had = steps * BK - g.Kd;
+  auto clear_a = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) ra[i][q] = 8 * half + q >= had ? ra[i][q] : 0.f;
+  };
+  auto clear_b = [&]() {
+#pragma unroll
+    for (int q = 0; q < BP; ++q) rb[q] = bk + q >= had ? rb[q] : 0.f;
+  };
+  auto stage_b = [&](int buf) {
+    unsigned int pb[3][BP / 2];
+    split_pairs<BP>(rb, pb);
+    least_b = least_of<BP>(rb, least_b);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      v4u* to = &smem[buf][p * PLANE + (bc / 32 * 2 + bk / 8) * 32 + bc % 32];
+      if constexpr (BP == 8) *to = v4u{pb[p][0], pb[p][1], pb[p][2], pb[p][3]};
+      else if constexpr (BP == 4) reinterpret_cast<uint2*>(to)[bk / 4 % 2] = make_uint2(pb[p][0], pb[p][1]);
+      else reinterpret_cast<unsigned int*>(to)[bk / 2 % 4] = pb[p][0];
+    }
+  };
+  auto is_tiny = [](uint32_t least) { return __any(least < (27u << 24) - 1u) != 0; };      // (27 << 24: 2^-100 shifted left)
+  v4u a[TM][3];
+  auto split_a = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      unsigned int pa[3][4];
+      split_pairs<8>(ra[i], pa);
+      least_a = least_of<8>(ra[i], least_a);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) a[i][p] = v4u{pa[p][0], pa[p][1], pa[p][2], pa[p][3]};
+    }
+  };
+  auto multiply = [&](int buf) {
+    const v4u* from = &smem[buf][half * 32 + lane % 32];
+    // All reads of B's operands ahead of the products as far as registers go, in the order in which they are needed.
+    constexpr int JB = TM == 1 ? TN : 1;
+#pragma unroll
+    for (int j0 = 0; j0 < TN; j0 += JB) {
+      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+      v4u b[JB][3];
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) b[j][PB[t]] = from[PB[t] * PLANE + (j0 + j) * 64];
+      if constexpr (TN == 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            acc[i][j0 + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][PA[t]]),
+                                                                     __builtin_bit_cast(bf16x8, b[j][PB[t]]), acc[i][j0 + j], 0, 0, 0);
+    }
+  };
+
+  // Step st: A's operands are in ra, B's in LDS since the step before; both of the next step are fetched ahead of the products.
+  // The buffer that B's next part goes to was read in the step before, which every wavefront has left at the barrier.
+  // The last two steps stand apart: next to a branch the loads would be waited for before the products.
+  int st = 0;
+  fetch(0);
+  stage_b(0);
+  for (; st + 2 < steps; ++st) {
+    split_a();
+    fetch((st + 1) * BK);
+    __syncthreads();
+    multiply(st & 1);
+    stage_b(~st & 1);
+  }
+  split_a();
+  fetch(last_k);
+  __syncthreads();
+  multiply(st & 1);
+  clear_b();
+  stage_b(~st & 1);
+  const int tiny_here = is_tiny(least_b);
+  if (lane == 0) tiny_b[wave] = tiny_here;
+  clear_a();
+  split_a();
+  __syncthreads();
+  multiply(~st & 1);
+  const bool tiny = is_tiny(least_a) || (tiny_b[0] | tiny_b[1] | tiny_b[2] | tiny_b[3]) != 0;      // an operand below 2^-100, not zero
+
+  // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
+  // Zero times an infinity or a NaN is a NaN: one instruction an element where nothing is to be computed again.
+  float zeros[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) zeros[v % 4] = __builtin_fmaf(acc[i][j][v], 0.f, zeros[v % 4]);
+  const bool stands = !tiny && !__any(zeros[0] + zeros[1] + zeros[2] + zeros[3] != 0.f);
+
+  // The bias goes in before the row tests: used inside them it would be waited for again in each, and such a wait is for every
+  // store before it too (rows written one after the other: 5,000 x 32 -> 128 columns 13.9 us with the waits, 7.7 without).
+  float* __restrict__ C = static_cast<float*>(g.C);
+  const float* bias = static_cast<const float*>(g.bias);
+  const int64_t row0 = m0 + 4 * half;
+  float bv[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) bv[j] = bias ? bias[min(n0 + j * 32 + (lane & 31), g.N - 1)] : 0.f;
+  auto value = [&](float x, int j) {
+    x += bv[j];
+    return g.relu ? fmaxf(x, 0.f) : x;
+  };
+  if (stands && m0 + 32 * TM <= g.M) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + j * 32 + (lane & 31);
+      if (col >= g.N) continue;
+      float* p = C + row0 * g.ldc + col;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) p[(i * 32 + 8 * (v >> 2) + (v & 3)) * g.ldc] = value(acc[i][j][v], j);
+    }
+    return;
+  }
+
+  auto outside = [&](float x) {
+    const uint32_t u = __float_as_uint(x) & 0x7fffffffu;
+    return u >= 0x7f800000u || (tiny && u < (97u << 23));              // (97 << 23: 2^-30)
+  };
+  uint32_t redo[(TM * TN + 1) / 2], again = 0;        // a bit an element
+#pragma unroll
+  for (int t = 0; t < TM * TN; ++t) {
+    if (t % 2 == 0) redo[t / 2] = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) redo[t / 2] |= outside(acc[t / TN][t % TN][v]) ? 1u << (t % 2 * 16 + v) : 0u;
+    again |= redo[t / 2];
+  }
+  // Rows past the end, or elements to compute again: those that stand are stored first.  Then the others are computed with fp32
+  // instructions, a column tile at a time (lane: row or column l % 32, four consecutive k of eight, straight from memory).
+  auto store = [&](const v16f (&x)[TM], int j, bool redone) {
+    const int col = n0 + j * 32 + (lane & 31);
+    float* p = C + row0 * g.ldc + col;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int r = i * 32 + 8 * (v >> 2) + (v & 3), t = i * TN + j;
+        if ((redo[t / 2] >> (t % 2 * 16 + v) & 1u) == redone && row0 + r < g.M && col < g.N) p[r * g.ldc] = value(x[i][v], j);
+      }
+  };
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    v16f x[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) x[i] = acc[i][j];
+    store(x, j, false);
+  }
+  if (!__any(again != 0)) return;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    v16f x[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[i][v] = 0.f;
+    const float* col = B + min(n0 + j * 32 + (lane & 31), g.N - 1);
+#pragma unroll 1
+    for (int k0 = 0; k0 < g.Kd; k0 += 8) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = k0 + 4 * half + q, kc = min(k, g.Kd - 1);
+        const float y = col[static_cast<int64_t>(kc) * g.ldb];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const float z = row_a[i][kc];
+          x[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(k < g.Kd ? z : 0.f, k < g.Kd ? y : 0.f, x[i], 0, 0, 0);
+        }
+      }
+    }
+    store(x, j, true);
   }
 }
 
@@ -530,28 +738,81 @@ int launch_short(const GemmArgs& g, hipStream_t s) {
   return LQ_OK;
 }
 
+// Deals the tiles of bm x bn out to the workgroups of one launch; all problems of the batch share N.  `blocks`: their number.
+int deal_tiles(GemmBatch& b, int bm, int bn, int64_t* blocks) {
+  *blocks = 0;
+  for (int p = 0; p < b.count; ++p) {
+    GemmArgs& g = b.g[p];
+    g.tiles_n = (g.N + bn - 1) / bn;
+    b.first_tile[p] = static_cast<int32_t>(*blocks);
+    *blocks += (g.M + bm - 1) / bm * g.tiles_n;
+    if (*blocks > 0x7fffffffLL) return fail(LQ_ERR_UNSUPPORTED, "gemm: %lld tiles exceed one grid", (long long)*blocks);
+  }
+  b.first_tile[b.count] = static_cast<int32_t>(*blocks);
+  return LQ_OK;
+}
+
 // All problems of the batch share N (hence the tile width) and the element types.
 template <typename TA, typename TC>
 int launch_tiled_batch(GemmBatch& b, hipStream_t s) {
   const bool wide = b.g[0].N > 64;
-  const int bn = wide ? 128 : 64;
-  int64_t blocks = 0;
   for (int p = 0; p < b.count; ++p) {
     GemmArgs& g = b.g[p];
     g.a_vec_ok = aligned(g.A, 16) && (g.lda * sizeof(TA)) % 16 == 0;
     g.b_vec_ok = aligned(g.B, 16) && (g.ldb * sizeof(TA)) % 16 == 0;
-    g.tiles_n = (g.N + bn - 1) / bn;
-    b.first_tile[p] = static_cast<int32_t>(blocks);
-    blocks += (g.M + BM - 1) / BM * g.tiles_n;
-    if (blocks > 0x7fffffffLL) return fail(LQ_ERR_UNSUPPORTED, "gemm: %lld tiles exceed one grid", (long long)blocks);
   }
-  b.first_tile[b.count] = static_cast<int32_t>(blocks);
-  if (blocks == 0) return LQ_OK;
+  int64_t blocks;
+  const int rc = deal_tiles(b, BM, wide ? 128 : 64, &blocks);
+  if (rc || blocks == 0) return rc;
   if (wide)
     hipLaunchKernelGGL((gemm_tiled_kernel<TA, TC, 128>), dim3(static_cast<unsigned>(blocks)), dim3(TILED_THREADS), 0, s, b);
   else
     hipLaunchKernelGGL((gemm_tiled_kernel<TA, TC, 64>), dim3(static_cast<unsigned>(blocks)), dim3(TILED_THREADS), 0, s, b);
   LQ_LAUNCH_CHECK("gemm_tiled_kernel");
+  return LQ_OK;
+}
+
+// All problems of the batch share N.  The narrowest tiles keep the most loads in flight and the shortest chain of a step, the widest
+// read A and split it the fewest times: 32 columns up to two and a half tiles of 128 x 32 a compute unit, 128 columns from four
+// tiles of 128 x 128 on, and the large instance from eight tiles of 256 x 128 on (four rounds of two).  Time in us with tiles of 32 / 64 / 128
+// columns for k = 64 and 320: 2,500 rows -> 200 columns 7.8 / 7.4 / 10.2 and 9.6 / 15.1 / 22.4; 10,000 -> 200 (553 narrow tiles) 7.5 /
+// 9.1 / 12.1 and 19.9 / 20.1 / 24.4; 10,000 -> 500 (1,264) 12.0 / 12.0 / 15.4 and 34.5 / 29.3 / 34.2; 100,000 -> 128 (3,128) 21.8 / 21.2 / 23.4
+// and 85.5 / 61.6 / 63.0; 16,555 x 683 -> 2,048 (8,320) 294 with 64 columns, 271 with 128, 277 with the large instance;
+// 200,000 x 1,024 -> 1,024 2,440, 2,230 and 2,000.
+int launch_split_batch(GemmBatch& b, hipStream_t s) {
+  const int N = b.g[0].N;
+  const int64_t cus = num_cus();
+  int64_t large, wide, narrow, blocks;
+  if (int rc = deal_tiles(b, 128, 32, &narrow)) return rc;
+  if (narrow == 0) return LQ_OK;
+  if (int rc = deal_tiles(b, 256, 128, &large)) return rc;
+  if (int rc = deal_tiles(b, 128, 128, &wide)) return rc;
+  const dim3 block(TILED_THREADS);
+  auto deal = [&](int bm, int bn) { return deal_tiles(b, bm, bn, &blocks); };
+#define LQ_SPLIT(TM_, TN_)                                                                                                    \
+  do {                                                                                                                        \
+    if (int rc = deal(128 * TM_, 32 * TN_)) return rc;                                                                        \
+    hipLaunchKernelGGL((gemm_split_kernel<TM_, TN_>), dim3(static_cast<unsigned>(blocks)), block, 0, s, b);                   \
+  } while (0)
+  if (N <= 32 || 2 * narrow <= 5 * cus) LQ_SPLIT(1, 1);
+  else if (N <= 64 || wide < 4 * cus) LQ_SPLIT(1, 2);
+  else if (large < 8 * cus) LQ_SPLIT(1, 4);
+  else LQ_SPLIT(2, 4);
+#undef LQ_SPLIT
+  LQ_LAUNCH_CHECK("gemm_split_kernel");
+  return LQ_OK;
+}
+
+// fp32 problems of one N, more than 16 columns: each by its k alone, so that a row does not depend on the table it is part of.
+int launch_wide_f32(const GemmBatch& all, hipStream_t s) {
+  for (const bool split : {false, true}) {
+    GemmBatch b{};
+    for (int p = 0; p < all.count; ++p)
+      if ((all.g[p].Kd > 16) == split) b.g[b.count++] = all.g[p];
+    if (b.count == 0) continue;
+    const int rc = split ? launch_split_batch(b, s) : launch_tiled_batch<float, float>(b, s);
+    if (rc) return rc;
+  }
   return LQ_OK;
 }
 
@@ -592,7 +853,8 @@ int launch_typed(GemmArgs g, hipStream_t s) {
   GemmBatch b{};
   b.g[0] = g;
   b.count = 1;
-  return launch_tiled_batch<TA, TC>(b, s);
+  if constexpr (sizeof(TA) == 4) return launch_wide_f32(b, s);
+  else return launch_tiled_batch<TA, TC>(b, s);
 }
 
 // ------------------------------------------------------------------ row split ----------
@@ -829,7 +1091,7 @@ int launch_project_dims_all(int32_t K, const lq_mat* D, const lq_mat& W, int32_t
     }
     return LQ_OK;
   }
-  if (f32) return launch_tiled_batch<float, float>(all, s);
+  if (f32) return launch_wide_f32(all, s);
   if (mixed) return launch_tiled_batch<bf16_t, float>(all, s);
   return launch_tiled_batch<bf16_t, bf16_t>(all, s);
 }

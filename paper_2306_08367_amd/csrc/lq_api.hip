@@ -307,16 +307,22 @@ int lq_fusion_advice(const lq_star* star, const lq_model* model, double queries_
   //   streamed bytes (fact columns, keys, outputs, T written and read back)   ~5 TB/s
   //   gathered bytes (rows of P_k or D_k; from L2 / the 256 MB Infinity Cache while the tables fit
   //   in half of it, else whole 128-byte lines from memory)                    ~14 TB/s / ~3 TB/s
-  //   dense products                                                           ~60 TFLOP/s fp32, ~400 bf16
+  //   dense products                                                           ~60 TFLOP/s fp32, ~400 bf16; 200 for fp32 products
+  //   of more than 16 k and 16 columns outside the fused kernels (gemm_split_kernel).  32 -> 128 columns on 2.4e6 rows, which
+  //   decides for the non-fused pipeline: 0.42 ms measured, 0.50 so, 0.73 with 60; fused 0.51 measured, 0.52 so
   //   a kernel launch                                                          ~4 us
   const double c_f = star->fact.cols > 0 ? star->fact.cols : 0;
   const double K = star->n_dims;
   constexpr double STREAM = 5.0e12, CACHE_GATHER = 14.0e12, MEMORY_GATHER = 3.0e12, LAUNCH = 4.0e-6;
   constexpr double CACHE_BYTES = 128.0 * 1024 * 1024;
   const double dense = c.dtype == LQ_BF16 ? 400.0e12 : 60.0e12;
-  double later_flops = 0, later_bytes = 0;     // layers after the first: same products in both pipelines,
-  for (int j = 1; j < model->n_layers; ++j) {  // but the non-fused one moves every activation through memory
+  auto product_seconds = [&](double in, double cols) {       // a row of a dense product outside the fused kernels
+    return 2.0 * in * cols / (c.dtype != LQ_BF16 && in > 16 && cols > 16 ? 200.0e12 : dense);
+  };
+  double later_flops = 0, later_seconds = 0, later_bytes = 0;     // layers after the first: same products in both pipelines,
+  for (int j = 1; j < model->n_layers; ++j) {                     // but the non-fused one moves every activation through memory
     later_flops += 2.0 * static_cast<double>(model->W[j].rows) * model->W[j].cols;
+    later_seconds += product_seconds(static_cast<double>(model->W[j].rows), model->W[j].cols);
     later_bytes += 2.0 * es * static_cast<double>(model->W[j].rows);
   }
   auto gather_seconds = [&](double row_bytes, double table_bytes) {
@@ -324,16 +330,18 @@ int lq_fusion_advice(const lq_star* star, const lq_model* model, double queries_
     return std::max(row_bytes, 128.0) / MEMORY_GATHER;
   };
   double gather_f = 0, gather_n = 0;           // one row of P_j / of D_j per dimension and fact row
+  double products = 0;
   for (int j = 0; j < star->n_dims; ++j) {
+    products += static_cast<double>(star->dims[j].rows) * product_seconds(star->dims[j].cols, l);
     gather_f += gather_seconds(es * l, p_elems * es);
     gather_n += gather_seconds(es * star->dims[j].cols, dim_elems * es);
   }
   const double stream_f = es * c_f + 4.0 * K + es * c.l_out;
   const double stream_n = es * c_f + 4.0 * K + 2.0 * es * k + later_bytes + es * c.l_out;
   out->seconds_fused = n * (stream_f / STREAM + gather_f + later_flops / dense) + LAUNCH;
-  out->seconds_no_fusion = n * (stream_n / STREAM + gather_n + (2.0 * k * l + later_flops) / dense) +
+  out->seconds_no_fusion = n * (stream_n / STREAM + gather_n + product_seconds(k, l) + later_seconds) +
                            (1.0 + model->n_layers) * LAUNCH;
-  out->seconds_prefusion = (dim_elems + p_elems) * es / STREAM + 2.0 * prefuse / dense + LAUNCH;
+  out->seconds_prefusion = (dim_elems + p_elems) * es / STREAM + products + LAUNCH;
   out->fuse = queries_per_update * (out->seconds_no_fusion - out->seconds_fused) > out->seconds_prefusion ? 1 : 0;
   return LQ_OK;
 }

@@ -1,5 +1,6 @@
 """Projections onto a few outputs (gemm_rowsplit_kernel, gemm_skinny_kernel): one launch for all tables that a kernel serves,
-sums scattered over the lanes of a row.  Against float64, with the bound of k fp32 multiply-adds."""
+sums scattered over the lanes of a row.  Against float64, with the bound of k fp32 multiply-adds.
+Projections onto more than 16 outputs (gemm_split_kernel): fp32 operands in three bf16 pieces, what these cannot hold in fp32."""
 import pytest
 import torch
 
@@ -31,3 +32,87 @@ def test_few_outputs(outputs, rows, cols):
         if D.shape[0] > 16:
             few = lq.lq_project_dims([D[5:16].contiguous()], torch.cat([W[:3], w.float()]), 3)[0]
             assert torch.equal(few, p[5:16])
+
+
+def _project(D, W):
+    import paper_2306_08367_amd as lq
+    return lq.lq_project_dims([D], W, 0)[0][:, :W.shape[1]]
+
+
+def _within_bound(got, D, W):
+    # k fp32 multiply-adds; the products left out of nine are below 3 * 2^-26 of the product and within the two terms added to k
+    bound = (D.shape[1] + 2) * 2.0 ** -24 * (D.double().abs() @ W.double().abs())
+    return bool(((got.double() - D.double() @ W.double()).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("k", [1, 7, 16, 17, 31, 48, 100, 683])
+@pytest.mark.parametrize("outputs", [17, 32, 33, 64, 65, 128, 130, 257])
+def test_split_products(outputs, k):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1_000 * outputs + k)
+    W = torch.randn(k, outputs, generator=gen, device="cuda")
+    D = torch.randn(385, k, generator=gen, device="cuda") * torch.exp2(torch.randint(-20, 20, (385, 1), generator=gen, device="cuda").float())
+    whole = _project(D, W)
+    assert _within_bound(whole, D, W)
+    for rows in (1, 31, 127, 128, 129, 256):                  # a row does not depend on the table it is part of
+        assert torch.equal(_project(D[:rows].contiguous(), W), whole[:rows])
+    assert torch.equal(_project(D[100:300].contiguous(), W), whole[100:300])
+
+
+@pytest.mark.parametrize("k", [17, 64])
+def test_split_products_of_large_tables(k):
+    """Enough 256-row tiles for the larger instance, the last one ragged: the bits of the smaller one."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    rows, outputs = 65_536 + 77, 1_025
+    D, W = torch.randn(rows, k, generator=gen, device="cuda"), torch.randn(k, outputs, generator=gen, device="cuda")
+    got = _project(D, W)
+    for at in (0, 30_000, rows - 1_000):
+        part = D[at:at + 1_000].contiguous()
+        assert torch.equal(_project(part, W), got[at:at + 1_000]) and _within_bound(got[at:at + 1_000], part, W)
+    D[3, 1], D[rows - 1, 0] = float("inf"), float("nan")
+    again = _project(D, W)
+    assert torch.equal(again[4:-1], got[4:-1]) and bool(again[-1].isnan().all())
+    assert torch.equal(again[3], torch.sign(W[1]) * float("inf"))
+
+
+@pytest.mark.parametrize("outputs", [20, 64, 200])
+def test_split_products_outside_the_range_of_the_pieces(outputs):
+    """Infinities, NaNs, values next to the largest and below the smallest normal ones: as fp32 arithmetic gives them, and
+    nothing else changes."""
+    inf, nan = float("inf"), float("nan")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(outputs)
+    D, W = torch.randn(300, 40, generator=gen, device="cuda"), torch.randn(40, outputs, generator=gen, device="cuda")
+    W[:, 3] = 0
+    W[0, 3] = 0.5
+    plain = _project(D, W)
+    special = D.clone()
+    special[5, 7], special[140, 0], special[299, 39] = inf, nan, -inf
+    special[50], special[51] = 0, 0
+    special[50, 0] = 3.4e38                                   # rounds to a bf16 infinity, times 0.5 in column 3
+    got = _project(special, W)
+    assert torch.equal(got[5, 4:], torch.sign(W[7, 4:]) * inf) and bool(got[140].isnan().all())
+    assert torch.equal(got[299, 4:], torch.sign(W[39, 4:]) * -inf)
+    assert bool(got[5, 3].isnan()) and bool(got[299, 3].isnan())   # inf * 0
+    assert float(got[50, 3]) == float(special[50, 0] * 0.5) and bool((got[51] == 0).all())
+    rest = torch.ones(300, dtype=torch.bool, device="cuda")
+    rest[[5, 50, 51, 140, 299]] = False
+    assert torch.equal(got[rest], plain[rest])
+    w = W.clone()
+    w[11, 9], w[12, 10] = inf, nan
+    got = _project(D, w)
+    assert torch.equal(got[:, 9], torch.sign(D[:, 11]) * inf) and bool(got[:, 10].isnan().all())
+    assert torch.equal(got[:, 11:], plain[:, 11:]) and torch.equal(got[:, :9], plain[:, :9])
+
+
+@pytest.mark.parametrize("scale_d, scale_w", [(-20, 0), (-100, 0), (-118, 0), (-130, 0), (-142, 0), (-75, -45), (0, -125), (-120, 60), (100, -100)])
+def test_split_products_of_small_numbers(scale_d, scale_w):
+    """Down to subnormal operands and results: the bound of fp32 arithmetic, half a unit of the smallest subnormal a term besides."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    D = torch.ldexp(torch.randn(200, 30, generator=gen, device="cuda"), torch.tensor(scale_d, device="cuda"))
+    W = torch.ldexp(torch.randn(30, 70, generator=gen, device="cuda"), torch.tensor(scale_w, device="cuda"))
+    got = _project(D, W)
+    bound = 32 * 2.0 ** -24 * (D.double().abs() @ W.double().abs()) + 30 * 2.0 ** -149
+    assert bool(((got.double() - D.double() @ W.double()).abs() <= bound).all())
