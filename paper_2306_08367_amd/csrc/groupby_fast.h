@@ -523,123 +523,198 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_fast_mem_kernel(FastArgs a,
   }
 }
 
-// First pass of the bucketed form.  Per round of the workgroup (up to 8 rows per thread): every survivor takes a
+// What a side table holds for a key: the bitmap word, or the code table's entry (one byte; with WIDE, some table of the call has
+// entries of two bytes, and of a table of bytes the aligned pair is read, so that there is no branch between the reads of
+// several rows: tables are padded to 16 bytes).
+template <bool BYTE, bool WIDE>
+__device__ __forceinline__ uint32_t side_word(const uint8_t* t, uint32_t j, bool wide) {
+  if constexpr (!BYTE) return reinterpret_cast<const uint32_t*>(t)[j >> 5];
+  else if constexpr (WIDE) return *reinterpret_cast<const uint16_t*>(t + (wide ? 2u * j : j & ~1u));
+  else return t[j];
+}
+template <bool BYTE, bool WIDE>
+__device__ __forceinline__ void side_apply(uint32_t w, uint32_t j, int32_t stride, bool wide, bool& alive, int32_t& g) {
+  if constexpr (!BYTE) {
+    alive = alive && ((w >> (j & 31)) & 1u);
+  } else {
+    const uint32_t code = WIDE && !wide ? (w >> (8 * (j & 1u))) & 0xffu : w, none = WIDE && wide ? 0xffffu : 0xffu;
+    alive = alive && code != none;                             // (all ones: filtered out)
+    g += static_cast<int32_t>(code) * stride;
+  }
+}
+
+// All dimensions of N fact rows.  A dimension's reads for all rows go out together (row by row, each under a test of its own, they
+// are waited for one after the other).  Tables in memory are only
+// read by lanes with a survivor of those in LDS; its dead rows read the first entry.
+template <int N, int NBL, int NML, int NMG, int NBG, bool WIDE = false>
+__device__ __forceinline__ void classify_rows(const FastArgs& a, const uint8_t* tab, const int32_t (&key)[NBL + NML + NMG + NBG][N],
+                                              bool (&alive)[N], int32_t (&g)[N]) {
+  constexpr int NL = NBL + NML, ND = NL + NMG + NBG;
+  uint32_t w[ND][N];
+#pragma unroll
+  for (int k = 0; k < ND; ++k) {
+    const bool wide = WIDE && a.wide[k] != 0;
+    uint32_t j[N];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      alive[q] = alive[q] && key[k][q] >= 0;
+      j[q] = k < NL ? max(key[k][q], 0) : alive[q] ? key[k][q] : 0;
+      any = any || alive[q];
+      w[k][q] = 0;
+    }
+    if (k < NL) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) w[k][q] = k < NBL ? side_word<true, WIDE>(tab + a.off[k], j[q], wide) : side_word<false, false>(tab + a.off[k], j[q], false);
+    } else if (any) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) w[k][q] = k < NL + NMG ? side_word<false, false>(a.packed + a.off[k], j[q], false) : side_word<true, WIDE>(a.packed + a.off[k], j[q], wide);
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      if (k < NBL || k >= NL + NMG) side_apply<true, WIDE>(w[k][q], j[q], a.stride[k], wide, alive[q], g[q]);
+      else side_apply<false, false>(w[k][q], j[q], 0, false, alive[q], g[q]);
+    }
+  }
+}
+
+// Keys (and fact-mask bytes) of four neighbouring fact rows.  A scan holds two of them and fills one again, with the rows two steps on,
+// as soon as its keys have been looked up and the measures of its rows are requested: loads complete in the order of their
+// issue, so whatever is waited for next does not wait for keys that are needed much later, and nothing in flight is copied.
+// `v` past the last one: that one again (its rows are then not alive).
+template <int ND>
+struct Keys { v4i k[ND]; uint32_t fact_mask; };
+template <int ND, bool WIDE>
+__device__ __forceinline__ void load_keys(const FastArgs& a, int64_t v, int64_t v_end, Keys<ND>& keys) {
+  const int64_t at = min(v, v_end - 1);
+#pragma unroll
+  for (int k = 0; k < ND; ++k) keys.k[k] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(a.fk[k]) + at);
+  keys.fact_mask = fact_mask_word<WIDE>(a, at);
+}
+
+// The measures of rows 4 v .. 4 v + 3.  Measure columns are only touched where a lane has a survivor: the others read the first
+// element (under a test, the values would be waited for inside it).
+template <int MM>
+__device__ __forceinline__ void load_measures(const FastArgs& a, bool any, int64_t v, v4i (&val)[MM]) {
+#pragma unroll
+  for (int m = 0; m < MM; ++m) val[m] = *(reinterpret_cast<const v4i*>(a.meas[m]) + (any ? v : 0));
+  asm volatile("" ::: "memory");                   // (not moved behind the keys, nor these ahead)
+}
+
+// The eight fact rows of two steps: their groups and which of them survive; `there`: the steps are not past the end.
+template <int NBL, int NML, int NMG, int NBG, bool WIDE>
+__device__ __forceinline__ void rows_of(const FastArgs& a, const uint8_t* tab, const Keys<NBL + NML + NMG + NBG> (&keys)[2],
+                                        const bool (&there)[2], bool (&alive)[8], int32_t (&g)[8]) {
+  int32_t key[NBL + NML + NMG + NBG][8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+#pragma unroll
+    for (int k = 0; k < NBL + NML + NMG + NBG; ++k) key[k][q] = keys[q / 4].k[k][q % 4];
+    key[0][q] = masked_key<WIDE>(keys[q / 4].fact_mask, q % 4, key[0][q]);
+    g[q] = 0;
+    alive[q] = there[q / 4];
+  }
+  classify_rows<8, NBL, NML, NMG, NBG, WIDE>(a, tab, key, alive, g);
+}
+
+// First pass of the bucketed form.  Per round of the workgroup (8 rows per thread): every survivor takes a
 // rank inside its bucket from an LDS counter; one thread per bucket with survivors reserves that many slots
-// of the bucket with one device-wide atomic; the survivors are then written to their slots.  Every thread
-// of the workgroup takes the same number of steps (the barriers are inside the loop); lanes past the end
-// carry keys of -1.  gcount is zero and the outputs are cleared before the launch.
+// of the bucket with one device-wide atomic; the survivors are then written to their slots.  Workgroups take steps in turn;
+// every thread of a workgroup takes the same number of rounds (the barriers are inside the loop), rows past the end are not
+// alive.  gcount is zero and the outputs are cleared before the launch.
+// A round is a chain of waits: keys, gathers from tables in memory, measures, the reservation, the stores of the round before.  The
+// gathers of a thread's eight rows go out together, and the keys of the next round behind the measures of this one.
+// 24e6 rows into 342 buckets, a table in memory, 20 % survive: 183 us with the gathers row by row, 162 so; 6e6 rows, 0.8 % survive:
+// 32.5 and 29; calls of one round, which has a second, empty step now, 1 to 2 us more (500,000 rows 21.1 -> 22.2).  With the keys of
+// the next round requested only where there is one: 168, and no gain for calls of one round.  (Slots of its own for every workgroup, without reservation and barriers: 190 us, the lines of a slot leave the L2
+// in more pieces; survivors sorted in LDS and written in runs: 180; both: 163, with the fold 6 us longer and calls of
+// 500,000 rows 20 % longer.)
 template <int NBL, int NML, int NMG, int NBG, int MM, bool WIDE>
-__global__ __launch_bounds__(SCAN_THREADS) void scan_fast_bucket_kernel(FastArgs a, BucketArgs b, int64_t per_block) {
+__global__ __launch_bounds__(SCAN_THREADS) void scan_fast_bucket_kernel(FastArgs a, BucketArgs b) {
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int ND = NBL + NML + NMG + NBG;
   uint8_t* tab = smem;
-  unsigned int* lcount = reinterpret_cast<unsigned int*>(smem + round_up(static_cast<size_t>(a.lds_bytes), 16));
-  unsigned int* lbase = lcount + b.buckets;
-  const int tid = threadIdx.x;
+  const int B = b.buckets, tid = threadIdx.x;
+  unsigned int* count = reinterpret_cast<unsigned int*>(smem + round_up(static_cast<size_t>(a.lds_bytes), 16));
+  unsigned int* base = count + B;                 // first slot of a bucket's survivors of this round
   const GlobalOut gout{a.gsums, a.gcounts, nullptr, nullptr};
 
-  const int64_t n_vec = a.n / 4;
-  const int64_t v_begin = static_cast<int64_t>(blockIdx.x) * per_block;
-  const int64_t v_end = min(n_vec, v_begin + per_block);
-  const int64_t steps = v_begin < v_end ? (v_end - v_begin + SCAN_THREADS - 1) / SCAN_THREADS : 0;
-  int64_t v = v_begin + tid;
-  const v4i none = {-1, -1, -1, -1};
-  v4i cur[ND], nxt[ND];
-#pragma unroll
-  for (int k = 0; k < ND; ++k)
-    cur[k] = v < v_end ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(a.fk[k]) + v) : none;
-  uint32_t fm_cur = v < v_end ? fact_mask_word<WIDE>(a, v) : ~0u, fm_nxt = ~0u;
+  const int64_t n_vec = a.n / 4, stride = static_cast<int64_t>(gridDim.x) * SCAN_THREADS;
+  int64_t v = static_cast<int64_t>(blockIdx.x) * SCAN_THREADS + tid;
+  Keys<ND> keys[2];
+  if (n_vec > 0) {
+    load_keys<ND, WIDE>(a, v, n_vec, keys[0]);
+    load_keys<ND, WIDE>(a, v + stride, n_vec, keys[1]);
+  }
   {
     const uint4* src = reinterpret_cast<const uint4*>(a.packed);
     uint4* dst = reinterpret_cast<uint4*>(tab);
     for (uint32_t i = tid; i < a.lds_bytes / 16; i += SCAN_THREADS) dst[i] = src[i];
   }
-  for (int i = tid; i < b.buckets; i += SCAN_THREADS) lcount[i] = 0u;
+  for (int i = tid; i < B; i += SCAN_THREADS) count[i] = 0u;
   __syncthreads();
 
-  // A round is up to NS steps (4 NS rows per thread): their survivors stay in registers until the round's
-  // slots are reserved, so that the two barriers and the reservation are paid once per 4 NS rows.
-  constexpr int NS = 2;
-  for (int64_t st0 = 0; st0 < steps; st0 += NS) {
-    int32_t g[NS][4];
-    int32_t val[NS][4][MM];
-    unsigned int rank[NS][4];
-    unsigned int alive_bits = 0u;                   // bit 4 s + q: row q of step s survives
+  // A survivor into slot `pos` of its bucket, or through the atomics when the bucket is full (the whole wavefront takes part).
+  auto put = [&](bool alive, unsigned int pos, int32_t g, const int32_t (&val)[MM]) {
+    const bool over = alive && pos >= b.cap;
+    if (alive && !over) {
+      uint32_t* dst = b.pairs + (static_cast<size_t>(g >> b.shift) * b.cap + pos) * (1 + MM);
+      const uint32_t gl = static_cast<uint32_t>(g & ((1 << b.shift) - 1));
+      // (ordinary stores: the runs of a bucket are completed in L2 by later rounds and other workgroups;
+      // streaming stores send every 8-byte piece to memory on its own and were measured 3.6x slower)
+      if constexpr (MM == 1) {             // one 8-byte store (slots of two words are 8-byte aligned)
+        typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+        *reinterpret_cast<v2u*>(dst) = v2u{gl, static_cast<uint32_t>(val[0])};
+      } else {
+        dst[0] = gl;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      if (st0 + s < steps) {                        // (the same for the whole workgroup)
-        const int64_t vn = v + SCAN_THREADS;
-#pragma unroll
-        for (int k = 0; k < ND; ++k)
-          nxt[k] = vn < v_end ? __builtin_nontemporal_load(reinterpret_cast<const v4i*>(a.fk[k]) + vn) : none;
-        fm_nxt = vn < v_end ? fact_mask_word<WIDE>(a, vn) : ~0u;
-        bool alive[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          int32_t j[ND];
-#pragma unroll
-          for (int k = 0; k < ND; ++k) j[k] = cur[k][q];
-          j[0] = masked_key<WIDE>(fm_cur, q, j[0]);
-          g[s][q] = 0;
-          alive[q] = true;
-          classify_fast<NBL, NML, NMG, NBG, WIDE>(a, tab, j, alive[q], g[s][q]);
-        }
-        const bool any = alive[0] || alive[1] || alive[2] || alive[3];
-#pragma unroll
-        for (int m = 0; m < MM; ++m) {              // measure columns are only touched where a lane has a survivor
-          const v4i t = any ? *(reinterpret_cast<const v4i*>(a.meas[m]) + v) : none;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) val[s][q][m] = t[q];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          rank[s][q] = alive[q] ? atomicAdd(&lcount[g[s][q] >> b.shift], 1u) : 0u;
-          alive_bits |= alive[q] ? 1u << (4 * s + q) : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < ND; ++k) cur[k] = nxt[k];
-        fm_cur = fm_nxt;
-        v = vn;
+        for (int m = 0; m < MM; ++m) dst[1 + m] = static_cast<uint32_t>(val[m]);
       }
     }
+    if (__ballot(over) != 0ull) {
+      long long wide[MM];
+#pragma unroll
+      for (int m = 0; m < MM; ++m) wide[m] = val[m];
+      merge_and_add<MM>(over, g, wide, MM, a.G, gout);
+    }
+  };
+
+  // Two steps at a time: their gathers go out together, then their measures, then the keys of the next round.
+  int32_t g[8], val[MM][8];
+  unsigned int rank[8];
+  bool alive[8];
+  auto look = [&]() {
+    const bool there[2] = {v < n_vec, v + stride < n_vec};
+    rows_of<NBL, NML, NMG, NBG, WIDE>(a, tab, keys, there, alive, g);
+    v4i m4[2][MM];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) load_measures(a, alive[4 * s] || alive[4 * s + 1] || alive[4 * s + 2] || alive[4 * s + 3], v + s * stride, m4[s]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) load_keys<ND, WIDE>(a, v + (2 + s) * stride, n_vec, keys[s]);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      rank[q] = alive[q] ? atomicAdd(&count[g[q] >> b.shift], 1u) : 0u;
+#pragma unroll
+      for (int m = 0; m < MM; ++m) val[m][q] = m4[q / 4][m][q % 4];
+    }
+    v += 2 * stride;
+  };
+
+  while (v - tid < n_vec) {
+    look();
     __syncthreads();
-    for (int i = tid; i < b.buckets; i += SCAN_THREADS) {
-      const unsigned int c = lcount[i];
-      if (c) { lbase[i] = atomicAdd(&b.gcount[i], c); lcount[i] = 0u; }
+    for (int i = tid; i < B; i += SCAN_THREADS) {
+      const unsigned int c = count[i];
+      if (c) { base[i] = atomicAdd(&b.gcount[i], c); count[i] = 0u; }
     }
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
+    for (int q = 0; q < 8; ++q) {
+      int32_t x[MM];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        bool over = false;
-        if ((alive_bits >> (4 * s + q)) & 1u) {
-          const int bk = g[s][q] >> b.shift;
-          const unsigned int pos = lbase[bk] + rank[s][q];
-          if (pos < b.cap) {
-            uint32_t* dst = b.pairs + (static_cast<size_t>(bk) * b.cap + pos) * (1 + MM);
-            const uint32_t gl = static_cast<uint32_t>(g[s][q] & ((1 << b.shift) - 1));
-            // (ordinary stores: the runs of a bucket are completed in L2 by later rounds and other workgroups;
-            // streaming stores send every 8-byte piece to memory on its own and were measured 3.6x slower)
-            if constexpr (MM == 1) {             // one 8-byte store (slots of two words are 8-byte aligned)
-              typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-              *reinterpret_cast<v2u*>(dst) = v2u{gl, static_cast<uint32_t>(val[s][q][0])};
-            } else {
-              dst[0] = gl;
-#pragma unroll
-              for (int m = 0; m < MM; ++m) dst[1 + m] = static_cast<uint32_t>(val[s][q][m]);
-            }
-          } else {
-            over = true;
-          }
-        }
-        if (__ballot(over) != 0ull) {                // rare: a bucket is full, the rest of it takes the atomics
-          long long wide[MM];
-#pragma unroll
-          for (int m = 0; m < MM; ++m) wide[m] = val[s][q][m];
-          merge_and_add<MM>(over, g[s][q], wide, MM, a.G, gout);
-        }
-      }
+      for (int m = 0; m < MM; ++m) x[m] = val[m][q];
+      put(alive[q], alive[q] ? base[g[q] >> b.shift] + rank[q] : 0u, g[q], x);
+    }
   }
   // ragged tail (n % 4 rows): one row per lane, straight to memory
   if (blockIdx.x == 0) {
@@ -705,12 +780,8 @@ int launch_fast_inst(const FastArgs& a, const FastLaunch& L) {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(L.lds)));
     // one resident set of workgroups (this kernel's registers allow fewer per compute unit than its LDS does)
     const int64_t resident = static_cast<int64_t>(num_cus()) * resident_per_cu(reinterpret_cast<const void*>(kernel), SCAN_THREADS, L.lds);
-    const int64_t n_vec = a.n / 4;
-    int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(L.blocks, resident));
-    int64_t per_block = (n_vec + blocks - 1) / blocks;
-    per_block = std::max<int64_t>(SCAN_THREADS, (per_block + SCAN_THREADS - 1) / SCAN_THREADS * SCAN_THREADS);
-    blocks = std::max<int64_t>(1, (n_vec + per_block - 1) / per_block);
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(SCAN_THREADS), L.lds, L.s, a, L.bucket, per_block);
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(L.blocks, resident));
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(SCAN_THREADS), L.lds, L.s, a, L.bucket);
     LQ_LAUNCH_CHECK("scan_fast_bucket_kernel");
     const size_t fold_lds = static_cast<size_t>(MM + 1) * (size_t{1} << L.bucket.shift) * 8;
     if (fold_lds > 64 * 1024)

@@ -381,6 +381,21 @@ def test_bucketed_many_groups_ragged_sizes_and_negative_keys(lq, n):
     _check(lq, _many_groups(360 + n, n, (70, 110, 50, 130), (70, 110, 3, 1), 2, sel=(None, 0.8, 0.5, 0.6), neg=True))
 
 
+@pytest.mark.parametrize("rows,card,sel", [
+    ((140_000, 200_000, 90), (25, 400, 7), (None, 0.3, None)),          # a masked 16-bit table in memory
+    ((140_000, 2_000_000, 300_000), (25, 1, 1_000), (None, 0.4, 0.5)),  # a bitmap and a 16-bit table in memory
+    ((250_000, 180_000, 90), (200, 90, 3), (0.5, None, None)),          # byte tables, one or two of them in memory
+], ids=["u16", "bitmap_u16", "bytes"])
+def test_bucketed_many_groups_with_tables_in_memory(lq, rows, card, sel):
+    """Tables too large for LDS: the reads of a thread's eight rows go out together.  Sizes around one row, a step and a round of a
+    workgroup, with keys that match nothing; with one fact mask."""
+    for n in (1, 6, 4_095, 4_097, 8_193, 2_300_003):
+        _check(lq, _many_groups(390 + n, n, rows, card, 1 + n % 2, sel=sel, neg=True))
+    w = _many_groups(389, 50_001, rows, card, 2, sel=sel, neg=True)
+    w.fact_mask = (torch.arange(w.n) % 3 != 0).to(torch.uint8)
+    _check(lq, w)
+
+
 @pytest.mark.parametrize("card,n_measures", [
     ((91, 91), 1),                  # 8,281 groups: just past the LDS limit at one measure, buckets of 32 groups
     ((65, 64), 2),                  # 4,160 groups x 3 accumulators: buckets of 16
