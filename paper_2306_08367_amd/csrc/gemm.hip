@@ -295,8 +295,9 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 // wavefront, before it is stored:
 //  * an infinity, a NaN or a value that rounds to a bf16 infinity leaves a NaN or an infinity in its row or column, since
 //    the second piece is then inf - inf or an infinity of the other sign;
-//  * an operand below 2^-100 other than zero loses bits below 2^-134 of it.  The kernel looks for such operands; if there is one,
-//    results below 2^-30 are computed again.
+//  * an operand below 2^-100 other than zero has pieces among the subnormal numbers and may lose up to 2^-126.  Where there is one,
+//    results below 2^-30 are computed again, and all of them if the other side has an operand of 2^64 or more.  What stands is then
+//    at least 2^-30 and has lost less than 2^-62 a term.
 // Apart from that, the order of the sums depends on k only: a row computed alone equals the same row computed as part of a table,
 // whichever of the instances below computes it.
 //
@@ -329,6 +330,15 @@ __device__ __forceinline__ uint32_t least_of(const float (&x)[N], uint32_t least
   return least;
 }
 
+// The larger of `most` and |x|; a NaN stays one.
+template <int N>
+__device__ __forceinline__ float most_of(const float (&x)[N], float most) {
+#pragma unroll
+  for (int q = 0; q < N; q += 2)
+    most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(x[q]), __builtin_fabsf(x[q + 1])), most);
+  return most;
+}
+
 template <int TM, int TN>
 __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split_kernel(GemmBatch batch) {
   int problem = 0;
@@ -344,7 +354,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   static_assert(TILED_THREADS % BN == 0 && BP * (TILED_THREADS / BN) == BK, "B's tile must be dealt out evenly");
   constexpr int PLANE = BN * 2;                                // 16-byte pieces of a part: [column / 32][half of k][column % 32]
   __shared__ __align__(16) v4u smem[2][3 * PLANE];
-  __shared__ int tiny_b[4];
+  __shared__ int range_b[4];
   const float* __restrict__ A = static_cast<const float*>(g.A);
   const float* __restrict__ B = static_cast<const float*>(g.B);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
@@ -370,6 +380,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   const int bk = tid / BN * BP, bc = tid % BN;
   const uint32_t col_b = min(n0 + bc, g.N - 1);
   uint32_t least_a = 0xffffffffu, least_b = 0xffffffffu;
+  float most_a = 0.f, most_b = 0.f;
 
   auto fetch = [&](int k0) {
 #pragma unroll
@@ -400,6 +411,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
     unsigned int pb[3][BP / 2];
     split_pairs<BP>(rb, pb);
     least_b = least_of<BP>(rb, least_b);
+    most_b = most_of<BP>(rb, most_b);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       v4u* to = &smem[buf][p * PLANE + (bc / 32 * 2 + bk / 8) * 32 + bc % 32];
@@ -408,7 +420,10 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
       else reinterpret_cast<unsigned int*>(to)[bk / 2 % 4] = pb[p][0];
     }
   };
-  auto is_tiny = [](uint32_t least) { return __any(least < (27u << 24) - 1u) != 0; };      // (27 << 24: 2^-100 shifted left)
+  constexpr int TINY = 1, VAST = 2;          // an operand below 2^-100 and not zero (27 << 24: 2^-100 shifted left); one of 2^64 or more, or a NaN
+  auto range_of = [](uint32_t least, float most) {
+    return (__any(least < (27u << 24) - 1u) ? TINY : 0) | (__any(!(most < 0x1p64f)) ? VAST : 0);
+  };
   v4u a[TM][3];
   auto split_a = [&]() {
 #pragma unroll
@@ -416,6 +431,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
       unsigned int pa[3][4];
       split_pairs<8>(ra[i], pa);
       least_a = least_of<8>(ra[i], least_a);
+      most_a = most_of<8>(ra[i], most_a);
 #pragma unroll
       for (int p = 0; p < 3; ++p) a[i][p] = v4u{pa[p][0], pa[p][1], pa[p][2], pa[p][3]};
     }
@@ -463,13 +479,15 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   multiply(st & 1);
   clear_b();
   stage_b(~st & 1);
-  const int tiny_here = is_tiny(least_b);
-  if (lane == 0) tiny_b[wave] = tiny_here;
+  const int range_here = range_of(least_b, most_b);
+  if (lane == 0) range_b[wave] = range_here;
   clear_a();
   split_a();
   __syncthreads();
   multiply(~st & 1);
-  const bool tiny = is_tiny(least_a) || (tiny_b[0] | tiny_b[1] | tiny_b[2] | tiny_b[3]) != 0;      // an operand below 2^-100, not zero
+  const int of_a = range_of(least_a, most_a), of_b = range_b[0] | range_b[1] | range_b[2] | range_b[3];
+  const bool tiny = ((of_a | of_b) & TINY) != 0;
+  const bool lost = ((of_a & TINY) && (of_b & VAST)) || ((of_b & TINY) && (of_a & VAST));
 
   // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
   // Zero times an infinity or a NaN is a NaN: one instruction an element where nothing is to be computed again.
@@ -510,7 +528,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
 
   auto outside = [&](float x) {
     const uint32_t u = __float_as_uint(x) & 0x7fffffffu;
-    return u >= 0x7f800000u || (tiny && u < (97u << 23));              // (97 << 23: 2^-30)
+    return u >= 0x7f800000u || lost || (tiny && u < (97u << 23));      // (97 << 23: 2^-30)
   };
   uint32_t redo[(TM * TN + 1) / 2], again = 0;        // a bit an element
 #pragma unroll

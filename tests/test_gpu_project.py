@@ -106,7 +106,8 @@ def test_split_products_outside_the_range_of_the_pieces(outputs):
     assert torch.equal(got[:, 11:], plain[:, 11:]) and torch.equal(got[:, :9], plain[:, :9])
 
 
-@pytest.mark.parametrize("scale_d, scale_w", [(-20, 0), (-100, 0), (-118, 0), (-130, 0), (-142, 0), (-75, -45), (0, -125), (-120, 60), (100, -100)])
+@pytest.mark.parametrize("scale_d, scale_w", [(-20, 0), (-100, 0), (-118, 0), (-130, 0), (-142, 0), (-75, -45), (0, -125), (-120, 60), (100, -100),
+                                              (-70, -70), (-66, -72), (-120, 100), (-130, 110), (-124, 124), (116, -116), (120, -120), (124, -124)])
 def test_split_products_of_small_numbers(scale_d, scale_w):
     """Down to subnormal operands and results: the bound of fp32 arithmetic, half a unit of the smallest subnormal a term besides."""
     gen = torch.Generator(device="cuda")
@@ -116,3 +117,12 @@ def test_split_products_of_small_numbers(scale_d, scale_w):
     got = _project(D, W)
     bound = 32 * 2.0 ** -24 * (D.double().abs() @ W.double().abs()) + 30 * 2.0 ** -149
     assert bool(((got.double() - D.double() @ W.double()).abs() <= bound).all())
+
+
+def test_split_products_of_a_small_and_a_large_operand_beside_others():
+    """A term that its operand's pieces do not hold, in a sum that is not small."""
+    D, W = torch.zeros(40, 30, device="cuda"), torch.zeros(30, 70, device="cuda")
+    D[:, 0], D[:, 1] = 2.0 ** -140, 2.0 ** -25
+    W[0], W[1] = 2.0 ** 120, 1
+    assert bool((_project(D, W) == 2.0 ** -20 + 2.0 ** -25).all())
+    assert bool((_project(W.t().contiguous(), D.t().contiguous()) == 2.0 ** -20 + 2.0 ** -25).all())
