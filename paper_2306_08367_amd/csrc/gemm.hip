@@ -295,11 +295,11 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 // wavefront, before it is stored:
 //  * an infinity, a NaN or a value that rounds to a bf16 infinity leaves a NaN or an infinity in its row or column, since
 //    the second piece is then inf - inf or an infinity of the other sign;
-//  * an operand below 2^-100 other than zero has pieces among the subnormal numbers and may lose up to 2^-126.  Where there is one,
-//    results below 2^-30 are computed again, and all of them if the other side has an operand of 2^64 or more.  What stands is then
-//    at least 2^-30 and has lost less than 2^-62 a term.
-// Apart from that, the order of the sums depends on k only: a row computed alone equals the same row computed as part of a table,
-// whichever of the instances below computes it.
+//  * an operand below 2^-100 other than zero has pieces among the subnormal numbers and may lose up to 2^-126.  A result whose row or
+//    column holds one is computed again if it is below 2^-30, or if its column or row holds an operand of 2^64 or more.  What
+//    stands is then at least 2^-30 and has lost less than 2^-62 a term.
+// Which results these are depends on their own row and column only, and the order of the sums on k only: a row computed alone equals
+// the same row computed as part of a table, whichever of the instances below computes it.
 //
 // A wavefront owns 32 TM rows and all 32 TN columns of the tile.  Its rows of A go from memory straight into operand layout
 // (lane: row l % 32, eight consecutive k) and are split once, in registers; only B passes through LDS, split by the workgroup,
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   static_assert(TILED_THREADS % BN == 0 && BP * (TILED_THREADS / BN) == BK, "B's tile must be dealt out evenly");
   constexpr int PLANE = BN * 2;                                // 16-byte pieces of a part: [column / 32][half of k][column % 32]
   __shared__ __align__(16) v4u smem[2][3 * PLANE];
-  __shared__ int range_b[4];
+  __shared__ int range_b[TILED_THREADS], tiny_b[4];            // of a thread's part of its column, of a wavefront
   const float* __restrict__ A = static_cast<const float*>(g.A);
   const float* __restrict__ B = static_cast<const float*>(g.B);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
@@ -379,8 +379,10 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   for (int i = 0; i < TM; ++i) row_a[i] = A + min(m0 + 32 * i + (lane & 31), g.M - 1) * g.lda;
   const int bk = tid / BN * BP, bc = tid % BN;
   const uint32_t col_b = min(n0 + bc, g.N - 1);
-  uint32_t least_a = 0xffffffffu, least_b = 0xffffffffu;
-  float most_a = 0.f, most_b = 0.f;
+  uint32_t least_a[TM], least_b = 0xffffffffu;
+  float most_a[TM], most_b = 0.f;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) { least_a[i] = 0xffffffffu; most_a[i] = 0.f; }
 
   auto fetch = [&](int k0) {
 #pragma unroll
@@ -421,17 +423,15 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
     }
   };
   constexpr int TINY = 1, VAST = 2;          // an operand below 2^-100 and not zero (27 << 24: 2^-100 shifted left); one of 2^64 or more, or a NaN
-  auto range_of = [](uint32_t least, float most) {
-    return (__any(least < (27u << 24) - 1u) ? TINY : 0) | (__any(!(most < 0x1p64f)) ? VAST : 0);
-  };
+  auto range_of = [](uint32_t least, float most) { return (least < (27u << 24) - 1u ? TINY : 0) | (most < 0x1p64f ? 0 : VAST); };
   v4u a[TM][3];
   auto split_a = [&]() {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       unsigned int pa[3][4];
       split_pairs<8>(ra[i], pa);
-      least_a = least_of<8>(ra[i], least_a);
-      most_a = most_of<8>(ra[i], most_a);
+      least_a[i] = least_of<8>(ra[i], least_a[i]);
+      most_a[i] = most_of<8>(ra[i], most_a[i]);
 #pragma unroll
       for (int p = 0; p < 3; ++p) a[i][p] = v4u{pa[p][0], pa[p][1], pa[p][2], pa[p][3]};
     }
@@ -479,15 +479,19 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   multiply(st & 1);
   clear_b();
   stage_b(~st & 1);
-  const int range_here = range_of(least_b, most_b);
-  if (lane == 0) range_b[wave] = range_here;
+  range_b[tid] = range_of(least_b, most_b);
+  tiny_b[wave] = __any((range_b[tid] & TINY) != 0);
   clear_a();
   split_a();
   __syncthreads();
   multiply(~st & 1);
-  const int of_a = range_of(least_a, most_a), of_b = range_b[0] | range_b[1] | range_b[2] | range_b[3];
-  const bool tiny = ((of_a | of_b) & TINY) != 0;
-  const bool lost = ((of_a & TINY) && (of_b & VAST)) || ((of_b & TINY) && (of_a & VAST));
+  int range_a[TM], tiny_a = 0;                 // of a lane's part of its rows
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    range_a[i] = range_of(least_a[i], most_a[i]);
+    tiny_a |= range_a[i] & TINY;
+  }
+  const bool tiny = __any(tiny_a) || (tiny_b[0] | tiny_b[1] | tiny_b[2] | tiny_b[3]) != 0;
 
   // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
   // Zero times an infinity or a NaN is a NaN: one instruction an element where nothing is to be computed again.
@@ -526,16 +530,33 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
     return;
   }
 
-  auto outside = [&](float x) {
-    const uint32_t u = __float_as_uint(x) & 0x7fffffffu;
-    return u >= 0x7f800000u || lost || (tiny && u < (97u << 23));      // (97 << 23: 2^-30)
+  // What a lane knows of its row (half of the k) as a bit a row, shifted to the first row of this half of the lanes.
+  auto rows_with = [&](bool mine) {
+    const uint64_t both = __ballot(mine);
+    return static_cast<uint32_t>(both | both >> 32) >> 4 * half;
   };
+  uint32_t tiny_rows[TM], vast_rows[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    tiny_rows[i] = rows_with((range_a[i] & TINY) != 0);
+    vast_rows[i] = rows_with((range_a[i] & VAST) != 0);
+  }
   uint32_t redo[(TM * TN + 1) / 2], again = 0;        // a bit an element
 #pragma unroll
   for (int t = 0; t < TM * TN; ++t) {
+    const int i = t / TN, j = t % TN;
+    int of_b = 0;
+#pragma unroll
+    for (int q = 0; q < TILED_THREADS; q += BN) of_b |= range_b[q + j * 32 + (lane & 31)];
     if (t % 2 == 0) redo[t / 2] = 0;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) redo[t / 2] |= outside(acc[t / TN][t % TN][v]) ? 1u << (t % 2 * 16 + v) : 0u;
+    for (int v = 0; v < 16; ++v) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      const uint32_t u = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
+      const bool small = u < (97u << 23);             // (2^-30)
+      const bool lost = ((tiny_rows[i] >> r & 1u) && (small || (of_b & VAST))) || ((of_b & TINY) && (small || (vast_rows[i] >> r & 1u)));
+      redo[t / 2] |= u >= 0x7f800000u || lost ? 1u << (t % 2 * 16 + v) : 0u;
+    }
     again |= redo[t / 2];
   }
   // Rows past the end, or elements to compute again: those that stand are stored first.  Then the others are computed with fp32

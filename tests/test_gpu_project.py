@@ -126,3 +126,27 @@ def test_split_products_of_a_small_and_a_large_operand_beside_others():
     W[0], W[1] = 2.0 ** 120, 1
     assert bool((_project(D, W) == 2.0 ** -20 + 2.0 ** -25).all())
     assert bool((_project(W.t().contiguous(), D.t().contiguous()) == 2.0 ** -20 + 2.0 ** -25).all())
+
+
+@pytest.mark.parametrize("rows,outputs", [(385, 130), (45_003, 50), (20_011, 1_030), (65_613, 1_025)])
+def test_split_products_of_small_numbers_beside_others(rows, outputs):
+    """Operands below 2^-100 in single rows and columns and results below 2^-30: no other row or column changes, and a row computed
+    alone is the row of the table."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    D = torch.randn(rows, 40, generator=gen, device="cuda") * 1e-10
+    W = torch.randn(40, outputs, generator=gen, device="cuda") * 1e-3
+    plain = _project(D, W)
+    at, col = [0, 33, 130, rows - 2], [0, 37, outputs - 1]
+    D[at, 3], W[5, col] = 1e-40, -1e-38
+    D[200, 7], W[9, 20] = 1e25, 1e22                         # (and large ones: every result of such a pair)
+    got = _project(D, W)
+    same_row, same_col = torch.ones(rows, dtype=torch.bool, device="cuda"), torch.ones(outputs, dtype=torch.bool, device="cuda")
+    same_row[at + [200]], same_col[col + [20]] = False, False
+    assert torch.equal(got[same_row][:, same_col], plain[same_row][:, same_col])
+    assert _within_bound(got, D, W)
+    for first in (0, 1, 33, 129, 199, rows - 3):
+        assert torch.equal(_project(D[first:first + 2].contiguous(), W), got[first:first + 2])
+    assert torch.equal(_project(D[30:300].contiguous(), W), got[30:300])
+    few = [c for c in (0, 20, 36, 37, outputs - 1) for _ in range(5)]
+    assert torch.equal(_project(D, W[:, few].contiguous()), got[:, few])
