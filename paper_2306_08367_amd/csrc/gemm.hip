@@ -284,13 +284,19 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 
 // ------------------------------------------------------------------ split --------------
 
-// fp32, more than 16 k and 16 columns.  An fp32 number is exactly the sum of three bf16 numbers (24 bits in three pieces of 8, each
-// rounded to nearest, so a piece is at most 2^-9 of the one before it).  Of the nine products of two such sums the six largest go
-// through the bf16 matrix instruction, whose products are exact and whose sums are fp32; the other three are below 2^-25 of the
-// product.  Six bf16 instructions take 3/8 of the time of the fp32 instructions for the same tile.  The accumulator is rounded six times
-// per 16 k instead of eight times, so the result is a little closer to the exact one than with fp32 instructions: normal values, relative
-// error in the 2-norm for k = 32, 64, 128, 320, 683, 1,024: 1.0e-7, 1.4e-7, 2.0e-7, 3.2e-7, 4.7e-7, 5.7e-7 with those, 6.9e-8, 1.1e-7,
-// 1.6e-7, 2.7e-7, 4.0e-7, 4.9e-7 so (the small products first: they then meet an accumulator of zero in the first step).
+// fp32, more than 16 k and 16 columns.  An fp32 number is exactly the sum of three bf16 numbers: each piece is rounded to nearest at 8 bits,
+// so the second one is at most 2^-8 of the number and the third one at most 2^-17.  Of the nine products of two such sums the six
+// largest go through the bf16 matrix instruction, whose products are exact and whose sums are fp32.  The other three are at most 2^-24 of the
+// product (both operands next to 1.0039) and 2^-28 of it on average over all mantissas, of either sign.  Six bf16 instructions take 3/8 of the
+// time of the fp32 instructions for the same tile.
+// The products of the two first pieces and the five small ones have sums of their own, added at the end: a sum is rounded with every
+// instruction that adds to it, so the large one is rounded once per 16 k, and the rounding of the small ones does not show.  (All six in
+// one sum: 280 us instead of 292 at 16,555 x 683 -> 2,048 in three problems, 2,090 instead of 2,230 at 200,000 x 1,024 -> 1,024, but
+// farther off than fp32 instructions where operands are zero, which round nothing then: in the table, and a little biased.)
+// Relative error in the 2-norm against float64 with fp32 instructions / one sum / so, for k = 64 and 683: normal values 1.4e-7, 1.1e-7,
+// 5.0e-8 and 4.7e-7, 4.0e-7, 1.5e-7; values in [0, 1] 1.2e-7, 8.5e-8, 4.9e-8 and 4.0e-7, 2.9e-7, 1.5e-7; normal values cut off at zero
+// 1.0e-7, 1.05e-7, 4.2e-8 and 3.3e-7, 3.8e-7, 1.2e-7; one operand of 20 not zero 4.1e-8, 6.5e-8, 2.7e-8 and 1.1e-7, 2.1e-7, 4.2e-8; a single
+// product of two 24-bit numbers, where the products left out do show, 2.53e-8, 3.3e-8, 2.58e-8.
 // What the pieces cannot hold is computed again with fp32 instructions, element by element of the result and wavefront by
 // wavefront, before it is stored:
 //  * an infinity, a NaN or a value that rounds to a bf16 infinity leaves a NaN or an infinity in its row or column, since
@@ -301,12 +307,14 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 // Which results these are depends on their own row and column only, and the order of the sums on k only: a row computed alone equals
 // the same row computed as part of a table, whichever of the instances below computes it.
 //
-// A wavefront owns 32 TM rows and all 32 TN columns of the tile.  Its rows of A go from memory straight into operand layout
+// A wavefront owns 32 rows and all 32 TN columns of the tile.  Its rows of A go from memory straight into operand layout
 // (lane: row l % 32, eight consecutive k) and are split once, in registers; only B passes through LDS, split by the workgroup,
-// in two buffers with one barrier per 16 k.  (Both operands through LDS, 64 x 64 a wavefront: 278 instead of 271 us
-// at 16,555 x 683 -> 2,048 in three problems, 2,200 instead of 2,000 at 200,000 x 1,024 -> 1,024; with fp32 instructions, one word of
-// either operand a lane from LDS, 412 and 3,250.)  The latter is 1.26 PFLOP/s in bf16 operations, the rate that a bf16 product of
-// 8,192^3 from the vendor's library reaches on this card; short tables are bound by the chain of a step: load, split, LDS, products.
+// in two buffers with one barrier per 16 k.  With 128 columns the two sums leave room for two wavefronts a SIMD, in two workgroups or in
+// one of eight wavefronts, which splits B half as often.  (Both operands through LDS, 64 x 64 a wavefront, in one sum: 278 instead of 271 us
+// for the former shape, 2,200 instead of 2,000 for the latter; 64 rows a wavefront and 64 columns in two sums: 309 and 2,410, 64 rows
+// and 128 columns, one wavefront a SIMD: 350 and 2,520; with fp32 instructions, one word of either operand a lane from LDS, 412 and 3,250.)
+// Large tables are bound by the matrix instructions and the splitting beside them: 1.1 PFLOP/s in bf16 operations, 1.26 in a bf16
+// product of 8,192^3 from the vendor's library; short tables by the chain of a step: load, split, LDS, products.
 
 // Floats as sums of three bf16 numbers each, packed in pairs.
 template <int N>
@@ -339,8 +347,8 @@ __device__ __forceinline__ float most_of(const float (&x)[N], float most) {
   return most;
 }
 
-template <int TM, int TN>
-__global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split_kernel(GemmBatch batch) {
+template <int TN, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, TN > 2 ? 2 : 4) void gemm_split_kernel(GemmBatch batch) {
   int problem = 0;
   while (problem + 1 < batch.count && static_cast<int32_t>(blockIdx.x) >= batch.first_tile[problem + 1]) ++problem;
   const GemmArgs g = batch.g[problem];
@@ -350,49 +358,38 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   const int32_t tiles = batch.first_tile[problem + 1] - batch.first_tile[problem];
   const int32_t tile = at % 8 * (tiles / 8) + min(at % 8, tiles % 8) + at / 8;
   constexpr int BK = 16, BN = 32 * TN;
-  constexpr int BP = BN * BK / TILED_THREADS;                  // consecutive k of B in a thread
-  static_assert(TILED_THREADS % BN == 0 && BP * (TILED_THREADS / BN) == BK, "B's tile must be dealt out evenly");
+  constexpr int THREADS = 64 * WAVES, BP = BN * BK / THREADS;  // consecutive k of B in a thread
+  static_assert(THREADS % BN == 0 && BP * (THREADS / BN) == BK, "B's tile must be dealt out evenly");
   constexpr int PLANE = BN * 2;                                // 16-byte pieces of a part: [column / 32][half of k][column % 32]
   __shared__ __align__(16) v4u smem[2][3 * PLANE];
-  __shared__ int range_b[TILED_THREADS], tiny_b[4];            // of a thread's part of its column, of a wavefront
+  __shared__ int range_b[THREADS], tiny_b[WAVES];            // of a thread's part of its column, of a wavefront
   const float* __restrict__ A = static_cast<const float*>(g.A);
   const float* __restrict__ B = static_cast<const float*>(g.B);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
-  const int64_t m0 = (static_cast<int64_t>(tile / g.tiles_n) * 4 + wave) * 32 * TM;
+  const int64_t m0 = (static_cast<int64_t>(tile / g.tiles_n) * WAVES + wave) * 32;
   const int n0 = tile % g.tiles_n * BN;
 
-  v16f acc[TM][TN];
-  auto clear = [&]() {
+  v16f acc[TN], low[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  };
-  clear();
+    for (int v = 0; v < 16; ++v) { acc[j][v] = 0.f; low[j][v] = 0.f; }
 
   // Rows past the end repeat the last row and columns past the end the last column; both are never stored.
-  float ra[TM][8], rb[BP];
-  const float* row_a[TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) row_a[i] = A + min(m0 + 32 * i + (lane & 31), g.M - 1) * g.lda;
+  float ra[8], rb[BP];
+  const float* row_a = A + min(m0 + (lane & 31), g.M - 1) * g.lda;
   const int bk = tid / BN * BP, bc = tid % BN;
   const uint32_t col_b = min(n0 + bc, g.N - 1);
-  uint32_t least_a[TM], least_b = 0xffffffffu;
-  float most_a[TM], most_b = 0.f;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) { least_a[i] = 0xffffffffu; most_a[i] = 0.f; }
+  uint32_t least_a = 0xffffffffu, least_b = 0xffffffffu;
+  float most_a = 0.f, most_b = 0.f;
 
   auto fetch = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int h = 0; h < 8; h += 4) {
-        const Words4 t = *reinterpret_cast<const Words4*>(row_a[i] + k0 + 8 * half + h);
-        ra[i][h] = __uint_as_float(t.x); ra[i][h + 1] = __uint_as_float(t.y);
-        ra[i][h + 2] = __uint_as_float(t.z); ra[i][h + 3] = __uint_as_float(t.w);
-      }
+    for (int h = 0; h < 8; h += 4) {
+      const Words4 t = *reinterpret_cast<const Words4*>(row_a + k0 + 8 * half + h);
+      ra[h] = __uint_as_float(t.x); ra[h + 1] = __uint_as_float(t.y);
+      ra[h + 2] = __uint_as_float(t.z); ra[h + 3] = __uint_as_float(t.w);
+    }
     const float* base = B + static_cast<int64_t>(k0 + (BN >= 64 ? __builtin_amdgcn_readfirstlane(bk) : bk)) * g.ldb;
 #pragma unroll
     for (int q = 0; q < BP; ++q) rb[q] = (base + q * g.ldb)[col_b];
@@ -401,9 +398,7 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   const int steps = (g.Kd + BK - 1) / BK, last_k = g.Kd - BK, had = steps * BK - g.Kd;
   auto clear_a = [&]() {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) ra[i][q] = 8 * half + q >= had ? ra[i][q] : 0.f;
+    for (int q = 0; q < 8; ++q) ra[q] = 8 * half + q >= had ? ra[q] : 0.f;
   };
   auto clear_b = [&]() {
 #pragma unroll
@@ -424,39 +419,35 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   };
   constexpr int TINY = 1, VAST = 2;          // an operand below 2^-100 and not zero (27 << 24: 2^-100 shifted left); one of 2^64 or more, or a NaN
   auto range_of = [](uint32_t least, float most) { return (least < (27u << 24) - 1u ? TINY : 0) | (most < 0x1p64f ? 0 : VAST); };
-  v4u a[TM][3];
+  v4u a[3];
   auto split_a = [&]() {
+    unsigned int pa[3][4];
+    split_pairs<8>(ra, pa);
+    least_a = least_of<8>(ra, least_a);
+    most_a = most_of<8>(ra, most_a);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      unsigned int pa[3][4];
-      split_pairs<8>(ra[i], pa);
-      least_a[i] = least_of<8>(ra[i], least_a[i]);
-      most_a[i] = most_of<8>(ra[i], most_a[i]);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) a[i][p] = v4u{pa[p][0], pa[p][1], pa[p][2], pa[p][3]};
-    }
+    for (int p = 0; p < 3; ++p) a[p] = v4u{pa[p][0], pa[p][1], pa[p][2], pa[p][3]};
   };
   auto multiply = [&](int buf) {
     const v4u* from = &smem[buf][half * 32 + lane % 32];
-    // All reads of B's operands ahead of the products as far as registers go, in the order in which they are needed.
-    constexpr int JB = TM == 1 ? TN : 1;
+    // Two column tiles at a time: their sums are independent of each other, and no more of B's operands fit beside the sums of four.
+    constexpr int JB = TN > 2 ? 2 : 1;
 #pragma unroll
     for (int j0 = 0; j0 < TN; j0 += JB) {
-      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+      constexpr int PA[6] = {2, 0, 1, 0, 1, 0}, PB[6] = {0, 2, 1, 0, 0, 1}, READ[3] = {0, 2, 1};
       v4u b[JB][3];
 #pragma unroll
       for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int j = 0; j < JB; ++j) b[j][PB[t]] = from[PB[t] * PLANE + (j0 + j) * 64];
+        for (int j = 0; j < JB; ++j) b[j][READ[t]] = from[READ[t] * PLANE + (j0 + j) * 64];
       if constexpr (TN == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int j = 0; j < JB; ++j)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-            acc[i][j0 + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][PA[t]]),
-                                                                     __builtin_bit_cast(bf16x8, b[j][PB[t]]), acc[i][j0 + j], 0, 0, 0);
+        for (int j = 0; j < JB; ++j) {
+          v16f& sum = PA[t] + PB[t] == 0 ? acc[j0 + j] : low[j0 + j];
+          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[PA[t]]), __builtin_bit_cast(bf16x8, b[j][PB[t]]), sum, 0, 0, 0);
+        }
     }
   };
 
@@ -485,23 +476,21 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
   split_a();
   __syncthreads();
   multiply(~st & 1);
-  int range_a[TM], tiny_a = 0;                 // of a lane's part of its rows
+  const int range_a = range_of(least_a, most_a);               // of a lane's part of its row
+  bool tiny = __any((range_a & TINY) != 0);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    range_a[i] = range_of(least_a[i], most_a[i]);
-    tiny_a |= range_a[i] & TINY;
-  }
-  const bool tiny = __any(tiny_a) || (tiny_b[0] | tiny_b[1] | tiny_b[2] | tiny_b[3]) != 0;
+  for (int w = 0; w < WAVES; ++w) tiny = tiny || tiny_b[w] != 0;
 
   // 32x32 accumulator: register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
   // Zero times an infinity or a NaN is a NaN: one instruction an element where nothing is to be computed again.
   float zeros[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) zeros[v % 4] = __builtin_fmaf(acc[i][j][v], 0.f, zeros[v % 4]);
+    for (int v = 0; v < 16; ++v) {
+      acc[j][v] += low[j][v];
+      zeros[v % 4] = __builtin_fmaf(acc[j][v], 0.f, zeros[v % 4]);
+    }
   const bool stands = !tiny && !__any(zeros[0] + zeros[1] + zeros[2] + zeros[3] != 0.f);
 
   // The bias goes in before the row tests: used inside them it would be waited for again in each, and such a wait is for every
@@ -516,16 +505,14 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
     x += bv[j];
     return g.relu ? fmaxf(x, 0.f) : x;
   };
-  if (stands && m0 + 32 * TM <= g.M) {
+  if (stands && m0 + 32 <= g.M) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int col = n0 + j * 32 + (lane & 31);
       if (col >= g.N) continue;
       float* p = C + row0 * g.ldc + col;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) p[(i * 32 + 8 * (v >> 2) + (v & 3)) * g.ldc] = value(acc[i][j][v], j);
+      for (int v = 0; v < 16; ++v) p[(8 * (v >> 2) + (v & 3)) * g.ldc] = value(acc[j][v], j);
     }
     return;
   }
@@ -535,70 +522,51 @@ __global__ __launch_bounds__(TILED_THREADS, TM * TN > 4 ? 2 : 3) void gemm_split
     const uint64_t both = __ballot(mine);
     return static_cast<uint32_t>(both | both >> 32) >> 4 * half;
   };
-  uint32_t tiny_rows[TM], vast_rows[TM];
+  const uint32_t tiny_rows = rows_with((range_a & TINY) != 0), vast_rows = rows_with((range_a & VAST) != 0);
+  uint32_t redo[TN], again = 0;        // a bit an element
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    tiny_rows[i] = rows_with((range_a[i] & TINY) != 0);
-    vast_rows[i] = rows_with((range_a[i] & VAST) != 0);
-  }
-  uint32_t redo[(TM * TN + 1) / 2], again = 0;        // a bit an element
-#pragma unroll
-  for (int t = 0; t < TM * TN; ++t) {
-    const int i = t / TN, j = t % TN;
+  for (int j = 0; j < TN; ++j) {
     int of_b = 0;
 #pragma unroll
-    for (int q = 0; q < TILED_THREADS; q += BN) of_b |= range_b[q + j * 32 + (lane & 31)];
-    if (t % 2 == 0) redo[t / 2] = 0;
+    for (int q = 0; q < THREADS; q += BN) of_b |= range_b[q + j * 32 + (lane & 31)];
+    redo[j] = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int r = 8 * (v >> 2) + (v & 3);
-      const uint32_t u = __float_as_uint(acc[i][j][v]) & 0x7fffffffu;
+      const uint32_t u = __float_as_uint(acc[j][v]) & 0x7fffffffu;
       const bool small = u < (97u << 23);             // (2^-30)
-      const bool lost = ((tiny_rows[i] >> r & 1u) && (small || (of_b & VAST))) || ((of_b & TINY) && (small || (vast_rows[i] >> r & 1u)));
-      redo[t / 2] |= u >= 0x7f800000u || lost ? 1u << (t % 2 * 16 + v) : 0u;
+      const bool lost = ((tiny_rows >> r & 1u) && (small || (of_b & VAST))) || ((of_b & TINY) && (small || (vast_rows >> r & 1u)));
+      redo[j] |= u >= 0x7f800000u || lost ? 1u << v : 0u;
     }
-    again |= redo[t / 2];
+    again |= redo[j];
   }
   // Rows past the end, or elements to compute again: those that stand are stored first.  Then the others are computed with fp32
   // instructions, a column tile at a time (lane: row or column l % 32, four consecutive k of eight, straight from memory).
-  auto store = [&](const v16f (&x)[TM], int j, bool redone) {
+  auto store = [&](const v16f& x, int j, bool redone) {
     const int col = n0 + j * 32 + (lane & 31);
     float* p = C + row0 * g.ldc + col;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = i * 32 + 8 * (v >> 2) + (v & 3), t = i * TN + j;
-        if ((redo[t / 2] >> (t % 2 * 16 + v) & 1u) == redone && row0 + r < g.M && col < g.N) p[r * g.ldc] = value(x[i][v], j);
-      }
+    for (int v = 0; v < 16; ++v) {
+      const int r = 8 * (v >> 2) + (v & 3);
+      if ((redo[j] >> v & 1u) == redone && row0 + r < g.M && col < g.N) p[r * g.ldc] = value(x[v], j);
+    }
   };
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    v16f x[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) x[i] = acc[i][j];
-    store(x, j, false);
-  }
+  for (int j = 0; j < TN; ++j) store(acc[j], j, false);
   if (!__any(again != 0)) return;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    v16f x[TM];
+    v16f x;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) x[i][v] = 0.f;
+    for (int v = 0; v < 16; ++v) x[v] = 0.f;
     const float* col = B + min(n0 + j * 32 + (lane & 31), g.N - 1);
 #pragma unroll 1
     for (int k0 = 0; k0 < g.Kd; k0 += 8) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int k = k0 + 4 * half + q, kc = min(k, g.Kd - 1);
-        const float y = col[static_cast<int64_t>(kc) * g.ldb];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const float z = row_a[i][kc];
-          x[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(k < g.Kd ? z : 0.f, k < g.Kd ? y : 0.f, x[i], 0, 0, 0);
-        }
+        const float y = col[static_cast<int64_t>(kc) * g.ldb], z = row_a[kc];
+        x = __builtin_amdgcn_mfma_f32_32x32x2f32(k < g.Kd ? z : 0.f, k < g.Kd ? y : 0.f, x, 0, 0, 0);
       }
     }
     store(x, j, true);
@@ -813,11 +781,13 @@ int launch_tiled_batch(GemmBatch& b, hipStream_t s) {
 
 // All problems of the batch share N.  The narrowest tiles keep the most loads in flight and the shortest chain of a step, the widest
 // read A and split it the fewest times: 32 columns up to two and a half tiles of 128 x 32 a compute unit, 128 columns from four
-// tiles of 128 x 128 on, and the large instance from eight tiles of 256 x 128 on (four rounds of two).  Time in us with tiles of 32 / 64 / 128
-// columns for k = 64 and 320: 2,500 rows -> 200 columns 7.8 / 7.4 / 10.2 and 9.6 / 15.1 / 22.4; 10,000 -> 200 (553 narrow tiles) 7.5 /
-// 9.1 / 12.1 and 19.9 / 20.1 / 24.4; 10,000 -> 500 (1,264) 12.0 / 12.0 / 15.4 and 34.5 / 29.3 / 34.2; 100,000 -> 128 (3,128) 21.8 / 21.2 / 23.4
-// and 85.5 / 61.6 / 63.0; 16,555 x 683 -> 2,048 (8,320) 294 with 64 columns, 271 with 128, 277 with the large instance;
-// 200,000 x 1,024 -> 1,024 2,440, 2,230 and 2,000.
+// tiles of 128 x 128 on, and those in workgroups of eight wavefronts from eight tiles of 256 x 128 on (eight rounds) unless k is short, when
+// filling and emptying a tile is most of it.  Time in us with 32 / 64 / 128 columns / eight wavefronts for k = 32, 128 and 512:
+// 16,384 rows -> 128 columns (512 narrow tiles) 5.2 / 5.4 / 6.7 / 7.7, 8.7 / 9.5 / 11 / 14 and 25 / 28 / 32 / 40; 41,600 -> 128 (1,300; 325 wide ones)
+// 9.3 / 8.3 / 9.4 / 14, 20 / 16 / 17 / 20 and 59 / 42 / 44 / 45; 28,000 -> 512 (3,500; 876) 17 / 17 / 21 / 22, 41 / 32 / 36 / 37 and 135 / 98 / 97 / 96;
+// 40,000 -> 512 (1,252 wide) 23 / 22 / 25 / 29, 57 / 46 / 45 / 51 and 188 / 136 / 130 / 136; 96,000 -> 512 (3,000; 1,500 large ones) 50 / 43 / 43 / 47,
+// 130 / 100 / 95 / 93 and 459 / 336 / 311 / 301; 160,000 -> 512 (2,500 large) 114 / 90 / 90 / 89, 235 / 185 / 180 / 164 and 764 / 556 / 519 / 497; 600,000 x 33 ->
+// 128 (2,344) 128 / 98 / 91 / 102; 16,555 x 683 -> 2,048 (1,040) 419 / 316 / 300 / 307; 200,000 x 1,024 -> 1,024 (6,256) 3,750 / 2,610 / 2,380 / 2,310.
 int launch_split_batch(GemmBatch& b, hipStream_t s) {
   const int N = b.g[0].N;
   const int64_t cus = num_cus();
@@ -826,17 +796,15 @@ int launch_split_batch(GemmBatch& b, hipStream_t s) {
   if (narrow == 0) return LQ_OK;
   if (int rc = deal_tiles(b, 256, 128, &large)) return rc;
   if (int rc = deal_tiles(b, 128, 128, &wide)) return rc;
-  const dim3 block(TILED_THREADS);
-  auto deal = [&](int bm, int bn) { return deal_tiles(b, bm, bn, &blocks); };
-#define LQ_SPLIT(TM_, TN_)                                                                                                    \
+#define LQ_SPLIT(TN_, WAVES_)                                                                                                 \
   do {                                                                                                                        \
-    if (int rc = deal(128 * TM_, 32 * TN_)) return rc;                                                                        \
-    hipLaunchKernelGGL((gemm_split_kernel<TM_, TN_>), dim3(static_cast<unsigned>(blocks)), block, 0, s, b);                   \
+    if (int rc = deal_tiles(b, 32 * WAVES_, 32 * TN_, &blocks)) return rc;                                                    \
+    hipLaunchKernelGGL((gemm_split_kernel<TN_, WAVES_>), dim3(static_cast<unsigned>(blocks)), dim3(64 * WAVES_), 0, s, b);    \
   } while (0)
-  if (N <= 32 || 2 * narrow <= 5 * cus) LQ_SPLIT(1, 1);
-  else if (N <= 64 || wide < 4 * cus) LQ_SPLIT(1, 2);
-  else if (large < 8 * cus) LQ_SPLIT(1, 4);
-  else LQ_SPLIT(2, 4);
+  if (N <= 32 || 2 * narrow <= 5 * cus) LQ_SPLIT(1, 4);
+  else if (N <= 64 || wide < 4 * cus) LQ_SPLIT(2, 4);
+  else if (large < 8 * cus || b.g[0].Kd < 64) LQ_SPLIT(4, 4);
+  else LQ_SPLIT(4, 8);
 #undef LQ_SPLIT
   LQ_LAUNCH_CHECK("gemm_split_kernel");
   return LQ_OK;
