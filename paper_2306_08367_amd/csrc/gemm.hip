@@ -291,21 +291,24 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 // time of the fp32 instructions for the same tile.
 // The products of the two first pieces and the five small ones have sums of their own, added at the end: a sum is rounded with every
 // instruction that adds to it, so the large one is rounded once per 16 k, and the rounding of the small ones does not show.  (All six in
-// one sum: 280 us instead of 292 at 16,555 x 683 -> 2,048 in three problems, 2,090 instead of 2,230 at 200,000 x 1,024 -> 1,024, but
+// one sum: 277 us instead of 289 at 16,555 x 683 -> 2,048 in three problems, 2,110 instead of 2,220 at 200,000 x 1,024 -> 1,024, but
 // farther off than fp32 instructions where operands are zero, which round nothing then: in the table, and a little biased.)
 // Relative error in the 2-norm against float64 with fp32 instructions / one sum / so, for k = 64 and 683: normal values 1.4e-7, 1.1e-7,
 // 5.0e-8 and 4.7e-7, 4.0e-7, 1.5e-7; values in [0, 1] 1.2e-7, 8.5e-8, 4.9e-8 and 4.0e-7, 2.9e-7, 1.5e-7; normal values cut off at zero
 // 1.0e-7, 1.05e-7, 4.2e-8 and 3.3e-7, 3.8e-7, 1.2e-7; one operand of 20 not zero 4.1e-8, 6.5e-8, 2.7e-8 and 1.1e-7, 2.1e-7, 4.2e-8; a single
 // product of two 24-bit numbers, where the products left out do show, 2.53e-8, 3.3e-8, 2.58e-8.
-// What the pieces cannot hold is computed again with fp32 instructions, element by element of the result and wavefront by
-// wavefront, before it is stored:
-//  * an infinity, a NaN or a value that rounds to a bf16 infinity leaves a NaN or an infinity in its row or column, since
-//    the second piece is then inf - inf or an infinity of the other sign;
+// What the pieces cannot hold is computed again with fp32 instructions before it is stored:
+//  * an infinity or a value that rounds to a bf16 infinity leaves a NaN in its row or column, since the second piece is then inf - inf or an
+//    infinity of the other sign (a NaN leaves one too, which stands);
 //  * an operand below 2^-100 other than zero has pieces among the subnormal numbers and may lose up to 2^-126.  A result whose row or
 //    column holds one is computed again if it is below 2^-30, or if its column or row holds an operand of 2^64 or more.  What
-//    stands is then at least 2^-30 and has lost less than 2^-62 a term.
+//    stands is then at least 2^-30 and has lost less than 2^-62 a term.  (Not where the row or the column is all zeros.)
 // Which results these are depends on their own row and column only, and the order of the sums on k only: a row computed alone equals
 // the same row computed as part of a table, whichever of the instances below computes it.
+// A wavefront with such an operand, or with a NaN, reads its rows once more, and its rows and the columns of a tile of 32 again for
+// a tile with results to compute again.  16,555 x 683 -> 2,048, 289 us without any and 411 with fp32 instructions: a NaN in one row 290, in a row
+// of a hundred 318, in all rows 349, in one column 288; operands below 2^-100 in one row 292, in one of a hundred 323, in all 363; an infinity in one
+// row 383, in one of a hundred 710, in all 1,003, in one column 342.  10,000 x 32 -> 64, 4.0 us: 7.2 to 9.6 in rows, 11.1 with a column of infinities.
 //
 // A wavefront owns 32 rows and all 32 TN columns of the tile.  Its rows of A go from memory straight into operand layout
 // (lane: row l % 32, eight consecutive k) and are split once, in registers; only B passes through LDS, split by the workgroup,
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(64 * WAVES, TN > 2 ? 2 : 4) void gemm_split_kernel(
   static_assert(THREADS % BN == 0 && BP * (THREADS / BN) == BK, "B's tile must be dealt out evenly");
   constexpr int PLANE = BN * 2;                                // 16-byte pieces of a part: [column / 32][half of k][column % 32]
   __shared__ __align__(16) v4u smem[2][3 * PLANE];
-  __shared__ int range_b[THREADS], tiny_b[WAVES];            // of a thread's part of its column, of a wavefront
+  __shared__ int range_b[THREADS], tiny_b[WAVES];              // of a thread's part of its column, of a wavefront
   const float* __restrict__ A = static_cast<const float*>(g.A);
   const float* __restrict__ B = static_cast<const float*>(g.B);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
@@ -381,15 +384,18 @@ __global__ __launch_bounds__(64 * WAVES, TN > 2 ? 2 : 4) void gemm_split_kernel(
   const int bk = tid / BN * BP, bc = tid % BN;
   const uint32_t col_b = min(n0 + bc, g.N - 1);
   uint32_t least_a = 0xffffffffu, least_b = 0xffffffffu;
-  float most_a = 0.f, most_b = 0.f;
+  float most_b = 0.f;
 
-  auto fetch = [&](int k0) {
+  auto fetch_a = [&](int k0) {
 #pragma unroll
     for (int h = 0; h < 8; h += 4) {
       const Words4 t = *reinterpret_cast<const Words4*>(row_a + k0 + 8 * half + h);
       ra[h] = __uint_as_float(t.x); ra[h + 1] = __uint_as_float(t.y);
       ra[h + 2] = __uint_as_float(t.z); ra[h + 3] = __uint_as_float(t.w);
     }
+  };
+  auto fetch = [&](int k0) {
+    fetch_a(k0);
     const float* base = B + static_cast<int64_t>(k0 + (BN >= 64 ? __builtin_amdgcn_readfirstlane(bk) : bk)) * g.ldb;
 #pragma unroll
     for (int q = 0; q < BP; ++q) rb[q] = (base + q * g.ldb)[col_b];
@@ -417,14 +423,16 @@ __global__ __launch_bounds__(64 * WAVES, TN > 2 ? 2 : 4) void gemm_split_kernel(
       else reinterpret_cast<unsigned int*>(to)[bk / 2 % 4] = pb[p][0];
     }
   };
-  constexpr int TINY = 1, VAST = 2;          // an operand below 2^-100 and not zero (27 << 24: 2^-100 shifted left); one of 2^64 or more, or a NaN
-  auto range_of = [](uint32_t least, float most) { return (least < (27u << 24) - 1u ? TINY : 0) | (most < 0x1p64f ? 0 : VAST); };
+  auto is_tiny = [](uint32_t least) { return least < (27u << 24) - 1u; };           // (27 << 24: 2^-100 shifted left)
+  constexpr int TINY = 1, VAST = 2, NANS = 4, SOME = 8;        // an operand below 2^-100, one of 2^64 or more, a NaN, one that is not zero
+  auto range_of = [&](uint32_t least, float most) {
+    return (is_tiny(least) ? TINY : 0) | (most < 0x1p64f ? 0 : VAST) | (most != most ? NANS : 0) | (least != 0xffffffffu ? SOME : 0);
+  };
   v4u a[3];
   auto split_a = [&]() {
     unsigned int pa[3][4];
     split_pairs<8>(ra, pa);
     least_a = least_of<8>(ra, least_a);
-    most_a = most_of<8>(ra, most_a);
 #pragma unroll
     for (int p = 0; p < 3; ++p) a[p] = v4u{pa[p][0], pa[p][1], pa[p][2], pa[p][3]};
   };
@@ -470,14 +478,14 @@ __global__ __launch_bounds__(64 * WAVES, TN > 2 ? 2 : 4) void gemm_split_kernel(
   multiply(st & 1);
   clear_b();
   stage_b(~st & 1);
+  const int tiny_here = __any(is_tiny(least_b));
+  if (lane == 0) tiny_b[wave] = tiny_here;
   range_b[tid] = range_of(least_b, most_b);
-  tiny_b[wave] = __any((range_b[tid] & TINY) != 0);
   clear_a();
   split_a();
   __syncthreads();
   multiply(~st & 1);
-  const int range_a = range_of(least_a, most_a);               // of a lane's part of its row
-  bool tiny = __any((range_a & TINY) != 0);
+  bool tiny = __any(is_tiny(least_a)) != 0;                    // an operand below 2^-100, not zero, in these rows or columns
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) tiny = tiny || tiny_b[w] != 0;
 
@@ -517,59 +525,87 @@ __global__ __launch_bounds__(64 * WAVES, TN > 2 ? 2 : 4) void gemm_split_kernel(
     return;
   }
 
-  // What a lane knows of its row (half of the k) as a bit a row, shifted to the first row of this half of the lanes.
-  auto rows_with = [&](bool mine) {
-    const uint64_t both = __ballot(mine);
-    return static_cast<uint32_t>(both | both >> 32) >> 4 * half;
-  };
-  const uint32_t tiny_rows = rows_with((range_a & TINY) != 0), vast_rows = rows_with((range_a & VAST) != 0);
-  uint32_t redo[TN], again = 0;        // a bit an element
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    int of_b = 0;
-#pragma unroll
-    for (int q = 0; q < THREADS; q += BN) of_b |= range_b[q + j * 32 + (lane & 31)];
-    redo[j] = 0;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 8 * (v >> 2) + (v & 3);
-      const uint32_t u = __float_as_uint(acc[j][v]) & 0x7fffffffu;
-      const bool small = u < (97u << 23);             // (2^-30)
-      const bool lost = ((tiny_rows >> r & 1u) && (small || (of_b & VAST))) || ((of_b & TINY) && (small || (vast_rows >> r & 1u)));
-      redo[j] |= u >= 0x7f800000u || lost ? 1u << v : 0u;
-    }
-    again |= redo[j];
-  }
-  // Rows past the end, or elements to compute again: those that stand are stored first.  Then the others are computed with fp32
-  // instructions, a column tile at a time (lane: row or column l % 32, four consecutive k of eight, straight from memory).
-  auto store = [&](const v16f& x, int j, bool redone) {
+  auto store = [&](const v16f& x, int j, uint32_t which) {
     const int col = n0 + j * 32 + (lane & 31);
     float* p = C + row0 * g.ldc + col;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int r = 8 * (v >> 2) + (v & 3);
-      if ((redo[j] >> v & 1u) == redone && row0 + r < g.M && col < g.N) p[r * g.ldc] = value(x[v], j);
+      if ((which >> v & 1u) && row0 + r < g.M && col < g.N) p[r * g.ldc] = value(x[v], j);
     }
   };
+  if (stands) {
 #pragma unroll
-  for (int j = 0; j < TN; ++j) store(acc[j], j, false);
-  if (!__any(again != 0)) return;
+    for (int j = 0; j < TN; ++j) store(acc[j], j, 0xffffu);
+    return;
+  }
+
+  // Something is to be computed again, or may be.  The rows are read once more, for what they hold; a lane reads half of one.
+  // (Kept up in the loop above, their largest operands took 3 % of every product.)
+  least_a = 0xffffffffu;
+  float most_a = 0.f;
+#pragma unroll 4
+  for (int st = 0; st < steps; ++st) {
+    fetch_a(min(st * BK, last_k));
+    least_a = least_of<8>(ra, least_a);
+    most_a = most_of<8>(ra, most_a);
+  }
+  int of_a = range_of(least_a, most_a);
+  of_a |= __shfl_xor(of_a, 32);
+  auto rows_with = [&](int what) { return static_cast<uint32_t>(__ballot((of_a & what) != 0)) >> 4 * half; };      // a bit a row, from row0 on
+  const uint32_t tiny_rows = rows_with(TINY), vast_rows = rows_with(VAST), nan_rows = rows_with(NANS), some_rows = rows_with(SOME);
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
+    float zero = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) zero = __builtin_fmaf(acc[j][v], 0.f, zero);
+    uint32_t redo = 0;                                         // a bit an element
+    const int c = n0 + j * 32 + (lane & 31);
+    const float* col = B + min(c, g.N - 1);
+    auto load_b = [&](int k0, float (&x)[8]) {
+      const float* p = col + static_cast<int64_t>(k0 + 8 * half) * g.ldb;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = p[q * g.ldb];
+    };
+    if (tiny || __any(zero != 0.f)) {
+      int of_b = 0;
+#pragma unroll
+      for (int q = 0; q < THREADS; q += BN) of_b |= range_b[q + j * 32 + (lane & 31)];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int r = 8 * (v >> 2) + (v & 3);
+        const uint32_t u = __float_as_uint(acc[j][v]) & 0x7fffffffu;
+        const bool small = u < (97u << 23);                    // (2^-30)
+        const bool lost = ((tiny_rows >> r & 1u) && (small || (of_b & VAST))) || ((of_b & TINY) && (small || (vast_rows >> r & 1u)));
+        const bool again = u >= 0x7f800000u ? !((nan_rows >> r & 1u) || (of_b & NANS)) : lost && (some_rows >> r & 1u) && (of_b & SOME);
+        redo |= again && row0 + r < g.M && c < g.N ? 1u << v : 0u;
+      }
+    }
+    store(acc[j], j, ~redo);
+    if (!__any(redo != 0)) continue;
+    // With fp32 instructions, the operands straight from memory (lane: row or column l % 32, eight consecutive k), those of the next step ahead of
+    // the products.  The last step as above.
     v16f x;
 #pragma unroll
     for (int v = 0; v < 16; ++v) x[v] = 0.f;
-    const float* col = B + min(n0 + j * 32 + (lane & 31), g.N - 1);
+    float xb[8];
+    fetch_a(0);
+    load_b(0, xb);
 #pragma unroll 1
-    for (int k0 = 0; k0 < g.Kd; k0 += 8) {
+    for (int st = 0; st < steps; ++st) {
+      const int skip = st + 1 < steps ? 0 : had, next = min((st + 1) * BK, last_k);
+      float ya[8], yb[8];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = k0 + 4 * half + q, kc = min(k, g.Kd - 1);
-        const float y = col[static_cast<int64_t>(kc) * g.ldb], z = row_a[kc];
-        x = __builtin_amdgcn_mfma_f32_32x32x2f32(k < g.Kd ? z : 0.f, k < g.Kd ? y : 0.f, x, 0, 0, 0);
+      for (int q = 0; q < 8; ++q) {
+        ya[q] = 8 * half + q >= skip ? ra[q] : 0.f;
+        yb[q] = 8 * half + q >= skip ? xb[q] : 0.f;
       }
+      fetch_a(next);
+      load_b(next, xb);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x = __builtin_amdgcn_mfma_f32_32x32x2f32(ya[q], yb[q], x, 0, 0, 0);
     }
-    store(x, j, true);
+    store(x, j, redo);
   }
 }
 
@@ -783,11 +819,11 @@ int launch_tiled_batch(GemmBatch& b, hipStream_t s) {
 // read A and split it the fewest times: 32 columns up to two and a half tiles of 128 x 32 a compute unit, 128 columns from four
 // tiles of 128 x 128 on, and those in workgroups of eight wavefronts from eight tiles of 256 x 128 on (eight rounds) unless k is short, when
 // filling and emptying a tile is most of it.  Time in us with 32 / 64 / 128 columns / eight wavefronts for k = 32, 128 and 512:
-// 16,384 rows -> 128 columns (512 narrow tiles) 5.2 / 5.4 / 6.7 / 7.7, 8.7 / 9.5 / 11 / 14 and 25 / 28 / 32 / 40; 41,600 -> 128 (1,300; 325 wide ones)
-// 9.3 / 8.3 / 9.4 / 14, 20 / 16 / 17 / 20 and 59 / 42 / 44 / 45; 28,000 -> 512 (3,500; 876) 17 / 17 / 21 / 22, 41 / 32 / 36 / 37 and 135 / 98 / 97 / 96;
-// 40,000 -> 512 (1,252 wide) 23 / 22 / 25 / 29, 57 / 46 / 45 / 51 and 188 / 136 / 130 / 136; 96,000 -> 512 (3,000; 1,500 large ones) 50 / 43 / 43 / 47,
-// 130 / 100 / 95 / 93 and 459 / 336 / 311 / 301; 160,000 -> 512 (2,500 large) 114 / 90 / 90 / 89, 235 / 185 / 180 / 164 and 764 / 556 / 519 / 497; 600,000 x 33 ->
-// 128 (2,344) 128 / 98 / 91 / 102; 16,555 x 683 -> 2,048 (1,040) 419 / 316 / 300 / 307; 200,000 x 1,024 -> 1,024 (6,256) 3,750 / 2,610 / 2,380 / 2,310.
+// 16,384 rows -> 128 columns (512 narrow tiles) 5.2 / 5.4 / 6.7 / 7.6, 8.0 / 9.0 / 11 / 14 and 23 / 26 / 31 / 39; 41,600 -> 128 (1,300; 325 wide ones)
+// 9.4 / 8.5 / 9.3 / 9.3, 18 / 15 / 17 / 16 and 54 / 42 / 43 / 42; 28,000 -> 512 (3,500; 876) 18 / 15 / 16 / 17, 39 / 31 / 31 / 31 and 128 / 95 / 89 / 93;
+// 40,000 -> 512 (1,252 wide) 23 / 20 / 20 / 23, 54 / 43 / 41 / 43 and 182 / 132 / 123 / 127; 96,000 -> 512 (3,000; 1,500 large ones) 51 / 42 / 42 / 45,
+// 128 / 101 / 94 / 93 and 444 / 326 / 302 / 294; 160,000 -> 512 (2,500 large) 117 / 90 / 86 / 85, 238 / 185 / 175 / 162 and 746 / 540 / 504 / 480; 600,000 x 33 ->
+// 128 (2,344) 123 / 94 / 87 / 96; 16,555 x 683 -> 2,048 (1,040) 404 / 306 / 291 / 294; 200,000 x 1,024 -> 1,024 (6,256) 3,610 / 2,530 / 2,320 / 2,210.
 int launch_split_batch(GemmBatch& b, hipStream_t s) {
   const int N = b.g[0].N;
   const int64_t cus = num_cus();
