@@ -3,6 +3,8 @@
 // compile in parallel.)
 #ifndef LQ_GROUPBY_FAST_H_
 #define LQ_GROUPBY_FAST_H_
+#include <type_traits>
+
 #include "lq_common.h"
 
 namespace lq {
@@ -544,8 +546,8 @@ __device__ __forceinline__ void side_apply(uint32_t w, uint32_t j, int32_t strid
 }
 
 // All dimensions of N fact rows.  A dimension's reads for all rows go out together (row by row, each under a test of its own, they
-// are waited for one after the other).  Tables in memory are only
-// read by lanes with a survivor of those in LDS; its dead rows read the first entry.
+// are waited for one after the other).  Tables in memory are only read by lanes with a survivor of those in LDS; the dead rows of
+// such a lane read the first entry.
 template <int N, int NBL, int NML, int NMG, int NBG, bool WIDE = false>
 __device__ __forceinline__ void classify_rows(const FastArgs& a, const uint8_t* tab, const int32_t (&key)[NBL + NML + NMG + NBG][N],
                                               bool (&alive)[N], int32_t (&g)[N]) {
@@ -601,23 +603,23 @@ __device__ __forceinline__ void load_measures(const FastArgs& a, bool any, int64
   asm volatile("" ::: "memory");                   // (not moved behind the keys, nor these ahead)
 }
 
-// The eight fact rows of two steps: their groups and which of them survive; `there`: the steps are not past the end.
-template <int NBL, int NML, int NMG, int NBG, bool WIDE>
+// The four fact rows of each of S steps: their groups and which of them survive; `there`: the steps are not past the end.
+template <int S, int NBL, int NML, int NMG, int NBG, bool WIDE>
 __device__ __forceinline__ void rows_of(const FastArgs& a, const uint8_t* tab, const Keys<NBL + NML + NMG + NBG> (&keys)[2],
-                                        const bool (&there)[2], bool (&alive)[8], int32_t (&g)[8]) {
-  int32_t key[NBL + NML + NMG + NBG][8];
+                                        const bool (&there)[S], bool (&alive)[4 * S], int32_t (&g)[4 * S]) {
+  int32_t key[NBL + NML + NMG + NBG][4 * S];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
+  for (int q = 0; q < 4 * S; ++q) {
 #pragma unroll
     for (int k = 0; k < NBL + NML + NMG + NBG; ++k) key[k][q] = keys[q / 4].k[k][q % 4];
     key[0][q] = masked_key<WIDE>(keys[q / 4].fact_mask, q % 4, key[0][q]);
     g[q] = 0;
     alive[q] = there[q / 4];
   }
-  classify_rows<8, NBL, NML, NMG, NBG, WIDE>(a, tab, key, alive, g);
+  classify_rows<4 * S, NBL, NML, NMG, NBG, WIDE>(a, tab, key, alive, g);
 }
 
-// First pass of the bucketed form.  Per round of the workgroup (8 rows per thread): every survivor takes a
+// First pass of the bucketed form.  Per round of the workgroup (8 rows per thread, 4 in a last round of one step): every survivor takes a
 // rank inside its bucket from an LDS counter; one thread per bucket with survivors reserves that many slots
 // of the bucket with one device-wide atomic; the survivors are then written to their slots.  Workgroups take steps in turn;
 // every thread of a workgroup takes the same number of rounds (the barriers are inside the loop), rows past the end are not
@@ -625,10 +627,11 @@ __device__ __forceinline__ void rows_of(const FastArgs& a, const uint8_t* tab, c
 // A round is a chain of waits: keys, gathers from tables in memory, measures, the reservation, the stores of the round before.  The
 // gathers of a thread's eight rows go out together, and the keys of the next round behind the measures of this one.
 // 24e6 rows into 342 buckets, a table in memory, 20 % survive: 183 us with the gathers row by row, 162 so; 6e6 rows, 0.8 % survive:
-// 32.5 and 29; calls of one round, which has a second, empty step now, 1 to 2 us more (500,000 rows 21.1 -> 22.2).  With the keys of
-// the next round requested only where there is one: 168, and no gain for calls of one round.  (Slots of its own for every workgroup, without reservation and barriers: 190 us, the lines of a slot leave the L2
-// in more pieces; survivors sorted in LDS and written in runs: 180; both: 163, with the fold 6 us longer and calls of
-// 500,000 rows 20 % longer.)
+// 32.5 and 29.  With the keys of the next round requested only where there is one: 168.  A round of two steps with nothing in the second one
+// is longer than one of the first alone: the only round of 500,000 rows with it 22.5 us, without 20.7 (21.4 before the gathers went
+// out together); of 250,000 rows into 437,500 groups 34.7, 32.7 (32.7); the second round of 3e6 rows, two measures 66.2, 60.3 (62.1).
+// (Slots of its own for every workgroup, without reservation and barriers: 190 us, the lines of a slot leave the L2 in more pieces;
+// survivors sorted in LDS and written in runs: 180; both: 163, with the fold 6 us longer and calls of 500,000 rows 20 % longer.)
 template <int NBL, int NML, int NMG, int NBG, int MM, bool WIDE>
 __global__ __launch_bounds__(SCAN_THREADS) void scan_fast_bucket_kernel(FastArgs a, BucketArgs b) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -644,7 +647,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_fast_bucket_kernel(FastArgs
   Keys<ND> keys[2];
   if (n_vec > 0) {
     load_keys<ND, WIDE>(a, v, n_vec, keys[0]);
-    load_keys<ND, WIDE>(a, v + stride, n_vec, keys[1]);
+    if (v - tid + stride < n_vec) load_keys<ND, WIDE>(a, v + stride, n_vec, keys[1]);
   }
   {
     const uint4* src = reinterpret_cast<const uint4*>(a.packed);
@@ -679,29 +682,28 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_fast_bucket_kernel(FastArgs
     }
   };
 
-  // Two steps at a time: their gathers go out together, then their measures, then the keys of the next round.
-  int32_t g[8], val[MM][8];
-  unsigned int rank[8];
-  bool alive[8];
-  auto look = [&]() {
-    const bool there[2] = {v < n_vec, v + stride < n_vec};
-    rows_of<NBL, NML, NMG, NBG, WIDE>(a, tab, keys, there, alive, g);
-    v4i m4[2][MM];
+  // A round of S steps: their gathers go out together, then their measures, then the keys of the next round of two.
+  auto round = [&](auto number) {
+    constexpr int S = decltype(number)::value;
+    int32_t g[4 * S], val[MM][4 * S];
+    unsigned int rank[4 * S];
+    bool alive[4 * S], there[S];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) load_measures(a, alive[4 * s] || alive[4 * s + 1] || alive[4 * s + 2] || alive[4 * s + 3], v + s * stride, m4[s]);
+    for (int s = 0; s < S; ++s) there[s] = v + s * stride < n_vec;
+    rows_of<S, NBL, NML, NMG, NBG, WIDE>(a, tab, keys, there, alive, g);
+    v4i m4[S][MM];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) load_keys<ND, WIDE>(a, v + (2 + s) * stride, n_vec, keys[s]);
+    for (int s = 0; s < S; ++s) load_measures(a, alive[4 * s] || alive[4 * s + 1] || alive[4 * s + 2] || alive[4 * s + 3], v + s * stride, m4[s]);
+    if constexpr (S == 2) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+      for (int s = 0; s < S; ++s) load_keys<ND, WIDE>(a, v + (2 + s) * stride, n_vec, keys[s]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4 * S; ++q) {
       rank[q] = alive[q] ? atomicAdd(&count[g[q] >> b.shift], 1u) : 0u;
 #pragma unroll
       for (int m = 0; m < MM; ++m) val[m][q] = m4[q / 4][m][q % 4];
     }
-    v += 2 * stride;
-  };
-
-  while (v - tid < n_vec) {
-    look();
     __syncthreads();
     for (int i = tid; i < B; i += SCAN_THREADS) {
       const unsigned int c = count[i];
@@ -709,13 +711,15 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_fast_bucket_kernel(FastArgs
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < 4 * S; ++q) {
       int32_t x[MM];
 #pragma unroll
       for (int m = 0; m < MM; ++m) x[m] = val[m][q];
       put(alive[q], alive[q] ? base[g[q] >> b.shift] + rank[q] : 0u, g[q], x);
     }
-  }
+  };
+  for (; v - tid + stride < n_vec; v += 2 * stride) round(std::integral_constant<int, 2>{});
+  if (v - tid < n_vec) round(std::integral_constant<int, 1>{});
   // ragged tail (n % 4 rows): one row per lane, straight to memory
   if (blockIdx.x == 0) {
     const int64_t i = n_vec * 4 + tid;

@@ -389,7 +389,7 @@ def test_bucketed_many_groups_ragged_sizes_and_negative_keys(lq, n):
 def test_bucketed_many_groups_with_tables_in_memory(lq, rows, card, sel):
     """Tables too large for LDS: the reads of a thread's eight rows go out together.  Sizes around one row, a step and a round of a
     workgroup, with keys that match nothing; with one fact mask."""
-    for n in (1, 6, 4_095, 4_097, 8_193, 2_300_003):
+    for n in (1, 6, 4_095, 4_097, 8_193, 1_052_003, 2_300_003, 3_150_003):
         _check(lq, _many_groups(390 + n, n, rows, card, 1 + n % 2, sel=sel, neg=True))
     w = _many_groups(389, 50_001, rows, card, 2, sel=sel, neg=True)
     w.fact_mask = (torch.arange(w.n) % 3 != 0).to(torch.uint8)
