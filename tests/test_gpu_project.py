@@ -174,3 +174,76 @@ def test_split_products_are_as_close_as_multiply_adds(kind, k):
     for q in range(k):                                        # (the sum of an fp32 number and a product of two in float64, rounded once more)
         chain = (chain.double() + D[:, q:q + 1].double() * W[q].double()).float()
     assert float((_project(D, W).double() - exact).norm()) <= 1.1 * float((chain.double() - exact).norm())
+
+
+def _same(a, b):
+    return torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(nan=0.0), b.nan_to_num(nan=0.0))
+
+
+# Rows and outputs at which each tile of gemm_split_kernel is the chosen one (on 256 compute units; whichever it is, the bits are the same): 128 rows x 32
+# columns, x 64 (twice), x 128, and 256 x 128, this one for 64 or more columns of the table.  Rows and outputs end inside a tile, k inside a step.
+TILES = [(385, 130, 23), (45_003, 50, 31), (45_003, 200, 33), (100_003, 200, 17), (100_003, 200, 83), (65_613, 1_025, 67)]
+
+
+def _drawn(rows, outputs, k):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + outputs + k)
+    return torch.randn(rows, k, generator=gen, device="cuda"), torch.randn(k, outputs, generator=gen, device="cuda")
+
+
+def _check_parts(D, W, whole, places):
+    """Rows and columns computed alone are those of the whole, and within the bound where the sums are finite."""
+    for at in places:
+        at = max(0, min(at, D.shape[0] - 70))
+        part = D[at:at + 70].contiguous()
+        got = _project(part, W)
+        assert _same(got, whole[at:at + 70])
+        exact = part.double() @ W.double()
+        error = (got.double() - exact).abs()
+        bound = (D.shape[1] + 2) * 2.0 ** -24 * (part.double().abs() @ W.double().abs()) + D.shape[1] * 2.0 ** -149
+        finite = exact.abs() < 2.0 ** 127
+        assert bool((error[finite] <= bound[finite]).all()) and torch.equal(exact.isnan(), got.isnan())
+        assert bool((got[exact.isinf()] == exact[exact.isinf()]).all())
+    few = torch.arange(0, W.shape[1], max(1, W.shape[1] // 23), device="cuda")
+    rows = slice(places[0], places[0] + 70)
+    assert _same(_project(D[rows].contiguous(), W[:, few].contiguous()), whole[rows][:, few])
+
+
+@pytest.mark.parametrize("rows,outputs,k", TILES)
+def test_split_products_of_every_tile(rows, outputs, k):
+    D, W = _drawn(rows, outputs, k)
+    _check_parts(D, W, _project(D, W), (0, 90, 130, rows // 2, rows))
+
+
+@pytest.mark.parametrize("rows,outputs,k", TILES)
+def test_split_products_of_every_tile_outside_the_range_of_the_pieces(rows, outputs, k):
+    D, W = _drawn(rows, outputs, k)
+    W[1].clamp_(-0.9, 0.9)                                    # (3.4e38 times it stays finite, as it is in the float64 reference)
+    plain = _project(D, W)
+    inf, nan = float("inf"), float("nan")
+    middle = rows // 2
+    at = [5, 40, 131, 132, 133, middle, middle + 1, rows - 1]
+    D[5, 7], D[131, 0], D[middle, k - 1], D[rows - 1, 3] = inf, nan, -inf, inf
+    D[40, 1], D[132], D[133] = 3.4e38, 0, 0
+    D[132, 5] = 1e-42
+    D[middle + 1, 2] = inf
+    D[middle + 1, 4] = -inf                                   # (both signs: NaN)
+    got = _project(D, W)
+    same = torch.ones(rows, dtype=torch.bool, device="cuda")
+    same[at] = False
+    assert torch.equal(got[same], plain[same])
+    _check_parts(D, W, got, (0, 100, middle - 30, rows))
+    W[11, 9], W[12, 10], W[:, 17], W[3, outputs - 1], W[:, 33] = inf, nan, 0, -inf, 1e-39
+    again = _project(D, W)
+    cols = torch.ones(outputs, dtype=torch.bool, device="cuda")
+    cols[[9, 10, 17, 33, outputs - 1]] = False
+    assert _same(again[:, cols], got[:, cols])
+    _check_parts(D, W, again, (0, 100, middle - 30, rows))
+
+
+@pytest.mark.parametrize("scale_d,scale_w", [(-120, 100), (116, -116), (-130, 0), (-70, -70), (0, -125)])
+@pytest.mark.parametrize("rows,outputs,k", TILES)
+def test_split_products_of_every_tile_of_small_numbers(rows, outputs, k, scale_d, scale_w):
+    D, W = _drawn(rows, outputs, k)
+    D, W = torch.ldexp(D, torch.tensor(scale_d, device="cuda")), torch.ldexp(W, torch.tensor(scale_w, device="cuda"))
+    _check_parts(D, W, _project(D, W), (0, 90, rows // 2, rows))
