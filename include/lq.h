@@ -154,7 +154,9 @@ int lq_project_dim_rows(const lq_star* star, const lq_model* model, lq_mat* P, i
  *                  Each pipeline is priced by what it streams, gathers and multiplies per fact row at
  *                  the rates these kernels sustain on an MI355X (about 5 TB/s streamed, 14 TB/s
  *                  gathered while the tables fit the Infinity Cache and 3 TB/s in 128-byte lines
- *                  beyond it, 60 / 400 TFLOP/s fp32 / bf16 in the dense products, 4 us per launch).
+ *                  beyond it, 60 / 400 TFLOP/s fp32 / bf16 in the dense products, 200 in fp32 products
+ *                  of more than 16 columns onto more than 16 outputs outside the fused kernels, 4 us
+ *                  per launch).
  *   fuse           = 1 when queries_per_update * (seconds_no_fusion - seconds_fused) > seconds_prefusion
  */
 typedef struct {

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 // The products of the two first pieces and the five small ones have sums of their own, added at the end: a sum is rounded with every
 // instruction that adds to it, so the large one is rounded once per 16 k, and the rounding of the small ones does not show.  (All six in
 // one sum: 277 us instead of 289 at 16,555 x 683 -> 2,048 in three problems, 2,110 instead of 2,220 at 200,000 x 1,024 -> 1,024, but
-// farther off than fp32 instructions where operands are zero, which round nothing then: in the table, and a little biased.)
+// farther off than fp32 instructions where operands are zero, which round nothing there, and a little biased.)
 // Relative error in the 2-norm against float64 with fp32 instructions / one sum / so, for k = 64 and 683: normal values 1.4e-7, 1.1e-7,
 // 5.0e-8 and 4.7e-7, 4.0e-7, 1.5e-7; values in [0, 1] 1.2e-7, 8.5e-8, 4.9e-8 and 4.0e-7, 2.9e-7, 1.5e-7; normal values cut off at zero
 // 1.0e-7, 1.05e-7, 4.2e-8 and 3.3e-7, 3.8e-7, 1.2e-7; one operand of 20 not zero 4.1e-8, 6.5e-8, 2.7e-8 and 1.1e-7, 2.1e-7, 4.2e-8; a single
@@ -316,8 +316,9 @@ __global__ __launch_bounds__(TILED_THREADS, BN == 64 ? 4 : 3) void gemm_tiled_ke
 // one of eight wavefronts, which splits B half as often.  (Both operands through LDS, 64 x 64 a wavefront, in one sum: 278 instead of 271 us
 // for the former shape, 2,200 instead of 2,000 for the latter; 64 rows a wavefront and 64 columns in two sums: 309 and 2,410, 64 rows
 // and 128 columns, one wavefront a SIMD: 350 and 2,520; with fp32 instructions, one word of either operand a lane from LDS, 412 and 3,250.)
-// Large tables are bound by the matrix instructions and the splitting beside them: 1.1 PFLOP/s in bf16 operations, 1.26 in a bf16
-// product of 8,192^3 from the vendor's library; short tables by the chain of a step: load, split, LDS, products.
+// Large tables are bound by the matrix instructions and the splitting beside them: 1.1 PFLOP/s in bf16 operations, 1.26 in a bf16 product of
+// 8,192^3 from the vendor's library, 1.6 to 1.8 in these instructions alone on registers with random operands (2.0 to 2.5 on zeros);
+// short tables by the chain of a step: load, split, LDS, products.
 
 // Floats as sums of three bf16 numbers each, packed in pairs.
 template <int N>

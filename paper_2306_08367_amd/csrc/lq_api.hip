@@ -309,7 +309,7 @@ int lq_fusion_advice(const lq_star* star, const lq_model* model, double queries_
   //   in half of it, else whole 128-byte lines from memory)                    ~14 TB/s / ~3 TB/s
   //   dense products                                                           ~60 TFLOP/s fp32, ~400 bf16; 200 for fp32 products
   //   of more than 16 k and 16 columns outside the fused kernels (gemm_split_kernel).  32 -> 128 columns on 2.4e6 rows, which
-  //   decides for the non-fused pipeline: 0.42 ms measured, 0.50 so, 0.73 with 60; fused 0.51 measured, 0.52 so
+  //   decides for the non-fused pipeline: 0.43 ms measured, 0.50 so, 0.73 with 60; fused 0.52 measured, 0.52 so
   //   a kernel launch                                                          ~4 us
   const double c_f = star->fact.cols > 0 ? star->fact.cols : 0;
   const double K = star->n_dims;
